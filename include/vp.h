@@ -404,9 +404,9 @@ vp_status vp_cluster_markers(const double* Qm, const double* Pm, const double* w
  * argument.  The workspace is the library's own file-scope device array of
  * VP_CLUSTER_STATIC_BYTES (16 MiB), one per device, held until the process ends; the call
  * allocates nothing.  Same arguments, outputs and results as vp_cluster_markers (bit for
- * bit); the starting indices are checked on the device.  Refused with VP_ERR_ARG when
- * vp_cluster_workspace_bytes(m, k) exceeds VP_CLUSTER_STATIC_BYTES (400k markers into 40k
- * clusters fit).  Every call clears the part of the array it uses first.  Calls that
+ * bit); the starting indices are checked on the device.  Refused with VP_ERR_ARG when even
+ * the smallest workspace for (m, k) exceeds VP_CLUSTER_STATIC_BYTES (400k markers into 40k
+ * clusters fit; vp_cluster_workspace_bytes asks for more, with which the call is faster).  Every call clears the part of the array it uses first.  Calls that
  * overlap on one device (two streams, two threads) share the array and race: serialise
  * them.  Synchronises `stream`.  Errors: VP_ERR_ARG, VP_ERR_HIP. */
 #define VP_CLUSTER_STATIC_BYTES (16u << 20)

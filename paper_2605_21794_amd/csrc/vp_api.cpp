@@ -960,7 +960,47 @@ static vp_status cluster_check(int64_t m, int32_t k) {
 vp_status vp_cluster_workspace_bytes(int64_t m, int32_t k, size_t* bytes_out) {
   if (!bytes_out) return fail(VP_ERR_ARG, "NULL argument");
   VP_TRY(cluster_check(m, k));
-  *bytes_out = vpk::cluster_layout(m, k).total;
+  *bytes_out = vpk::cluster_layout(m, k, 0, vpk::cluster_runs(m, k)).total;
+  return VP_OK;
+}
+
+// Check the indices and the velocities on the device, then cluster, in a workspace of layout
+// lay (`runs`: see cluster_run).  name_bad: a starting index out of range is named, by a copy
+// of them all; else only their number.
+static vp_status cluster_checked(const double* Qm, const double* Pm, const double* wm, int64_t m,
+                                 int32_t k, const int32_t* init_idx, const int32_t* batch_idx,
+                                 int32_t batch, int32_t nbatch, int32_t iters, double L, void* ws,
+                                 const vpk::ClusterWs& lay, bool runs, hipStream_t s, double* Q,
+                                 double* P, double* qs, double* ps, double* psi,
+                                 int32_t* assign_out, double* absorbed_out, int32_t* n_out,
+                                 bool name_bad) {
+  vpk::ClusterCheck chk{};
+  VP_HIP(vpk::cluster_check_inputs(Pm, m, init_idx, k, batch_idx, (long long)batch * nbatch, ws,
+                                   lay, &chk, s));
+  if (chk.bad[0]) {  // every starting marker index must address a marker
+    if (!name_bad)
+      return fail(VP_ERR_ARG, "%d starting indices outside [0, %lld)", chk.bad[0], (long long)m);
+    std::vector<int32_t> idx(k);
+    VP_HIP(hipMemcpyAsync(idx.data(), init_idx, (size_t)k * sizeof(int32_t),
+                          hipMemcpyDeviceToHost, s));
+    VP_HIP(hipStreamSynchronize(s));
+    int32_t a = 0;
+    while (a < k - 1 && idx[a] >= 0 && idx[a] < m) ++a;
+    return fail(VP_ERR_ARG, "init_idx[%d] = %d outside [0, %lld)", a, idx[a], (long long)m);
+  }
+  if (chk.bad[1])
+    return fail(VP_ERR_ARG, "%d batch indices outside [0, %lld)", chk.bad[1], (long long)m);
+  if (!std::isfinite(chk.minmax[0]) || !std::isfinite(chk.minmax[1]))
+    return fail(VP_ERR_ARG, "non-finite marker velocities");
+  int res[2] = {0, 0};
+  VP_HIP(vpk::cluster_run(Qm, Pm, wm, m, k, init_idx, batch_idx, batch, nbatch, iters, L,
+                          chk.minmax[0], chk.minmax[1], ws, lay, runs, Q, P, qs, ps, psi,
+                          assign_out, absorbed_out, res, s));
+  if (runs && res[1])  // a very uneven clustering: one cluster did not fit a run
+    VP_HIP(vpk::cluster_run(Qm, Pm, wm, m, k, init_idx, batch_idx, batch, nbatch, iters, L,
+                            chk.minmax[0], chk.minmax[1], ws, lay, false, Q, P, qs, ps, psi,
+                            assign_out, absorbed_out, res, s));
+  *n_out = res[0];
   return VP_OK;
 }
 
@@ -985,27 +1025,11 @@ static vp_status cluster_impl(const double* Qm, const double* Pm, const double* 
   if (nbatch > 0 && (!batch_idx || !aligned(batch_idx, 4)))
     return fail(VP_ERR_ARG, "batch_idx NULL or misaligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  // every starting marker index must address a marker
-  std::vector<int32_t> idx(k);
-  VP_HIP(hipMemcpyAsync(idx.data(), init_idx, (size_t)k * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-  VP_HIP(hipStreamSynchronize(s));
-  for (int32_t a = 0; a < k; ++a)
-    if (idx[a] < 0 || idx[a] >= m) return fail(VP_ERR_ARG, "init_idx[%d] = %d outside [0, %lld)", a, idx[a], (long long)m);
-  const vpk::ClusterWs lay = vpk::cluster_layout(m, k, nbatch > 0 ? batch : 0);
-  if (nbatch > 0) {  // and so must every batch index
-    int bad = 0;
-    VP_HIP(vpk::cluster_count_bad(batch_idx, (long long)batch * nbatch, m, workspace, lay, &bad, s));
-    if (bad) return fail(VP_ERR_ARG, "%d batch indices outside [0, %lld)", bad, (long long)m);
-  }
-  double mm[2] = {0.0, 0.0};
-  VP_HIP(vpk::cluster_p_range(Pm, m, workspace, lay, mm, s));
-  if (!std::isfinite(mm[0]) || !std::isfinite(mm[1])) return fail(VP_ERR_ARG, "non-finite marker velocities");
-  int n = 0;
-  VP_HIP(vpk::cluster_run(Qm, Pm, wm, m, k, init_idx, batch_idx, batch, nbatch, iters, L, mm[0],
-                          mm[1], workspace, lay, Q, P, qs, ps, psi, assign_out, absorbed_out, &n,
-                          s));
-  *n_out = n;
-  return VP_OK;
+  const bool runs = vpk::cluster_runs(m, k);
+  const vpk::ClusterWs lay = vpk::cluster_layout(m, k, nbatch > 0 ? batch : 0, runs);
+  return cluster_checked(Qm, Pm, wm, m, k, init_idx, batch_idx, nbatch > 0 ? batch : 0, nbatch,
+                         iters, L, workspace, lay, runs, s, Q, P, qs, ps, psi, assign_out,
+                         absorbed_out, n_out, true);
 }
 
 vp_status vp_cluster_markers(const double* Qm, const double* Pm, const double* wm, int64_t m,
@@ -1030,29 +1054,23 @@ vp_status vp_cluster_markers_static(const double* Qm, const double* Pm, const do
   if (assign_out && !aligned(assign_out, 4)) return fail(VP_ERR_ARG, "assign_out misaligned");
   if (!(iters >= 0)) return fail(VP_ERR_ARG, "iters must be >= 0");
   if (!(L > 0.0) || !std::isfinite(L)) return fail(VP_ERR_ARG, "L must be positive and finite");
-  const vpk::ClusterWs lay = vpk::cluster_layout(m, k);
+  // the radix sort's workspace decides what is taken; the runs are used where theirs fits too
+  vpk::ClusterWs lay = vpk::cluster_layout(m, k, 0, false);
   if (lay.total > (size_t)VP_CLUSTER_STATIC_BYTES)
     return fail(VP_ERR_ARG,
                 "%lld markers into %d clusters need %zu bytes of workspace; the static workspace "
                 "holds %zu (vp_cluster_markers takes a workspace of any size)",
                 (long long)m, k, lay.total, (size_t)VP_CLUSTER_STATIC_BYTES);
+  const vpk::ClusterWs wide = vpk::cluster_layout(m, k, 0, true);
+  const bool runs = vpk::cluster_runs(m, k) && wide.total <= (size_t)VP_CLUSTER_STATIC_BYTES;
+  if (runs) lay = wide;
   void* ws = nullptr;
   VP_HIP(vpk::cluster_static_workspace(&ws));
   hipStream_t s = static_cast<hipStream_t>(stream);
   // the array keeps the previous call's contents: this call's part starts cleared
   VP_HIP(vpk::launch_fill_zero(ws, lay.total, s));
-  // every starting marker index must address a marker (counted on the device)
-  int bad = 0;
-  VP_HIP(vpk::cluster_count_bad(init_idx, k, m, ws, lay, &bad, s));
-  if (bad) return fail(VP_ERR_ARG, "%d starting indices outside [0, %lld)", bad, (long long)m);
-  double mm[2] = {0.0, 0.0};
-  VP_HIP(vpk::cluster_p_range(Pm, m, ws, lay, mm, s));
-  if (!std::isfinite(mm[0]) || !std::isfinite(mm[1])) return fail(VP_ERR_ARG, "non-finite marker velocities");
-  int n = 0;
-  VP_HIP(vpk::cluster_run(Qm, Pm, wm, m, k, init_idx, nullptr, 0, 0, iters, L, mm[0], mm[1], ws,
-                          lay, Q, P, qs, ps, psi, assign_out, nullptr, &n, s));
-  *n_out = n;
-  return VP_OK;
+  return cluster_checked(Qm, Pm, wm, m, k, init_idx, nullptr, 0, 0, iters, L, ws, lay, runs, s, Q,
+                         P, qs, ps, psi, assign_out, nullptr, n_out, false);
 }
 
 static vp_status minibatch_check(int64_t m, int32_t k, int32_t batch, int32_t nbatch) {
@@ -1068,7 +1086,7 @@ vp_status vp_cluster_minibatch_workspace_bytes(int64_t m, int32_t k, int32_t bat
                                                size_t* bytes_out) {
   if (!bytes_out) return fail(VP_ERR_ARG, "NULL argument");
   VP_TRY(minibatch_check(m, k, batch, 1));
-  *bytes_out = vpk::cluster_layout(m, k, batch).total;
+  *bytes_out = vpk::cluster_layout(m, k, batch, vpk::cluster_runs(m, k)).total;
   return VP_OK;
 }
 

@@ -167,32 +167,40 @@ inline long long radix_blocks(long long m) { return (m + kRadixChunk - 1) / kRad
 
 // Byte offsets of the regions of the caller's clustering workspace (256-byte aligned).
 // `batch` > 0 adds the mini-batch regions (absorbed weights v, the gathered batch, its
-// visiting order) for batches of that many markers (batch <= m).
+// visiting order) for batches of that many markers (batch <= m).  `runs` adds what grouping
+// the members by runs takes (cluster_run).
 struct ClusterWs {
-  size_t cq, cp, assign, cnt, off, perm, keys_a, vals_a, keys_b, vals_b, hist, hoff, cell_of, ccnt,
-      coff, ccur, clist, mm, tQ, tP, tqs, tps, tpsi, flag, pos, scan, v, bq, bp, bw, bperm, bad,
-      total;
+  size_t cq, cp, assign, cnt, off, perm, keys_a, vals_a, keys_b, vals_b, hist, hoff, origid, ccnt,
+      coff, cc, clist, mm, tQ, tP, tqs, tps, tpsi, flag, pos, scan, v, bq, bp, bw, bperm, bcnt,
+      boff, bad, sq, sp, slot, mem, sw, total;
 };
-ClusterWs cluster_layout(long long m, int k, int batch = 0);
+ClusterWs cluster_layout(long long m, int k, int batch, bool runs);
+// The clusters are small enough on average to be grouped by runs.
+bool cluster_runs(long long m, int k);
 // The library's own workspace of vp_cluster_markers_static on the current device (a file-scope
 // device array of VP_CLUSTER_STATIC_BYTES, its address looked up once per device).
 hipError_t cluster_static_workspace(void** ptr_out);
-// *host_bad = how many of the n device indices idx lie outside [0, m) (synchronises).
-hipError_t cluster_count_bad(const int* idx, long long n, long long m, void* ws,
-                             const ClusterWs& w, int* host_bad, hipStream_t s);
-// Velocity range of the markers (synchronises the stream).
-hipError_t cluster_p_range(const double* p, long long m, void* ws, const ClusterWs& w,
-                           double* host_minmax, hipStream_t s);
+// What the host needs to know of the inputs before any index is used: how many starting and
+// batch indices lie outside [0, m), and the velocity range (synchronises the stream).
+struct ClusterCheck {
+  int bad[2];
+  double minmax[2];
+};
+hipError_t cluster_check_inputs(const double* p, long long m, const int* init_idx, int k,
+                                const int* batch_idx, long long nbatch_idx, void* ws,
+                                const ClusterWs& w, ClusterCheck* host, hipStream_t s);
 // nbatch mini-batch updates (batches of `batch` marker indices, batch_idx[t * batch ..]),
-// then Lloyd iterations, final assignment, moments and compaction; *host_n = decorated
-// particles written; absorbed_out (k doubles, or NULL) = the weight each centre absorbed in
-// the batches (synchronises the stream).
+// then Lloyd iterations, final assignment, moments and compaction; absorbed_out (k doubles, or
+// NULL) = the weight each centre absorbed in the batches (synchronises the stream).
+// host_res[0] = decorated particles written.  runs: the layout has the runs' regions, and the
+// members are grouped by runs; host_res[1] then says that some cluster was too large for one
+// and the results are void (run again without).
 hipError_t cluster_run(const double* q, const double* p, const double* w, long long m, int k,
                        const int* init_idx, const int* batch_idx, int batch, int nbatch,
                        int iters, double L, double pmin, double pmax, void* ws,
-                       const ClusterWs& lay, double* Q, double* P, double* qs, double* ps,
-                       double* psi, int* assign_out, double* absorbed_out, int* host_n,
-                       hipStream_t s);
+                       const ClusterWs& lay, bool runs, double* Q, double* P, double* qs,
+                       double* ps, double* psi, int* assign_out, double* absorbed_out,
+                       int* host_res, hipStream_t s);
 
 // out[2t] = step, out[2t+1] = nonfinite of instance slots[t], t < nslots.
 hipError_t launch_slot_status(const InstDev* d_inst, const int* d_slots, int nslots,
