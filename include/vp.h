@@ -143,7 +143,7 @@ typedef enum vp_solver {
   VP_SOLVE_SCAN = 0,  /* discrete Gauss law: on the periodic P1 mesh (A Phi)_j = E_j - E_{j-1},
                          so E is a prefix sum of b~ with sum_e E_e = 0 (periodic Phi), and Phi a
                          prefix sum of -h E with sum_j Phi_j = 0; exact, O(Ng), one workgroup */
-  VP_SOLVE_FFT = 1    /* diagonalise the circulant A by an in-LDS radix-2 FFT:
+  VP_SOLVE_FFT = 1    /* diagonalise the circulant A by an in-LDS FFT:
                          Phi_m = b~_m / lambda_m, lambda_m = (2/h)(1 - cos(2 pi m / Ng)), Phi_0 = 0 */
 } vp_solver;
 

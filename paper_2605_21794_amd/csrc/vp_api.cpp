@@ -168,6 +168,10 @@ void drop_graph(vp_handle* h) {
   h->graph_len = 0;
 }
 
+// Whether an instance runs in the kernels' general instances: general options, or the FFT
+// solver (whose code only those carry).
+bool runs_general(const InstDev& d) { return d.general || d.solver == VP_SOLVE_FFT; }
+
 // Rebuild the tile list and occupied-slot list from the slots and upload them (with the
 // instance table).  Synchronises the stream (no kernel may still read the old tables).
 vp_status rebuild_tables(vp_handle* h) {
@@ -181,11 +185,11 @@ vp_status rebuild_tables(vp_handle* h) {
     if (h->slots[s].used) h->h_occ.push_back(s);
   // tiles grouped by kind, one fused launch per non-empty group and step: decorated then
   // monopole-only instances; within each, P1 then P2 elements, each without then with
-  // general options; last the instances with second moments (P2, general, decorated)
+  // general options or the FFT solver; last the instances with second moments (P2, general, decorated)
   auto group_of = [&](int s) {
     const InstDev& d = h->h_inst[s];
     if (d.k3) return kGroupMoments;
-    return (h->slots[s].cfg.monopole_only ? 4 : 0) + (d.order == 2 ? 2 : 0) + (d.general ? 1 : 0);
+    return (h->slots[s].cfg.monopole_only ? 4 : 0) + (d.order == 2 ? 2 : 0) + (runs_general(d) ? 1 : 0);
   };
   std::vector<int> order;
   for (int gi = 0; gi < kGroups; ++gi)
@@ -259,10 +263,10 @@ hipError_t fused_step(vp_handle* h, int ph) {
   for (int gi = 0; gi < kGroups; ++gi) {
     const int e_ = h->group_end[gi];
     if (e_ > b) {
-      const bool km = gi == kGroupMoments;
+      const bool km = gi == kGroupMoments, general = (gi & 1) != 0 || km;
       const hipError_t e = vpk::launch_fused(h->precision, h->tun.threads, h->d_inst, h->d_tiles,
-                                             b, e_ - b, h->tun.ppt, h->max_ng, h->any_fft, ph,
-                                             gi < 4 || km, (gi & 1) != 0 || km,
+                                             b, e_ - b, h->tun.ppt, h->max_ng,
+                                             general && h->any_fft, ph, gi < 4 || km, general,
                                              (gi & 2) != 0 || km, km, h->stream);
       if (e != hipSuccess) return e;
     }
@@ -340,10 +344,10 @@ vp_status launch_steps_graphed(vp_handle* h, int nsteps) {
 
 constexpr int kMaxPersistSteps = 1024;  // steps per cooperative launch (bounds its duration)
 
-// Some occupied slot has general options (the persistent kernel then takes their path).
+// Some occupied slot runs in the general instances (the persistent kernel then takes that one).
 bool any_general(const vp_handle* h) {
   for (int s : h->h_occ)
-    if (h->h_inst[s].general) return true;
+    if (runs_general(h->h_inst[s])) return true;
   return false;
 }
 

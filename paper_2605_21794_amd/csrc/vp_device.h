@@ -424,46 +424,125 @@ __device__ __forceinline__ double wave_excl_scan(double v, int /*lane*/) {
   return wave_incl_scan(v) - v;
 }
 
-// Radix-2 FFT by one wavefront on (re, im) in LDS, input in bit-reversed order; tw holds
-// cos/sin(2 pi k / Ng) for k < Ng/2 (LDS).
-static __device__ void fft_wave(double* re, double* im, int ng, int m, const double* tw, bool inverse,
-                         int lane) {
-  for (int s = 1; s <= m; ++s) {
-    const int half = 1 << (s - 1);
-    const int tstride = ng >> s;
-    for (int b = lane; b < (ng >> 1); b += 64) {
-      const int pos = b & (half - 1);
-      const int i0 = ((b >> (s - 1)) << s) + pos;
-      const int i1 = i0 + half;
-      const int k = pos * tstride;
-      const double c = tw[2 * k];
-      const double sn = inverse ? -tw[2 * k + 1] : tw[2 * k + 1];
-      const double xr = re[i1], xi = im[i1];
-      const double tr = c * xr + sn * xi;  // (c - i sn) (xr + i xi)
-      const double ti = c * xi - sn * xr;
-      const double ur = re[i0], ui = im[i0];
-      re[i0] = ur + tr;
-      im[i0] = ui + ti;
-      re[i1] = ur - tr;
-      im[i1] = ui - ti;
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
+struct Cplx { double re, im; };
+__device__ __forceinline__ Cplx operator+(Cplx a, Cplx b) { return {a.re + b.re, a.im + b.im}; }
+__device__ __forceinline__ Cplx operator-(Cplx a, Cplx b) { return {a.re - b.re, a.im - b.im}; }
+__device__ __forceinline__ Cplx operator*(Cplx a, Cplx b) {
+  return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
 
-static __device__ void bit_reverse_wave(double* re, double* im, int ng, int m, int lane) {
-  for (int j = lane; j < ng; j += 64) {
-    const int r = (int)(__brev((unsigned)j) >> (32 - m));
-    if (j < r) {
-      double t = re[j];
-      re[j] = re[r];
-      re[r] = t;
-      t = im[j];
-      im[j] = im[r];
-      im[r] = t;
+// x <- IDFT(il . DFT(x)) of ng real values by the whole workgroup (unscaled; the result is
+// real and lands in re).  x: the input; re, im: LDS scratch of ng doubles each; tw: cos / sin
+// of 2 pi k / ng, k < ng/2 (LDS); il4: il at the bit-reversed places 4 tid .. 4 tid + 3
+// (threads below ng/4).  The forward transform decimates in frequency (natural order in,
+// bit-reversed out) and the inverse in time, so no reordering pass is needed; two radix-2
+// levels are taken at a time, four points per thread in registers, and the innermost pair of
+// levels of both directions and the product with il are one pass.  An odd number of levels
+// takes one radix-2 level by itself at either end.  Each pass ends at a barrier: all threads
+// call this, and the result does not depend on the workgroup size.
+// Bound by its chain of passes (nine for ng = 1024), each an LDS round trip and a barrier.
+// A fused P2 step of 2^18 float64 particles at ng = 1024: 45.5 us with one wavefront taking
+// the transforms radix 2 with two reordering passes, 19.5 us so.
+template <int TPB>
+__device__ void fft_diagonal(const double* x, double* re, double* im, const double* tw, int ng,
+                             int m, const double (&il4)[4]) {
+  const int b = threadIdx.x, half = ng >> 1;
+  const bool on = b < (ng >> 2);
+  bool real_in = true;
+  int len = ng;
+  if (m & 1) {
+    for (int i = b; i < half; i += TPB) {
+      const double u = x[i], v = x[i + half], d = u - v;
+      re[i] = u + v;
+      im[i] = 0.0;
+      re[i + half] = d * tw[2 * i];
+      im[i + half] = -(d * tw[2 * i + 1]);
+    }
+    __syncthreads();
+    real_in = false;
+    len = half;
+  }
+  for (; len > 4; len >>= 2) {
+    if (on) {
+      const int q = len >> 2, pos = b & (q - 1), i = ((b - pos) << 2) + pos;
+      const int k = pos * (ng / len);
+      Cplx z[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        z[u] = real_in ? Cplx{x[i + u * q], 0.0} : Cplx{re[i + u * q], im[i + u * q]};
+      const Cplx w1{tw[2 * k], -tw[2 * k + 1]}, w2{tw[4 * k], -tw[4 * k + 1]};
+      const Cplx a0 = z[0] + z[2], a1 = z[1] + z[3], a2 = (z[0] - z[2]) * w1;
+      const Cplx d = (z[1] - z[3]) * w1, a3{d.im, -d.re};
+      z[0] = a0 + a1;
+      z[1] = (a0 - a1) * w2;
+      z[2] = a2 + a3;
+      z[3] = (a2 - a3) * w2;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        re[i + u * q] = z[u].re;
+        im[i + u * q] = z[u].im;
+      }
+    }
+    __syncthreads();
+    real_in = false;
+  }
+  if (on) {
+    const int i = 4 * b;
+    Cplx z[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) z[u] = {re[i + u], im[i + u]};
+    const Cplx a0 = z[0] + z[2], a1 = z[1] + z[3], a2 = z[0] - z[2], d = z[1] - z[3];
+    const Cplx a3{d.im, -d.re};
+    z[0] = a0 + a1;
+    z[1] = a0 - a1;
+    z[2] = a2 + a3;
+    z[3] = a2 - a3;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) z[u] = {z[u].re * il4[u], z[u].im * il4[u]};
+    const Cplx c0 = z[0] + z[1], c1 = z[0] - z[1], c2 = z[2] + z[3], e = z[2] - z[3];
+    const Cplx c3{-e.im, e.re};
+    z[0] = c0 + c2;
+    z[1] = c1 + c3;
+    z[2] = c0 - c2;
+    z[3] = c1 - c3;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      re[i + u] = z[u].re;
+      im[i + u] = z[u].im;
     }
   }
-  __builtin_amdgcn_wave_barrier();
+  __syncthreads();
+  for (len = 4; 4 * len <= ng; len <<= 2) {
+    if (on) {
+      const int q = len, pos = b & (q - 1), i = ((b - pos) << 2) + pos;
+      const int k = pos * (ng / (4 * len));
+      Cplx z[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) z[u] = {re[i + u * q], im[i + u * q]};
+      const Cplx w1{tw[2 * k], tw[2 * k + 1]}, w2{tw[4 * k], tw[4 * k + 1]};
+      const Cplx t1 = z[1] * w2, t3 = z[3] * w2;
+      const Cplx c0 = z[0] + t1, c1 = z[0] - t1, c2 = (z[2] + t3) * w1, e = (z[2] - t3) * w1;
+      const Cplx c3{-e.im, e.re};
+      z[0] = c0 + c2;
+      z[1] = c1 + c3;
+      z[2] = c0 - c2;
+      z[3] = c1 - c3;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        re[i + u * q] = z[u].re;
+        im[i + u * q] = z[u].im;
+      }
+    }
+    __syncthreads();
+  }
+  if (m & 1) {
+    for (int i = b; i < half; i += TPB) {
+      const double u = re[i], t = tw[2 * i] * re[i + half] - tw[2 * i + 1] * im[i + half];
+      re[i] = u + t;
+      re[i + half] = u - t;
+    }
+    __syncthreads();
+  }
 }
 
 // ------------------------------------------------------------------ Poisson solve
@@ -629,7 +708,8 @@ __device__ __forceinline__ double solve_total(const double* red, int slot) {
 // and, with want_sum, sum[0..2] = W = (1/2) h sum_e E_e^2 and
 // E1 = (1/Ng) sum_e E_e exp(-2 pi i e / Ng), sum[3..6] = K, momentum, charge, U of the
 // previous pass (its per-tile sums in tile order), in every thread.
-// `fft` is LDS scratch of 3 Ng doubles (FFT solver only).  All threads of the workgroup call
+// `fft` is LDS scratch of 3 Ng doubles (FFT solver only).  The FFT is compiled into the GEN
+// instances alone (its registers would cost the scan solver's instances a wave per SIMD).  All threads of the workgroup call
 // it (it holds workgroup barriers; want_sum must be uniform); on return bt, E, g (and phi)
 // are visible to all threads.
 // P2 elements (GEN only): the background n0 = sum(b) / L is subtracted against each basis
@@ -650,7 +730,7 @@ __device__ void solve_compute(const InstDev& d, const SolveIn& in, bool want_sum
   const int per = solve_per(ng), j0 = tid * per;
   const bool solver_thread = tid < kSolveThreads;           // whole waves
   const bool act = solver_thread && j0 < ng;
-  const bool use_fft = d.solver == VP_SOLVE_FFT;
+  const bool use_fft = GEN && d.solver == VP_SOLVE_FFT;
   const bool p2 = P2 && d.order == 2;
 
   double part = 0.0;
@@ -672,9 +752,14 @@ __device__ void solve_compute(const InstDev& d, const SolveIn& in, bool want_sum
       if constexpr (GEN) solve_wave_total(in.kin[3], red, 9);
     }
   }
-  if (use_fft) {  // twiddles for the wavefront FFT
+  double il4[4] = {0.0, 0.0, 0.0, 0.0};
+  if (use_fft) {  // twiddles, and this thread's inverse eigenvalues in bit-reversed places
     const VPG double* tw_g = gp(d.tw);
     for (int j = tid; j < ng; j += TPB) fft[2 * ng + j] = tw_g[j];
+    const VPG double* il_g = gp(d.inv_lam);
+    if (tid < (ng >> 2))
+#pragma unroll
+      for (int u = 0; u < 4; ++u) il4[u] = il_g[__brev((unsigned)(4 * tid + u)) >> (32 - d.log2ng)];
   }
   __syncthreads();
   const double inv_ng = inv_pow2(d.log2ng);  // ng is a power of two
@@ -738,34 +823,13 @@ __device__ void solve_compute(const InstDev& d, const SolveIn& in, bool want_sum
     }
   } else {
     __syncthreads();  // b~ and the twiddles in LDS
-    if (tid < 64) {
-      double* re = fft;
-      double* im = fft + ng;
-      const double* tw = fft + 2 * ng;
-      const int m = d.log2ng;
-      for (int j = lane; j < ng; j += 64) {
-        re[j] = bt[j];
-        im[j] = 0.0;
-      }
-      __builtin_amdgcn_wave_barrier();
-      bit_reverse_wave(re, im, ng, m, lane);
-      fft_wave(re, im, ng, m, tw, false, lane);
-      const VPG double* il_g = gp(d.inv_lam);
-      for (int k = lane; k < ng; k += 64) {
-        const double il = il_g[k];
-        re[k] = re[k] * il;
-        im[k] = im[k] * il;
-      }
-      __builtin_amdgcn_wave_barrier();
-      bit_reverse_wave(re, im, ng, m, lane);
-      fft_wave(re, im, ng, m, tw, true, lane);
-      for (int j = lane; j < ng; j += 64) re[j] = re[j] * inv_ng;  // Phi
-      __builtin_amdgcn_wave_barrier();
-      const double inv_h = d.inv_h;
-      for (int e = lane; e < ng; e += 64) {
-        E[e] = -(re[(e + 1) & mask] - re[e]) * inv_h;
-        if (phi) phi[e] = re[e];
-      }
+    double* re = fft;
+    fft_diagonal<TPB>(bt, re, fft + ng, fft + 2 * ng, ng, d.log2ng, il4);
+    const double inv_h = d.inv_h;
+    for (int e = tid; e < ng; e += TPB) {
+      const double p0 = re[e] * inv_ng, p1 = re[(e + 1) & mask] * inv_ng;  // Phi
+      E[e] = -(p1 - p0) * inv_h;
+      if (phi) phi[e] = p0;
     }
     if (want_sum) {
       __syncthreads();  // E complete
@@ -787,7 +851,7 @@ __device__ void solve_compute(const InstDev& d, const SolveIn& in, bool want_sum
     }
   }
   // g below reads only b~, complete since the scan's barrier (the FFT path's first): this
-  // barrier is for the summary totals, the FFT's E (written by one wave) and phi
+  // barrier is for the summary totals, the FFT's E and phi
   if (want_sum || use_fft || phi) __syncthreads();  // bt, E and the summary totals complete
   if (want_sum) {
     sum[0] = 0.5 * d.h * solve_total(red, 3);

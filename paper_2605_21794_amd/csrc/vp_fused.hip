@@ -11,8 +11,8 @@ namespace vpk {
 
 // DIP = false: every tile of the launch belongs to a monopole-only instance; p* and q* are
 // neither read nor written (20 bytes of particle traffic per update instead of 36).
-// GEN = false: no instance of the launch has general options (d.general), so the field on a
-// particle is read straight from the mesh arrays.  P2 = true: the launch's instances have P2
+// GEN = false: no instance of the launch has general options (d.general) or the FFT solver, so
+// the field on a particle is read straight from the mesh arrays.  P2 = true: the launch's instances have P2
 // elements (separate instances keep the others' registers as they were).
 template <int MODE, int TPB, bool DIP, bool GEN, bool P2, bool KM = false>
 __global__ __launch_bounds__(TPB) void k_fused(const InstDev* __restrict__ insts,

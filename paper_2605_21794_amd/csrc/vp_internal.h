@@ -121,7 +121,8 @@ size_t particle_lds_bytes(int mode, int max_ng);
 
 // `lds_fft` is true when some instance of the launch uses the FFT solver (more LDS);
 // `dipoles` false when every tile of the launch is of a monopole-only instance; `general`
-// true when some instance of the launch has general options (InstDev::general); `p2` true
+// true when some instance of the launch has general options (InstDev::general) or the FFT
+// solver (with lds_fft, general must hold); `p2` true
 // when its instances have P2 elements; `moments` true when its instances carry second
 // moments (InstDev::k3; then dipoles, general and p2 hold too).
 hipError_t launch_fused(int mode, int tpb, const InstDev* d_inst, const Tile* d_tiles, int tile0,
@@ -144,8 +145,8 @@ hipError_t launch_diag(int mode, int tpb, const InstDev* d_inst, const Tile* d_t
 // Persistent form of the fused step: nsteps steps in one cooperative launch, the particles
 // of each tile held in registers between steps (ppt per thread, 2, 4 or 8).  Every tile of
 // the launch must be resident at once: persist_capacity gives how many workgroups can be.
-// `general`: some instance of the launch has general options (InstDev::general); `p2`:
-// some instance has P2 elements (never with second moments).
+// `general`: some instance of the launch has general options (InstDev::general) or the FFT
+// solver; `p2`: some instance has P2 elements (never with second moments).
 hipError_t launch_persist(int mode, int tpb, int ppt, const InstDev* d_inst, const Tile* d_tiles,
                           int ntiles, int max_ng, bool lds_fft, bool general, bool p2, int phase,
                           int nsteps, hipStream_t s);

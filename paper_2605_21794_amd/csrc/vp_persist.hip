@@ -28,7 +28,8 @@ namespace vpk {
 // LDS once per launch, and issues the loads of the previous pass's per-tile kinetic sums
 // together with the solve's loads, parking the per-thread partials in LDS after the solve
 // (device-scope loads after the arrival would hold it past the others' release).
-// GEN = false: no instance of the launch has general options (fewer registers).
+// GEN = false: no instance of the launch has general options or the FFT solver (fewer
+// registers).
 
 // The first tile's bookkeeping after step n, by its first wavefront alone (no workgroup
 // barrier, so the tile's other waves go on to the next step's wait): the field summary of
@@ -96,8 +97,16 @@ __device__ void persist_bookkeeping(const InstDev& d, const double* fE, const do
   rec[2] = e1i;
 }
 
+// Wavefronts per SIMD the registers must leave room for: two workgroups per CU at 512 x 2, and
+// at 512 x 4 for the float32 state with float64 sums and P1 elements (the number of tiles a
+// launch can hold is part of what persistent tuning accepts); else one.
+template <int MODE, int TPB, int PPT, bool P2>
+constexpr int persist_waves() {
+  return TPB == 1024 || PPT == 2 || (PPT == 4 && MODE == kFP32Comp && !P2) ? 4 : 2;
+}
+
 template <int MODE, int TPB, int PPT, bool GEN, bool P2>
-__global__ __launch_bounds__(TPB) void k_persist(const InstDev* __restrict__ insts,
+__global__ __launch_bounds__(TPB, (persist_waves<MODE, TPB, PPT, P2>())) void k_persist(const InstDev* __restrict__ insts,
                                                  const Tile* __restrict__ tiles, int phase0,
                                                  int nsteps) {
   extern __shared__ double smem[];
