@@ -184,7 +184,9 @@ typedef struct vp_tuning {
   int32_t threads;      /* threads per workgroup of the particle kernels: 256, 512 or 1024 */
   int32_t ppt;          /* particles per thread per tile: 1, 2, 4, 8, 16, 32 or 64 */
   int32_t acc_copies;   /* copies of each instance's global load accumulator, 1..8 */
-  int32_t use_graph;    /* 1: vp_step replays captured HIP graphs; 0: direct launches */
+  int32_t use_graph;    /* 1: vp_step replays captured HIP graphs (captured by vp_prepare_step,
+                         * or once the slots and the tuning have stood for several graph
+                         * lengths of steps; launched directly before); 0: direct launches */
   int32_t graph_steps;  /* steps per captured graph, 1..256 (rounded up to a multiple of 3) */
   int32_t persistent;   /* 1: vp_step runs many steps per cooperative launch with every tile's
                          * particles held in registers between steps (threads 512 or 1024,

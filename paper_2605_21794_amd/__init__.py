@@ -234,12 +234,15 @@ class Engine:
         cfg = make_config(n, ng, L_, dt, self.prec, sort_every, sort_chunk, hist_cap, solver,
                           projection, monopole_only, self_field, external, element_order,
                           moment_order)
-        ws = t.zeros(workspace_bytes(cfg), dtype=t.uint8, device=self.device)
+        ws = t.empty(workspace_bytes(cfg), dtype=t.uint8, device=self.device)
         if ws.data_ptr() % 256:
             raise RuntimeError("workspace allocation is not 256-byte aligned")
         parts = L.vp_particles(*(c_void_p(tens[k].data_ptr() if k in tens else None)
                                  for k in FIELDS + MOMENTS))
-        t.cuda.current_stream(self.device).synchronize()
+        # the copies above ran on the current stream
+        cur = t.cuda.current_stream(self.device)
+        if cur.cuda_stream != self.stream.cuda_stream:
+            cur.synchronize()
         L.check(self.lib.vp_admit(self.h, int(slot), byref(cfg), parts, c_void_p(ws.data_ptr())),
                 "vp_admit")
         self.slots[int(slot)] = {"tensors": tens, "ws": ws, "cfg": cfg}

@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <cmath>
 #include <cstdarg>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -111,8 +112,21 @@ struct Slot {
   int tile_begin = 0, ntiles = 0;
   long long step = 0;   // host mirror of the device step counter
   bool pending = false; // host mirror of the pending half-kick
+  bool solved = false;  // the field arrays (and the record owed) are those of the live ring entry
   long long last_sort = -1;
 };
+
+// What the FFT tables of a mesh of ng elements share whatever its L.
+struct MeshTables {
+  std::vector<double> tw;     // cos, sin of 2 pi k / ng, k < ng/2
+  std::vector<double> omc;    // 1 - cos(2 pi m / ng)
+  std::vector<double> taps;   // taps of circ(1, 4, 1)^-1 (see vp_admit)
+};
+
+// The scalars of an instance that the host reads: what lies before the barrier's counters.
+static_assert(sizeof(InstDev) % 8 == 0 && sizeof(Tile) % 8 == 0, "uploaded in 64-bit words");
+constexpr size_t kScalHead = offsetof(vpk::InstScal, arrive);
+constexpr size_t kArenaBytes = 256u << 10;  // pinned staging of the table uploads
 
 }  // namespace
 
@@ -124,9 +138,15 @@ struct vp_handle {
   std::vector<InstDev> h_inst;
   std::vector<Tile> h_tiles;
   std::vector<int> h_occ;
-  InstDev* d_inst = nullptr;
+  InstDev* d_inst = nullptr;  // one allocation holds d_inst, d_status, d_occ and d_ids
   Tile* d_tiles = nullptr;
   size_t tiles_cap = 0;
+  std::vector<Tile> up_tiles;  // what d_tiles and d_occ hold (once the stream gets there)
+  std::vector<int> up_occ;
+  char* arena = nullptr;      // pinned host memory that uploads in flight read from
+  size_t arena_bytes = 0, arena_off = 0;
+  MeshTables mesh[11];        // by log2 of ng, made when first needed
+  long long steps_since_tables = 0;  // steps run since the tables last changed
   int ntiles = 0;
   int ntiles_dip = 0;      // tiles of decorated instances
   // tile ranges by kind: decorated / monopole-only x P1 / P2 x without / with general
@@ -172,11 +192,107 @@ void drop_graph(vp_handle* h) {
 // solver (whose code only those carry).
 bool runs_general(const InstDev& d) { return d.general || d.solver == VP_SOLVE_FFT; }
 
-// Rebuild the tile list and occupied-slot list from the slots and upload them (with the
-// instance table).  Synchronises the stream (no kernel may still read the old tables).
-vp_status rebuild_tables(vp_handle* h) {
+// Wait for the stream; every upload has then read its part of the arena.
+vp_status sync_stream(vp_handle* h) {
   VP_HIP(hipStreamSynchronize(h->stream));
+  h->arena_off = 0;
+  return VP_OK;
+}
+
+// Room in the arena for the parts of one upload: `extra` bytes and the tables of the slots in
+// use.  Waits for the stream when what earlier uploads may still read fills it.
+vp_status arena_reserve(vp_handle* h, size_t extra) {
+  const long long tile_n = (long long)h->tun.threads * h->tun.ppt;
+  size_t tiles = 0, slots = 0;
+  for (int s = 0; s < h->max_slots; ++s)
+    if (h->slots[s].used) {
+      tiles += (size_t)((h->slots[s].cfg.n + tile_n - 1) / tile_n);
+      slots = s + 1;
+    }
+  const size_t bytes = extra + tiles * sizeof(Tile) + slots * (sizeof(InstDev) + sizeof(int)) +
+                       sizeof(InstDev) + 5 * 256;
+  if (h->arena_off + bytes <= h->arena_bytes) return VP_OK;
+  VP_TRY(sync_stream(h));
+  if (bytes <= h->arena_bytes) return VP_OK;
+  if (h->arena) VP_HIP(hipHostFree(h->arena));
+  h->arena = nullptr;
+  h->arena_bytes = 0;
+  VP_HIP(hipHostMalloc(reinterpret_cast<void**>(&h->arena), 2 * bytes, hipHostMallocDefault));
+  h->arena_bytes = 2 * bytes;
+  return VP_OK;
+}
+
+// `bytes` of the reserved room; they stay as written until the stream has been waited for.
+char* arena_take(vp_handle* h, size_t bytes) {
+  char* p = h->arena + h->arena_off;
+  h->arena_off += (bytes + 255) & ~size_t(255);
+  return p;
+}
+
+// Add to u the upload of new_[0..n) over device array d, which holds old: the elements from
+// the first that differs on (an admission or a retirement leaves the tiles before it alone).
+// Elements are whole 64-bit words, or 32-bit ones in an array padded to 64 bits.
+template <typename E>
+void add_upload(vp_handle* h, vpk::UploadArgs& u, E* d, std::vector<E>& old,
+                const std::vector<E>& new_) {
+  size_t i = 0;
+  const size_t n = new_.size();
+  while (i < n && i < old.size() && std::memcmp(&old[i], &new_[i], sizeof(E)) == 0) ++i;
+  i &= ~size_t(1);
+  if (i < n) {
+    const size_t bytes = ((n - i) * sizeof(E) + 7) & ~size_t(7);
+    char* p = arena_take(h, bytes);
+    std::memset(p + bytes - 8, 0, 8);
+    std::memcpy(p, &new_[i], (n - i) * sizeof(E));
+    u.seg[u.nseg++] = {d + i, p, bytes / 8};
+  }
+  old = new_;
+}
+
+// Device memory read back to the host (whole 64-bit words).
+struct ReadPart {
+  void* host;
+  const void* dev;
+  size_t bytes;
+};
+
+// The parts, n of them (at most six), after everything enqueued before; waits for the stream.
+// One launch writes them all into pinned memory (a copy of its own for each takes about 10 us
+// of host time); large ones, whose bytes count, are left to the copy engines.
+vp_status read_back(vp_handle* h, const ReadPart* parts, int n) {
+  size_t total = 0;
+  for (int k = 0; k < n; ++k) total += (parts[k].bytes + 255) & ~size_t(255);
+  if (total > kArenaBytes) {
+    for (int k = 0; k < n; ++k)
+      VP_HIP(hipMemcpyAsync(parts[k].host, parts[k].dev, parts[k].bytes, hipMemcpyDeviceToHost,
+                            h->stream));
+    return sync_stream(h);
+  }
+  VP_TRY(arena_reserve(h, total));
+  char* at[6] = {};
+  vpk::UploadArgs u{};
+  for (int k = 0; k < n; ++k) {
+    at[k] = arena_take(h, parts[k].bytes);
+    u.seg[u.nseg++] = {at[k], parts[k].dev, parts[k].bytes / 8};
+  }
+  VP_HIP(vpk::launch_upload(u, h->stream));
+  VP_TRY(sync_stream(h));
+  for (int k = 0; k < n; ++k) std::memcpy(parts[k].host, at[k], parts[k].bytes);
+  return VP_OK;
+}
+
+// Rebuild the tile list and occupied-slot list from the slots and upload what changed in them,
+// with the parts already in u (the arena is reserved) and the instance table (slot `only`, or
+// every slot in use for -1).  The stream orders the upload behind the launches that read the
+// old tables; it is waited for only where graphs in flight have to be dropped.  fold: the tiles
+// or the number of accumulator copies of slots with a history may have changed (an admission
+// and a retirement leave the other slots' as they are).
+vp_status rebuild_tables(vp_handle* h, vpk::UploadArgs u, int only, bool fold) {
+  bool graphs = h->gexec != nullptr;
+  for (int p = 0; p < vpk::kRing; ++p) graphs = graphs || h->step_exec[p];
+  if (graphs) VP_HIP(hipStreamSynchronize(h->stream));
   drop_graph(h);
+  h->steps_since_tables = 0;
   const int tile_n = h->tun.threads * h->tun.ppt;
   h->h_tiles.clear();
   h->h_occ.clear();
@@ -225,25 +341,30 @@ vp_status rebuild_tables(vp_handle* h) {
   h->any_fft = false;
   for (int s : h->h_occ) h->any_fft = h->any_fft || h->slots[s].cfg.solver == VP_SOLVE_FFT;
   if ((size_t)h->ntiles > h->tiles_cap) {
+    VP_HIP(hipStreamSynchronize(h->stream));
     if (h->d_tiles) VP_HIP(hipFree(h->d_tiles));
     h->d_tiles = nullptr;
+    h->tiles_cap = 0;
+    h->up_tiles.clear();
     size_t cap = std::max<size_t>(1024, (size_t)h->ntiles * 2);
     VP_HIP(hipMalloc(&h->d_tiles, cap * sizeof(Tile)));
     h->tiles_cap = cap;
   }
-  if (h->ntiles > 0)
-    VP_HIP(hipMemcpyAsync(h->d_tiles, h->h_tiles.data(), h->ntiles * sizeof(Tile),
-                          hipMemcpyHostToDevice, h->stream));
-  if (!h->h_occ.empty())
-    VP_HIP(hipMemcpyAsync(h->d_occ, h->h_occ.data(), h->h_occ.size() * sizeof(int),
-                          hipMemcpyHostToDevice, h->stream));
-  VP_HIP(hipMemcpyAsync(h->d_inst, h->h_inst.data(), h->max_slots * sizeof(InstDev),
-                        hipMemcpyHostToDevice, h->stream));
-  // the number of accumulator copies may have changed: fold the live ring entry into copy 0
+  const int i0 = only < 0 ? 0 : only, in = only < 0 ? (h->h_occ.empty() ? 0 : h->h_occ.back() + 1) : 1;
+  if (in > 0) {
+    char* p = arena_take(h, in * sizeof(InstDev));
+    std::memcpy(p, &h->h_inst[i0], in * sizeof(InstDev));
+    u.seg[u.nseg++] = {h->d_inst + i0, p, in * sizeof(InstDev) / 8};
+  }
+  add_upload(h, u, h->d_tiles, h->up_tiles, h->h_tiles);
+  add_upload(h, u, h->d_occ, h->up_occ, h->h_occ);
+  VP_HIP(vpk::launch_upload(u, h->stream));
+  if (!fold) return VP_OK;
+  // the live ring entry of every slot into copy 0
+  for (int s : h->h_occ) h->slots[s].solved = false;
   VP_HIP(vpk::launch_ring(h->precision, h->d_inst, h->d_occ, (int)h->h_occ.size(), vpk::kRingFold,
                           h->phase, h->stream));
-  VP_HIP(hipStreamSynchronize(h->stream));
-  return VP_OK;
+  return sync_stream(h);
 }
 
 vp_status check_slot(const vp_handle* h, int slot) {
@@ -343,6 +464,7 @@ vp_status launch_steps_graphed(vp_handle* h, int nsteps) {
 }
 
 constexpr int kMaxPersistSteps = 1024;  // steps per cooperative launch (bounds its duration)
+constexpr int kCaptureAfter = 8;        // graph lengths of steps before graphs are captured
 
 // Some occupied slot runs in the general instances (the persistent kernel then takes that one).
 bool any_general(const vp_handle* h) {
@@ -378,7 +500,17 @@ vp_status advance_persistent(vp_handle* h, int k) {
 // one-step replays for the rest; direct launches with graphs off.
 vp_status advance(vp_handle* h, int k) {
   if (h->tun.persistent) return advance_persistent(h, k);
-  const bool graphs = h->tun.use_graph && h->stream != nullptr;
+  bool graphs = h->tun.use_graph && h->stream != nullptr;
+  // A capture holds the first step back by 5 to 6 us per captured step, and replayed steps are
+  // no shorter than launched ones (the host launches one in 2.5 us, the GPU takes 8 or more):
+  // steps are launched directly until the tables have stood long enough to pay for it, so an
+  // engine that admits and retires every few dozen steps captures nothing.
+  h->steps_since_tables += k;
+  if (!h->graph_ok && h->steps_since_tables < kCaptureAfter * graph_len_of(h)) {
+    bool any = false;
+    for (int p = 0; p < vpk::kRing; ++p) any = any || h->step_exec[p];
+    graphs = graphs && any;
+  }
   if (!graphs) return launch_steps_direct(h, k);
   if (k >= graph_len_of(h)) {
     VP_TRY(ensure_graph(h));  // captured at the current phase if there was none
@@ -404,7 +536,16 @@ vp_status materialise(vp_handle* h, const int* d_slots, int nslots) {
 
 vp_status materialise_all(vp_handle* h) {
   VP_TRY(materialise(h, h->d_occ, (int)h->h_occ.size()));
+  for (int s : h->h_occ) h->slots[s].solved = true;
   h->field_stale = false;
+  return VP_OK;
+}
+
+// The same for one slot, unless its arrays are those of its live ring entry already.
+vp_status materialise_slot(vp_handle* h, int slot) {
+  if (h->slots[slot].solved) return VP_OK;
+  VP_TRY(materialise(h, h->d_ids + slot, 1));
+  h->slots[slot].solved = true;
   return VP_OK;
 }
 
@@ -415,10 +556,36 @@ vp_status deposit_all(vp_handle* h) {
   VP_HIP(vpk::launch_deposit(h->precision, h->tun.threads, h->d_inst, h->d_tiles, 0, h->ntiles, h->tun.ppt,
                              h->max_ng, h->phase, h->stream));
   h->acc_stale = false;
+  for (int s : h->h_occ) h->slots[s].solved = false;
   return VP_OK;
 }
 
 int sort_chunk_of(const vp_config& c) { return c.sort_chunk > 0 ? c.sort_chunk : max_sort_chunk(c.precision); }
+
+// The tables of meshes of ng elements.  Taps: on the infinite mesh circ(1, 4, 1)^-1 has entries
+// r^|d| / (2 sqrt 3), r = sqrt 3 - 2 (the root of x^2 + 4x + 1 inside the unit circle); summing
+// the periodic images gives entry (r^k + r^(Ng-k)) / ((1 - r^Ng) 2 sqrt 3) at circular offset k.
+const MeshTables& mesh_tables(vp_handle* h, int ng) {
+  MeshTables& mt = h->mesh[ilog2(ng)];
+  if (!mt.tw.empty()) return mt;
+  const double two_pi = 6.283185307179586;
+  mt.tw.resize(ng);
+  mt.omc.resize(ng);
+  for (int k = 0; k < ng / 2; ++k) {
+    mt.tw[2 * k] = std::cos(two_pi * k / ng);
+    mt.tw[2 * k + 1] = std::sin(two_pi * k / ng);
+  }
+  for (int m = 0; m < ng; ++m) mt.omc[m] = 1.0 - std::cos(two_pi * m / ng);
+  const double r = std::sqrt(3.0) - 2.0, a = 1.0 / (2.0 * std::sqrt(3.0));
+  const double rn = std::pow(r, ng);
+  const int taps = vpk::cons_taps(ng), off = vpk::cons_off(ng);
+  mt.taps.resize(taps);
+  for (int t = 0; t < taps; ++t) {
+    const int k = ((t + off) % ng + ng) % ng;
+    mt.taps[t] = a * (std::pow(r, k) + std::pow(r, ng - k)) / (1.0 - rn);
+  }
+  return mt;
+}
 
 void to_diag(const double* r, vp_diag* o) {
   o->step = (int64_t)r[0];
@@ -503,10 +670,19 @@ vp_status vp_engine_create(int32_t precision, int32_t max_slots, void* stream, v
   }
   std::vector<int> ids(max_slots);
   for (int i = 0; i < max_slots; ++i) ids[i] = i;
-  hipError_t e = hipMalloc(&h->d_inst, max_slots * sizeof(InstDev));
-  if (e == hipSuccess) e = hipMalloc(&h->d_occ, max_slots * sizeof(int));
-  if (e == hipSuccess) e = hipMalloc(&h->d_ids, max_slots * sizeof(int));
-  if (e == hipSuccess) e = hipMalloc(&h->d_status, 2 * (size_t)max_slots * sizeof(long long));
+  auto pad = [](size_t b) { return (b + 255) & ~size_t(255); };
+  const size_t bi = pad(max_slots * sizeof(InstDev)), bst = pad(2 * (size_t)max_slots * sizeof(long long)),
+               bo = pad(max_slots * sizeof(int));
+  char* block = nullptr;
+  hipError_t e = hipMalloc(&block, bi + bst + 2 * bo);
+  if (e == hipSuccess) {
+    h->d_inst = reinterpret_cast<InstDev*>(block);
+    h->d_status = reinterpret_cast<long long*>(block + bi);
+    h->d_occ = reinterpret_cast<int*>(block + bi + bst);
+    h->d_ids = reinterpret_cast<int*>(block + bi + bst + bo);
+    e = hipHostMalloc(reinterpret_cast<void**>(&h->arena), kArenaBytes, hipHostMallocDefault);
+    if (e == hipSuccess) h->arena_bytes = kArenaBytes;
+  }
   if (e == hipSuccess)
     e = hipMemcpyAsync(h->d_ids, ids.data(), max_slots * sizeof(int), hipMemcpyHostToDevice, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
@@ -577,45 +753,6 @@ vp_status vp_admit(vp_handle* h, int32_t slot, const vp_config* cfg, vp_particle
   d.kin = reinterpret_cast<double*>(ws + w.kin);
   d.kin_cap = vpk::kin_capacity(cfg->n);
 
-  // FFT twiddles and inverse stiffness eigenvalues lambda_m = (2/h)(1 - cos(2 pi m / Ng)).
-  const int ng = cfg->ng;
-  std::vector<double> tw(ng), il(ng);
-  const double two_pi = 6.283185307179586;
-  for (int k = 0; k < ng / 2; ++k) {
-    tw[2 * k] = std::cos(two_pi * k / ng);
-    tw[2 * k + 1] = std::sin(two_pi * k / ng);
-  }
-  il[0] = 0.0;
-  for (int m = 1; m < ng; ++m) il[m] = 1.0 / ((2.0 / d.h) * (1.0 - std::cos(two_pi * m / ng)));
-  // Taps of -M^-1 for the consistent projection, M = (h/6) circ(1, 4, 1).  On the infinite
-  // mesh circ(1, 4, 1)^-1 has entries r^|d| / (2 sqrt 3), r = sqrt 3 - 2 (the root of
-  // x^2 + 4x + 1 inside the unit circle); summing the periodic images gives entry
-  // (r^k + r^(Ng-k)) / ((1 - r^Ng) 2 sqrt 3) at circular offset k.
-  std::vector<double> cw(vpk::kConsTapsMax, 0.0);
-  {
-    const double r = std::sqrt(3.0) - 2.0, a = 1.0 / (2.0 * std::sqrt(3.0));
-    const double rn = std::pow(r, ng);
-    const int taps = vpk::cons_taps(ng), off = vpk::cons_off(ng);
-    for (int t = 0; t < taps; ++t) {
-      const int k = ((t + off) % ng + ng) % ng;
-      const double c = a * (std::pow(r, k) + std::pow(r, ng - k)) / (1.0 - rn);
-      cw[t] = -(6.0 / d.h) * c;
-    }
-  }
-
-  VP_HIP(hipStreamSynchronize(h->stream));
-  VP_HIP(vpk::launch_fill_zero(ws, w.total, h->stream));
-  VP_HIP(hipMemcpyAsync(d.tw, tw.data(), ng * sizeof(double), hipMemcpyHostToDevice, h->stream));
-  VP_HIP(hipMemcpyAsync(d.inv_lam, il.data(), ng * sizeof(double), hipMemcpyHostToDevice, h->stream));
-  VP_HIP(hipMemcpyAsync(d.cw, cw.data(), cw.size() * sizeof(double), hipMemcpyHostToDevice,
-                        h->stream));
-  if (cfg->monopole_only) {  // p* = q* = 0 from the start
-    const size_t bytes = (size_t)cfg->n * state_elem_size(cfg->precision);
-    VP_HIP(vpk::launch_fill_zero(parts.qs, bytes, h->stream));
-    VP_HIP(vpk::launch_fill_zero(parts.ps, bytes, h->stream));
-  }
-  VP_HIP(hipStreamSynchronize(h->stream));
-
   Slot& sl = h->slots[slot];
   sl.used = true;
   sl.cfg = *cfg;
@@ -623,18 +760,48 @@ vp_status vp_admit(vp_handle* h, int32_t slot, const vp_config* cfg, vp_particle
   sl.ws = workspace;
   sl.step = 0;
   sl.pending = false;
+  sl.solved = false;
   sl.last_sort = -1;
   h->h_inst[slot] = d;
-  vp_status st = rebuild_tables(h);
+
+  // FFT twiddles, inverse stiffness eigenvalues lambda_m = (2/h)(1 - cos(2 pi m / Ng)), and the
+  // taps of -M^-1 for the consistent projection, M = (h/6) circ(1, 4, 1): three neighbouring
+  // regions of the workspace, in one part of the upload.
+  const int ng = cfg->ng;
+  const MeshTables& mt = mesh_tables(h, ng);
+  const size_t tab_bytes = w.scal - w.tw;
+  const vp_status room = arena_reserve(h, tab_bytes);
+  if (room != VP_OK) {
+    sl.used = false;
+    return room;
+  }
+  char* tab = arena_take(h, tab_bytes);
+  std::memset(tab, 0, tab_bytes);
+  std::memcpy(tab, mt.tw.data(), ng * sizeof(double));
+  double* il = reinterpret_cast<double*>(tab + (w.inv_lam - w.tw));
+  for (int m = 1; m < ng; ++m) il[m] = 1.0 / ((2.0 / d.h) * mt.omc[m]);
+  double* cw = reinterpret_cast<double*>(tab + (w.cw - w.tw));
+  for (int t = 0; t < vpk::cons_taps(ng); ++t) cw[t] = -(6.0 / d.h) * mt.taps[t];
+  vpk::UploadArgs u{};
+  u.seg[u.nseg++] = {ws + w.tw, tab, tab_bytes / 8};
+  u.zero[u.nzero++] = {ws, nullptr, w.tw / 8};
+  u.zero[u.nzero++] = {ws + w.scal, nullptr, (w.total - w.scal) / 8};
+  if (cfg->monopole_only) {  // p* = q* = 0 from the start
+    const size_t bytes = (size_t)cfg->n * state_elem_size(cfg->precision);
+    VP_HIP(vpk::launch_fill_zero(parts.qs, bytes, h->stream));
+    VP_HIP(vpk::launch_fill_zero(parts.ps, bytes, h->stream));
+  }
+
+  vp_status st = rebuild_tables(h, u, slot, false);
   if (st != VP_OK) {
     sl.used = false;
+    (void)hipStreamSynchronize(h->stream);  // the caller's buffers are free again
     return st;
   }
   // Load vector and field at t = 0 from the initial state (the ring entries start cleared).
   VP_HIP(vpk::launch_deposit(h->precision, h->tun.threads, h->d_inst, h->d_tiles, sl.tile_begin, sl.ntiles,
                              h->tun.ppt, h->max_ng, h->phase, h->stream));
-  VP_TRY(materialise(h, h->d_ids + slot, 1));
-  return VP_OK;
+  return materialise_slot(h, slot);
 }
 
 vp_status vp_create(const vp_config* cfg, vp_particles parts, void* workspace, void* stream,
@@ -672,17 +839,16 @@ vp_status vp_retire(vp_handle* h, int32_t slot) {
   VP_TRY(check_slot(h, slot));
   Slot& sl = h->slots[slot];
   if (sl.pending) {
-    VP_TRY(materialise(h, h->d_ids + slot, 1));
+    VP_TRY(materialise_slot(h, slot));
     VP_HIP(vpk::launch_settle(h->precision, h->tun.threads, h->d_inst, h->d_tiles, sl.tile_begin, sl.ntiles,
                               h->tun.ppt, h->max_ng, h->phase, h->stream));
-    VP_HIP(vpk::launch_slot_scalars(h->d_inst, h->d_ids + slot, 1, vpk::kScalClearPending, h->phase,
-                                    h->stream));
     sl.pending = false;
   }
-  VP_HIP(hipStreamSynchronize(h->stream));
+  VP_TRY(sync_stream(h));
   sl.used = false;
   h->h_inst[slot] = InstDev{};
-  return rebuild_tables(h);
+  VP_TRY(arena_reserve(h, 0));
+  return rebuild_tables(h, vpk::UploadArgs{}, slot, false);
 }
 
 vp_status vp_destroy(vp_handle* h) {
@@ -691,9 +857,7 @@ vp_status vp_destroy(vp_handle* h) {
   drop_graph(h);
   if (h->d_inst) (void)hipFree(h->d_inst);
   if (h->d_tiles) (void)hipFree(h->d_tiles);
-  if (h->d_occ) (void)hipFree(h->d_occ);
-  if (h->d_ids) (void)hipFree(h->d_ids);
-  if (h->d_status) (void)hipFree(h->d_status);
+  if (h->arena) (void)hipHostFree(h->arena);
   delete h;
   return VP_OK;
 }
@@ -749,6 +913,7 @@ vp_status vp_step(vp_handle* h, int32_t nsteps) {
     for (int s : h->h_occ) {
       h->slots[s].step += chunk;
       h->slots[s].pending = true;
+      h->slots[s].solved = false;
     }
     done += chunk;
   }
@@ -810,21 +975,21 @@ vp_status vp_diagnostics(vp_handle* h, int32_t slot, vp_diag* host_out, double* 
   if (!host_out) return fail(VP_ERR_ARG, "host_out is NULL");
   const Slot& sl = h->slots[slot];
   const InstDev& d = h->h_inst[slot];
-  VP_TRY(materialise(h, h->d_ids + slot, 1));
+  VP_TRY(materialise_slot(h, slot));
   VP_HIP(vpk::launch_slot_scalars(h->d_inst, h->d_ids + slot, 1, vpk::kScalClearDiag, h->phase, h->stream));
   VP_HIP(vpk::launch_diag(h->precision, h->tun.threads, h->d_inst, h->d_tiles, sl.tile_begin, sl.ntiles, h->tun.ppt,
                           h->max_ng, h->phase, h->stream));
   vpk::InstScal sc{};
-  VP_HIP(hipMemcpyAsync(&sc, d.scal, sizeof sc, hipMemcpyDeviceToHost, h->stream));
+  ReadPart parts[5] = {{&sc, d.scal, kScalHead}};
+  int np = 1;
   if (host_grid) {  // b~ and Phi have nacc nodes (2 ng for P2), E and g ng elements
-    const int ng = sl.cfg.ng, na = d.nacc;
-    VP_HIP(hipMemcpyAsync(host_grid, d.bt, na * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    VP_HIP(hipMemcpyAsync(host_grid + na, d.Phi, na * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    VP_HIP(hipMemcpyAsync(host_grid + 2 * na, d.E, ng * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    VP_HIP(hipMemcpyAsync(host_grid + 2 * na + ng, d.g, ng * sizeof(double), hipMemcpyDeviceToHost,
-                          h->stream));
+    const size_t ng = sl.cfg.ng, na = d.nacc, w = sizeof(double);
+    parts[np++] = {host_grid, d.bt, na * w};
+    parts[np++] = {host_grid + na, d.Phi, na * w};
+    parts[np++] = {host_grid + 2 * na, d.E, ng * w};
+    parts[np++] = {host_grid + 2 * na + ng, d.g, ng * w};
   }
-  VP_HIP(hipStreamSynchronize(h->stream));
+  VP_TRY(read_back(h, parts, np));
   host_out->step = sc.step;
   host_out->t = (double)sc.step * sl.cfg.dt;
   const int p = h->phase;
@@ -852,26 +1017,27 @@ vp_status vp_history(vp_handle* h, int32_t slot, int64_t first_step, int32_t cou
   const Slot& sl = h->slots[slot];
   const InstDev& d = h->h_inst[slot];
   const long long cap = sl.cfg.hist_cap;
-  if (sl.pending) VP_TRY(materialise(h, h->d_ids + slot, 1));  // the last step's record
-  // the device step counter is authoritative: a frozen (non-finite) instance stops counting
+  if (sl.pending) VP_TRY(materialise_slot(h, slot));  // the last step's record
+  // the device step counter is authoritative: a frozen (non-finite) instance stops counting.
+  // The records come with it, and are used only if it covers them: one wait for both.
   vpk::InstScal sc{};
-  VP_HIP(hipMemcpyAsync(&sc, d.scal, sizeof sc, hipMemcpyDeviceToHost, h->stream));
-  VP_HIP(hipStreamSynchronize(h->stream));
+  ReadPart parts[3] = {{&sc, d.scal, kScalHead}};
+  int np = 1;
+  const bool in_ring = first_step >= 0 && count <= cap && first_step <= sl.step - count;
+  std::vector<double> buf(in_ring ? (size_t)count * vpk::kHistFields : 0);
+  for (long long k = 0; in_ring && k < count;) {  // two runs at most: count <= cap
+    const long long pos = (first_step + k) % cap;
+    const long long run = std::min<long long>(count - k, cap - pos);
+    parts[np++] = {buf.data() + k * vpk::kHistFields, d.hist + pos * vpk::kHistFields,
+                   run * vpk::kHistFields * sizeof(double)};
+    k += run;
+  }
+  VP_TRY(read_back(h, parts, np));
   const long long have = std::min<long long>(sc.step, sl.step);
   const long long lo = std::max(0LL, have - cap);
   if (first_step < lo || first_step + count > have)
     return fail(VP_ERR_RANGE, "records %lld..%lld not stored (have %lld..%lld)", (long long)first_step,
                 (long long)(first_step + count - 1), lo, have - 1);
-  std::vector<double> buf((size_t)count * vpk::kHistFields);
-  long long k = 0;
-  while (k < count) {
-    const long long st = first_step + k;
-    const long long pos = st % cap;
-    const long long run = std::min<long long>(count - k, cap - pos);
-    VP_HIP(hipMemcpy(buf.data() + k * vpk::kHistFields, d.hist + pos * vpk::kHistFields,
-                     run * vpk::kHistFields * sizeof(double), hipMemcpyDeviceToHost));
-    k += run;
-  }
   bool finite = true;
   for (int i = 0; i < count; ++i) {
     to_diag(buf.data() + (size_t)i * vpk::kHistFields, host_out + i);
@@ -903,14 +1069,16 @@ vp_status vp_set_tuning(vp_handle* h, const vp_tuning* t) {
   h->tun = *t;
   h->tun.use_graph = t->use_graph ? 1 : 0;
   h->tun.persistent = t->persistent ? 1 : 0;
-  VP_TRY(rebuild_tables(h));
+  VP_TRY(arena_reserve(h, 0));
+  VP_TRY(rebuild_tables(h, vpk::UploadArgs{}, -1, true));
   if (h->tun.persistent) {
     const int cap = vpk::persist_capacity(h->precision, h->tun.threads, h->tun.ppt, h->max_ng,
                                           h->any_fft, any_general(h), any_p2(h));
     if (h->ntiles > cap) {
       const int need = h->ntiles;
       h->tun = old;
-      VP_TRY(rebuild_tables(h));
+      VP_TRY(arena_reserve(h, 0));
+      VP_TRY(rebuild_tables(h, vpk::UploadArgs{}, -1, true));
       return fail(VP_ERR_ARG, "persistent steps need all %d workgroups resident; the device holds %d",
                   need, cap);
     }
@@ -943,9 +1111,8 @@ vp_status vp_slot_status(vp_handle* h, int32_t n, int64_t* host_steps, int32_t* 
   if (nocc == 0) return VP_OK;
   std::vector<long long> buf(2 * (size_t)nocc);
   VP_HIP(vpk::launch_slot_status(h->d_inst, h->d_occ, nocc, h->d_status, h->stream));
-  VP_HIP(hipMemcpyAsync(buf.data(), h->d_status, buf.size() * sizeof(long long),
-                        hipMemcpyDeviceToHost, h->stream));
-  VP_HIP(hipStreamSynchronize(h->stream));
+  const ReadPart part{buf.data(), h->d_status, buf.size() * sizeof(long long)};
+  VP_TRY(read_back(h, &part, 1));
   for (int t = 0; t < nocc; ++t) {
     const int s = h->h_occ[t];
     if (s >= n) continue;
@@ -1194,7 +1361,8 @@ vp_status vp_tune(vp_handle* h, void* dev_scratch, int32_t steps_per_trial, vp_t
       return false;
     }
     if (st != VP_OK) return false;
-    st = vp_step(h, t.graph_steps);
+    st = vp_prepare_step(h, t.graph_steps);
+    if (st == VP_OK) st = vp_step(h, t.graph_steps);
     if (st != VP_OK) return false;
     if (hipEventRecord(e0, h->stream) != hipSuccess) { st = fail(VP_ERR_HIP, "event record"); return false; }
     st = vp_step(h, steps_per_trial);

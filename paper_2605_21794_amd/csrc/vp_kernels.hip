@@ -472,6 +472,21 @@ __global__ void k_slot_status(const InstDev* __restrict__ insts, const int* __re
   out[2 * t + 1] = sc->nonfinite;
 }
 
+// Copies and clears in one launch (see UploadArgs).
+__global__ void k_upload(UploadArgs u) {
+  const size_t stride = (size_t)gridDim.x * blockDim.x;
+  const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int k = 0; k < u.nseg; ++k) {
+    VPG unsigned long long* dst = gp<unsigned long long>(u.seg[k].dst);
+    const VPG unsigned long long* src = gp<unsigned long long>(const_cast<void*>(u.seg[k].src));
+    for (size_t i = t; i < u.seg[k].n8; i += stride) dst[i] = src[i];
+  }
+  for (int k = 0; k < u.nzero; ++k) {
+    VPG unsigned long long* dst = gp<unsigned long long>(u.zero[k].dst);
+    for (size_t i = t; i < u.zero[k].n8; i += stride) dst[i] = 0ull;
+  }
+}
+
 // Zero n8 64-bit words, then a trailing 32-bit word when tail4 (an odd count of floats).
 __global__ void k_fill_zero(unsigned long long* p, size_t n8, bool tail4) {
   const size_t stride = (size_t)gridDim.x * blockDim.x;
@@ -716,6 +731,16 @@ hipError_t launch_slot_status(const InstDev* d_inst, const int* d_slots, int nsl
   if (nslots <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_slot_status, dim3((nslots + 63) / 64), dim3(64), 0, s, d_inst, d_slots,
                      nslots, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_upload(const UploadArgs& u, hipStream_t s) {
+  size_t n8 = 0;
+  for (int k = 0; k < u.nseg; ++k) n8 = n8 < u.seg[k].n8 ? u.seg[k].n8 : n8;
+  for (int k = 0; k < u.nzero; ++k) n8 = n8 < u.zero[k].n8 ? u.zero[k].n8 : n8;
+  if (n8 == 0) return hipSuccess;
+  const size_t blocks = (n8 + 255) / 256;
+  hipLaunchKernelGGL(k_upload, dim3((unsigned)(blocks > 4096 ? 4096 : blocks)), dim3(256), 0, s, u);
   return hipGetLastError();
 }
 
