@@ -61,6 +61,7 @@ __global__ __launch_bounds__(TPB) void k_fused(const InstDev* __restrict__ insts
   VPG T* __restrict__ Mqp_ = gp<T>(d.Mqq);
   VPG T* __restrict__ Mqpp = gp<T>(d.Mqp);
   VPG T* __restrict__ Mppp = gp<T>(d.Mpp);
+  const T zq = pad_position<T>(d);
   auto load_group = [&](int k0, Group& g) {
 #pragma unroll
     for (int u = 0; u < kGroup; ++u) {
@@ -68,11 +69,12 @@ __global__ __launch_bounds__(TPB) void k_fused(const InstDev* __restrict__ insts
       g.v[u] = (k0 + u < ppt) && (loc < tl.count);
       g.idx[u] = tl.begin + loc;
       // every lane loads (a lane past the end of the tile reads the tile's last particle, so
-      // no load is under a branch); such a lane then holds an all-zero particle (run_group)
+      // no load is under a branch); such a lane then holds an all-zero particle (run_group),
+      // away from its neighbours' (pad_position)
       const long long li = tl.begin + (g.v[u] ? loc : tl.count - 1);
       const T z = T(0);
       const T lq = ntld(Qp + li), lp = ntld(Pp + li), lw = ntld(psip + li);
-      g.q[u] = g.v[u] ? lq : z;
+      g.q[u] = g.v[u] ? lq : zq;
       g.p[u] = g.v[u] ? lp : z;
       g.w[u] = g.v[u] ? lw : z;
       g.a[u] = g.b[u] = z;
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(TPB) void k_fused(const InstDev* __restrict__ insts
     }
   }
 
-  // Every lane pushes all its particles without a branch: an all-zero particle (a lane past
+  // Every lane pushes all its particles without a branch: a weightless particle (a lane past
   // the end of the tile) deposits +0 and adds 0 to the kinetic sums, so the particles'
   // dependency chains interleave; only the stores test the lane.
   auto run_group = [&](Group& g) {

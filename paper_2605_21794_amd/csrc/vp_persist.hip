@@ -133,15 +133,16 @@ __global__ __launch_bounds__(TPB, (persist_waves<MODE, TPB, PPT, P2>())) void k_
   if (sc->frozen) return;  // fixed for the launch: all tiles of the instance leave together
   const bool first = tl.local == 0;
 
-  // A lane past the end of the tile holds an all-zero particle: its deposit adds +0 and its
-  // kinetic sums 0, so every lane runs the push without a branch (only the stores test it).
+  // A lane past the end of the tile holds a weightless particle: its deposit adds +0 and its
+  // kinetic sums 0 (pad_position), so every lane runs the push without a branch (only the stores test it).
   T q[PPT], p[PPT], a[PPT], b[PPT], w[PPT];
   bool v[PPT];
 #pragma unroll
   for (int u = 0; u < PPT; ++u) {
     const int loc = u * TPB + (int)threadIdx.x;
     v[u] = loc < tl.count;
-    q[u] = p[u] = a[u] = b[u] = w[u] = T(0);
+    p[u] = a[u] = b[u] = w[u] = T(0);
+    q[u] = pad_position<T>(d);
     if (v[u]) {
       const long long i = tl.begin + loc;
       q[u] = ntld(Qp + i); p[u] = ntld(Pp + i); a[u] = ntld(qsp + i);
