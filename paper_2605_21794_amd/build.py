@@ -18,10 +18,12 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libvp.so")
 # (source, object name, extra defines): the fused step is compiled once per precision mode
 SOURCES = [("vp_kernels.hip", "vp_kernels", []), ("vp_persist.hip", "vp_persist", []),
+           ("vp_resident.hip", "vp_resident", []),
            ("vp_cluster.hip", "vp_cluster", []), ("vp_api.cpp", "vp_api", [])] + [
     ("vp_fused.hip", f"vp_fused_{m}", [f"-DVP_FUSED_MODE={m}"]) for m in range(4)]
 # every file whose text the kernels are built from
-KERNEL_SOURCES = ["vp_device.h", "vp_internal.h", "vp_kernels.hip", "vp_fused.hip", "vp_persist.hip"]
+KERNEL_SOURCES = ["vp_device.h", "vp_internal.h", "vp_kernels.hip", "vp_fused.hip", "vp_persist.hip",
+                  "vp_resident.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 

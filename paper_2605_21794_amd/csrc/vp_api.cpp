@@ -158,6 +158,7 @@ struct vp_handle {
   int max_ng = VP_MIN_NG;   // largest ng of the slots, doubled for P2 (sizes the launches' LDS)
   bool any_fft = false;     // some slot uses the FFT solver (fused launches need more LDS)
   vp_tuning tun{1024, 4, 4, 1, 33, 0, 0};
+  bool tuned = false;       // the tuning was set (vp_set_tuning, vp_tune): it is taken as it is
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
   hipGraph_t step_graph[vpk::kRing] = {nullptr, nullptr, nullptr};  // one step at phase p
@@ -495,11 +496,37 @@ vp_status advance_persistent(vp_handle* h, int k) {
   return VP_OK;
 }
 
+// Whether k steps run as one workgroup per instance: the tuning is the default (an explicit one
+// is taken as it is), every instance is small enough (resident_capacity), and there is more than
+// one step to share the launch.
+bool steps_resident(const vp_handle* h, int k) {
+  if (h->tuned || k < 2) return false;
+  const long long cap = vpk::resident_capacity(h->precision, any_general(h), any_p2(h));
+  for (int s : h->h_occ)
+    if (h->slots[s].cfg.n > cap || h->h_inst[s].k3) return false;
+  return true;
+}
+
+vp_status advance_resident(vp_handle* h, int k) {
+  long long nmax = 0;
+  for (int s : h->h_occ) nmax = std::max<long long>(nmax, h->slots[s].cfg.n);
+  while (k > 0) {
+    const int c = std::min(k, kMaxPersistSteps);
+    VP_HIP(vpk::launch_resident(h->precision, nmax, h->d_inst, h->d_occ, (int)h->h_occ.size(),
+                                h->max_ng, h->any_fft, any_general(h), any_p2(h), h->phase, c,
+                                h->stream));
+    h->phase = (h->phase + c) % vpk::kRing;
+    k -= c;
+  }
+  return VP_OK;
+}
+
 // Run k fused steps of every slot.  With graphs on: replays of the whole graph where it
 // fits (after at most kRing-1 one-step replays that bring the phase to the graph's) and
 // one-step replays for the rest; direct launches with graphs off.
 vp_status advance(vp_handle* h, int k) {
   if (h->tun.persistent) return advance_persistent(h, k);
+  if (steps_resident(h, k)) return advance_resident(h, k);
   bool graphs = h->tun.use_graph && h->stream != nullptr;
   // A capture holds the first step back by 5 to 6 us per captured step, and replayed steps are
   // no shorter than launched ones (the host launches one in 2.5 us, the GPU takes 8 or more):
@@ -924,6 +951,7 @@ vp_status vp_prepare_step(vp_handle* h, int32_t nsteps) {
   if (!h) return fail(VP_ERR_ARG, "handle is NULL");
   if (nsteps < 0) return fail(VP_ERR_ARG, "nsteps < 0");
   if (h->h_occ.empty() || nsteps == 0 || h->tun.persistent) return VP_OK;
+  if (steps_resident(h, nsteps)) return VP_OK;
   if (!h->tun.use_graph || h->stream == nullptr) return VP_OK;
   if (nsteps >= graph_len_of(h)) VP_TRY(ensure_graph(h));
   for (int p = 0; p < vpk::kRing; ++p) VP_TRY(ensure_step_graph(h, p));
@@ -1066,6 +1094,7 @@ vp_status vp_set_tuning(vp_handle* h, const vp_tuning* t) {
                                 "steps do not run", s);
   }
   const vp_tuning old = h->tun;
+  h->tuned = true;
   h->tun = *t;
   h->tun.use_graph = t->use_graph ? 1 : 0;
   h->tun.persistent = t->persistent ? 1 : 0;

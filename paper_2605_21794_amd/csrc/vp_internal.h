@@ -152,6 +152,13 @@ hipError_t launch_persist(int mode, int tpb, int ppt, const InstDev* d_inst, con
                           int nsteps, hipStream_t s);
 int persist_capacity(int mode, int tpb, int ppt, int max_ng, bool lds_fft, bool general,
                      bool p2);
+// nsteps steps of the listed slots in one launch, one workgroup per instance (particles in
+// registers, load vector in LDS; no instance waits for another).  nmax: the largest instance, at
+// most resident_capacity; none with second moments.
+long long resident_capacity(int mode, bool general, bool p2);
+hipError_t launch_resident(int mode, long long nmax, const InstDev* d_inst, const int* d_slots,
+                           int nslots, int max_ng, bool lds_fft, bool general, bool p2, int phase,
+                           int nsteps, hipStream_t s);
 // Solve the listed slots from ring entry `phase` and write the field arrays (materialise).
 hipError_t launch_solve(int mode, const InstDev* d_inst, const int* d_slots, int nslots,
                         int max_ng, bool lds_fft, int phase, hipStream_t s);
