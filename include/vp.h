@@ -179,7 +179,9 @@ typedef struct vp_diag {
                        of the engine took; 0 from vp_diagnostics */
 } vp_diag;
 
-/* Launch shape of the particle kernels; chosen by vp_tune or set by the caller. */
+/* Launch shape of the particle kernels; chosen by vp_tune or set by the caller.  A handle on
+ * which neither was called picks its shapes by each instance's size (and runs instances that fit
+ * one workgroup many steps per launch); vp_get_tuning then returns {1024, 4, 4, 1, 33, 0, 0}. */
 typedef struct vp_tuning {
   int32_t threads;      /* threads per workgroup of the particle kernels: 256, 512 or 1024 */
   int32_t ppt;          /* particles per thread per tile: 1, 2, 4, 8, 16, 32 or 64 */

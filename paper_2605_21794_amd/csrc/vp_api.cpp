@@ -159,6 +159,7 @@ struct vp_handle {
   bool any_fft = false;     // some slot uses the FFT solver (fused launches need more LDS)
   vp_tuning tun{1024, 4, 4, 1, 33, 0, 0};
   bool tuned = false;       // the tuning was set (vp_set_tuning, vp_tune): it is taken as it is
+  int threads = 512, ppt = 4;  // of the launches over the current tiles (ppt: the largest tile's)
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
   hipGraph_t step_graph[vpk::kRing] = {nullptr, nullptr, nullptr};  // one step at phase p
@@ -193,6 +194,31 @@ void drop_graph(vp_handle* h) {
 // solver (whose code only those carry).
 bool runs_general(const InstDev& d) { return d.general || d.solver == VP_SOLVE_FFT; }
 
+// Threads per workgroup by default: 512, or 1024 for an engine that holds particles with second
+// moments (their kernel's registers leave 512-thread workgroups no better filled: 2^20 such
+// particles 19.1 us at 1024 x 4, 25.0 at 512 x 4, 20.4 at 512 x 8).
+int default_threads(const vp_handle* h) {
+  for (const Slot& sl : h->slots)
+    if (sl.used && sl.cfg.moment_order == 3) return 1024;
+  return 512;
+}
+
+// Particles per thread of a slot's tiles: the tuning's where one was set; by default, at 512
+// threads, 4 up to 2^20 particles (every tile resident at once, two or more to a CU), 8 above,
+// and 16 for the largest float32 states.  us a step at 512 x 4, x 8, x 16 and, before, 1024 x 4
+// (Ng 512, 4 copies): float32 state with float64 sums 2^17 8.1, 10.0, -, 9.6; 2^20 10.7, 10.8,
+// 15.0, 10.6 (11.0 against 10.25 with a ragged tail); 2^21 18.5, 16.0, 17.6, 19.0; 2^22 34.2,
+// 30.2, 29.2, 39.0 (P2 41.0, 34.2, 31.1, 43.6; without dipoles 23.3, 20.3, 18.1, 26.4); 2^23
+// 63.7, 56.7, 57.3, 70.7; float64 2^18 8.8, 11.3, -, 10.8; 2^20 14.4, 16.8, 23.6, 15.5; 2^21
+// 29.0, 27.1, 31.5, 30.9; 2^22 54.2, 52.3, 56.9, 59.1.
+int ppt_of(const vp_handle* h, const vp_config& c) {
+  if (h->tuned) return h->tun.ppt;
+  if (default_threads(h) == 1024) return 4;
+  if (c.n <= (1LL << 20)) return 4;
+  return c.n >= 7LL << 19 && c.precision != VP_FP64 ? 16 : 8;
+}
+int threads_of(const vp_handle* h) { return h->tuned ? h->tun.threads : default_threads(h); }
+
 // Wait for the stream; every upload has then read its part of the arena.
 vp_status sync_stream(vp_handle* h) {
   VP_HIP(hipStreamSynchronize(h->stream));
@@ -203,10 +229,10 @@ vp_status sync_stream(vp_handle* h) {
 // Room in the arena for the parts of one upload: `extra` bytes and the tables of the slots in
 // use.  Waits for the stream when what earlier uploads may still read fills it.
 vp_status arena_reserve(vp_handle* h, size_t extra) {
-  const long long tile_n = (long long)h->tun.threads * h->tun.ppt;
   size_t tiles = 0, slots = 0;
   for (int s = 0; s < h->max_slots; ++s)
     if (h->slots[s].used) {
+      const long long tile_n = (long long)threads_of(h) * ppt_of(h, h->slots[s].cfg);
       tiles += (size_t)((h->slots[s].cfg.n + tile_n - 1) / tile_n);
       slots = s + 1;
     }
@@ -294,7 +320,10 @@ vp_status rebuild_tables(vp_handle* h, vpk::UploadArgs u, int only, bool fold) {
   if (graphs) VP_HIP(hipStreamSynchronize(h->stream));
   drop_graph(h);
   h->steps_since_tables = 0;
-  const int tile_n = h->tun.threads * h->tun.ppt;
+  const int threads = threads_of(h);
+  if (threads != h->threads) fold = true;
+  h->threads = threads;
+  h->ppt = 1;
   h->h_tiles.clear();
   h->h_occ.clear();
   h->max_ng = VP_MIN_NG;
@@ -317,6 +346,8 @@ vp_status rebuild_tables(vp_handle* h, vpk::UploadArgs u, int only, bool fold) {
   for (int s : order) {
     Slot& sl = h->slots[s];
     h->max_ng = std::max(h->max_ng, order_of(sl.cfg) * sl.cfg.ng);  // LDS sizing
+    const int ppt = ppt_of(h, sl.cfg), tile_n = h->threads * ppt;
+    h->ppt = std::max(h->ppt, ppt);
     const long long n = sl.cfg.n;
     const int nt = (int)((n + tile_n - 1) / tile_n);
     sl.tile_begin = (int)h->h_tiles.size();
@@ -386,8 +417,8 @@ hipError_t fused_step(vp_handle* h, int ph) {
     const int e_ = h->group_end[gi];
     if (e_ > b) {
       const bool km = gi == kGroupMoments, general = (gi & 1) != 0 || km;
-      const hipError_t e = vpk::launch_fused(h->precision, h->tun.threads, h->d_inst, h->d_tiles,
-                                             b, e_ - b, h->tun.ppt, h->max_ng,
+      const hipError_t e = vpk::launch_fused(h->precision, h->threads, h->d_inst, h->d_tiles,
+                                             b, e_ - b, h->ppt, h->max_ng,
                                              general && h->any_fft, ph, gi < 4 || km, general,
                                              (gi & 2) != 0 || km, km, h->stream);
       if (e != hipSuccess) return e;
@@ -487,7 +518,7 @@ vp_status advance_persistent(vp_handle* h, int k) {
     const int c = std::min(k, kMaxPersistSteps);
     VP_HIP(vpk::launch_slot_scalars(h->d_inst, h->d_occ, (int)h->h_occ.size(), vpk::kScalPersistStart,
                                     h->phase, h->stream));
-    VP_HIP(vpk::launch_persist(h->precision, h->tun.threads, h->tun.ppt, h->d_inst, h->d_tiles, h->ntiles,
+    VP_HIP(vpk::launch_persist(h->precision, h->threads, h->ppt, h->d_inst, h->d_tiles, h->ntiles,
                                h->max_ng, h->any_fft, any_general(h), any_p2(h), h->phase, c,
                                h->stream));
     h->phase = (h->phase + c) % vpk::kRing;
@@ -580,7 +611,7 @@ vp_status materialise_slot(vp_handle* h, int slot) {
 vp_status deposit_all(vp_handle* h) {
   VP_HIP(vpk::launch_ring(h->precision, h->d_inst, h->d_occ, (int)h->h_occ.size(), vpk::kRingClear,
                           h->phase, h->stream));
-  VP_HIP(vpk::launch_deposit(h->precision, h->tun.threads, h->d_inst, h->d_tiles, 0, h->ntiles, h->tun.ppt,
+  VP_HIP(vpk::launch_deposit(h->precision, h->threads, h->d_inst, h->d_tiles, 0, h->ntiles, h->ppt,
                              h->max_ng, h->phase, h->stream));
   h->acc_stale = false;
   for (int s : h->h_occ) h->slots[s].solved = false;
@@ -826,8 +857,8 @@ vp_status vp_admit(vp_handle* h, int32_t slot, const vp_config* cfg, vp_particle
     return st;
   }
   // Load vector and field at t = 0 from the initial state (the ring entries start cleared).
-  VP_HIP(vpk::launch_deposit(h->precision, h->tun.threads, h->d_inst, h->d_tiles, sl.tile_begin, sl.ntiles,
-                             h->tun.ppt, h->max_ng, h->phase, h->stream));
+  VP_HIP(vpk::launch_deposit(h->precision, h->threads, h->d_inst, h->d_tiles, sl.tile_begin, sl.ntiles,
+                             h->ppt, h->max_ng, h->phase, h->stream));
   return materialise_slot(h, slot);
 }
 
@@ -867,8 +898,8 @@ vp_status vp_retire(vp_handle* h, int32_t slot) {
   Slot& sl = h->slots[slot];
   if (sl.pending) {
     VP_TRY(materialise_slot(h, slot));
-    VP_HIP(vpk::launch_settle(h->precision, h->tun.threads, h->d_inst, h->d_tiles, sl.tile_begin, sl.ntiles,
-                              h->tun.ppt, h->max_ng, h->phase, h->stream));
+    VP_HIP(vpk::launch_settle(h->precision, h->threads, h->d_inst, h->d_tiles, sl.tile_begin, sl.ntiles,
+                              h->ppt, h->max_ng, h->phase, h->stream));
     sl.pending = false;
   }
   VP_TRY(sync_stream(h));
@@ -906,7 +937,7 @@ vp_status vp_gather_push(vp_handle* h, double kick, double drift) {
   if (!std::isfinite(kick) || !std::isfinite(drift)) return fail(VP_ERR_ARG, "kick and drift must be finite");
   if (h->h_occ.empty()) return VP_OK;
   if (h->field_stale) VP_TRY(materialise_all(h));
-  VP_HIP(vpk::launch_gather_push(h->precision, h->tun.threads, h->d_inst, h->d_tiles, 0, h->ntiles, h->tun.ppt,
+  VP_HIP(vpk::launch_gather_push(h->precision, h->threads, h->d_inst, h->d_tiles, 0, h->ntiles, h->ppt,
                                  h->max_ng, kick, drift, h->stream));
   if (drift != 0.0) h->acc_stale = true;
   return VP_OK;
@@ -962,7 +993,7 @@ vp_status vp_sync_state(vp_handle* h) {
   if (!h) return fail(VP_ERR_ARG, "handle is NULL");
   if (h->h_occ.empty()) return VP_OK;
   VP_TRY(materialise_all(h));
-  VP_HIP(vpk::launch_settle(h->precision, h->tun.threads, h->d_inst, h->d_tiles, 0, h->ntiles, h->tun.ppt,
+  VP_HIP(vpk::launch_settle(h->precision, h->threads, h->d_inst, h->d_tiles, 0, h->ntiles, h->ppt,
                             h->max_ng, h->phase, h->stream));
   VP_HIP(vpk::launch_slot_scalars(h->d_inst, h->d_occ, (int)h->h_occ.size(), vpk::kScalClearPending,
                                   h->phase, h->stream));
@@ -1005,7 +1036,7 @@ vp_status vp_diagnostics(vp_handle* h, int32_t slot, vp_diag* host_out, double* 
   const InstDev& d = h->h_inst[slot];
   VP_TRY(materialise_slot(h, slot));
   VP_HIP(vpk::launch_slot_scalars(h->d_inst, h->d_ids + slot, 1, vpk::kScalClearDiag, h->phase, h->stream));
-  VP_HIP(vpk::launch_diag(h->precision, h->tun.threads, h->d_inst, h->d_tiles, sl.tile_begin, sl.ntiles, h->tun.ppt,
+  VP_HIP(vpk::launch_diag(h->precision, h->threads, h->d_inst, h->d_tiles, sl.tile_begin, sl.ntiles, h->ppt,
                           h->max_ng, h->phase, h->stream));
   vpk::InstScal sc{};
   ReadPart parts[5] = {{&sc, d.scal, kScalHead}};
@@ -1094,6 +1125,7 @@ vp_status vp_set_tuning(vp_handle* h, const vp_tuning* t) {
                                 "steps do not run", s);
   }
   const vp_tuning old = h->tun;
+  const bool old_tuned = h->tuned;
   h->tuned = true;
   h->tun = *t;
   h->tun.use_graph = t->use_graph ? 1 : 0;
@@ -1106,6 +1138,7 @@ vp_status vp_set_tuning(vp_handle* h, const vp_tuning* t) {
     if (h->ntiles > cap) {
       const int need = h->ntiles;
       h->tun = old;
+      h->tuned = old_tuned;
       VP_TRY(arena_reserve(h, 0));
       VP_TRY(rebuild_tables(h, vpk::UploadArgs{}, -1, true));
       return fail(VP_ERR_ARG, "persistent steps need all %d workgroups resident; the device holds %d",
@@ -1349,6 +1382,7 @@ vp_status vp_tune(vp_handle* h, void* dev_scratch, int32_t steps_per_trial, vp_t
   char* scratch = static_cast<char*>(dev_scratch);
   std::vector<Slot> saved = h->slots;
   const vp_tuning orig = h->tun;
+  const bool orig_tuned = h->tuned;
   const int saved_phase = h->phase;
   const bool saved_fs = h->field_stale, saved_as = h->acc_stale;
   VP_TRY(tune_copy(h, scratch, true));
@@ -1437,6 +1471,13 @@ vp_status vp_tune(vp_handle* h, void* dev_scratch, int32_t steps_per_trial, vp_t
   h->acc_stale = saved_as;
   vp_status s2 = tune_copy(h, scratch, false);
   vp_status s3 = vp_set_tuning(h, st == VP_OK ? &best : &orig);
+  if (st != VP_OK && !orig_tuned) {  // back to the default shapes
+    h->tuned = false;
+    const vp_status keep = st;
+    VP_TRY(arena_reserve(h, 0));
+    VP_TRY(rebuild_tables(h, vpk::UploadArgs{}, -1, true));
+    st = keep;
+  }
   if (st != VP_OK) return st;
   if (s2 != VP_OK) return s2;
   if (s3 != VP_OK) return s3;

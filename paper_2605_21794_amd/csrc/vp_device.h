@@ -949,7 +949,7 @@ static __device__ void write_record(const InstDev& d, long long step, double K, 
 // Loop shape shared by the particle kernels: thread t of the workgroup handles particles
 // tile.begin + k * TPB + t for k < ppt, four at a time with all loads issued first.
 #define VP_TILE_LOOP_BEGIN                                                        \
-  for (int k0 = 0; k0 < ppt; k0 += 4) {                                           \
+  for (int k0 = 0; k0 < ppt && k0 * TPB < tl.count; k0 += 4) {                     \
     bool v[4];                                                                    \
     long long idx[4];                                                             \
     _Pragma("unroll") for (int u = 0; u < 4; ++u) {                              \

@@ -17,13 +17,14 @@ namespace vpk {
 template <int MODE, int TPB, bool DIP, bool GEN, bool P2, bool KM = false>
 __global__ __launch_bounds__(TPB) void k_fused(const InstDev* __restrict__ insts,
                                                const Tile* __restrict__ tiles, int tile0,
-                                               int ppt, int phase) {
+                                               int ppt_max, int phase) {
   extern __shared__ double smem[];
   __shared__ double red[4 * (TPB / 64)];
   __shared__ double sred[kSolveRed];
   using T = typename StateType<MODE>::T;
   constexpr int kGroup = group_of<MODE, TPB>();
   const Tile tl = tiles[tile0 + blockIdx.x];
+  const int ppt = min(ppt_max, (tl.count + TPB - 1) / TPB);  // tiles may be smaller
   const InstDev& d = insts[tl.inst];
   const int ng = d.ng;
   const int r0 = phase, r1 = ring_next(phase), r2 = ring_prev(phase);
