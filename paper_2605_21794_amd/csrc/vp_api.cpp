@@ -45,8 +45,8 @@ vp_status fail(vp_status s, const char* fmt, ...) {
     if (s_ != VP_OK) return s_;   \
   } while (0)
 
-constexpr int kGroups = 9;        // kinds of tiles, one fused launch each (see rebuild_tables)
-constexpr int kGroupMoments = 8;  // the kind of instances with second moments
+constexpr int kGroups = 10;       // kinds of tiles, one fused launch each (see rebuild_tables)
+constexpr int kGroupMoments = 8;  // the two kinds of instances with second moments
 
 bool is_pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
 int ilog2(int x) { int m = 0; while ((1 << m) < x) ++m; return m; }
@@ -194,14 +194,7 @@ void drop_graph(vp_handle* h) {
 // solver (whose code only those carry).
 bool runs_general(const InstDev& d) { return d.general || d.solver == VP_SOLVE_FFT; }
 
-// Threads per workgroup by default: 512, or 1024 for an engine that holds particles with second
-// moments (their kernel's registers leave 512-thread workgroups no better filled: 2^20 such
-// particles 19.1 us at 1024 x 4, 25.0 at 512 x 4, 20.4 at 512 x 8).
-int default_threads(const vp_handle* h) {
-  for (const Slot& sl : h->slots)
-    if (sl.used && sl.cfg.moment_order == 3) return 1024;
-  return 512;
-}
+constexpr int kDefaultThreads = 512;
 
 // Particles per thread of a slot's tiles: the tuning's where one was set; by default, at 512
 // threads, 4 up to 2^20 particles (every tile resident at once, two or more to a CU), 8 above,
@@ -210,14 +203,16 @@ int default_threads(const vp_handle* h) {
 // 15.0, 10.6 (11.0 against 10.25 with a ragged tail); 2^21 18.5, 16.0, 17.6, 19.0; 2^22 34.2,
 // 30.2, 29.2, 39.0 (P2 41.0, 34.2, 31.1, 43.6; without dipoles 23.3, 20.3, 18.1, 26.4); 2^23
 // 63.7, 56.7, 57.3, 70.7; float64 2^18 8.8, 11.3, -, 10.8; 2^20 14.4, 16.8, 23.6, 15.5; 2^21
-// 29.0, 27.1, 31.5, 30.9; 2^22 54.2, 52.3, 56.9, 59.1.
+// 29.0, 27.1, 31.5, 30.9; 2^22 54.2, 52.3, 56.9, 59.1.  Particles with second moments, whose
+// push is longer: 2 up to 2^19 (512 x 2, x 4, x 8; float32 state: 2^18 9.4, 11.0, 14.3; 2^19
+// 11.1, 11.5, 14.6; 2^20 19.0, 15.5, 16.5; 2^21 35.1, 28.9, 27.1), 4 and 8 as the others.
 int ppt_of(const vp_handle* h, const vp_config& c) {
   if (h->tuned) return h->tun.ppt;
-  if (default_threads(h) == 1024) return 4;
-  if (c.n <= (1LL << 20)) return 4;
-  return c.n >= 7LL << 19 && c.precision != VP_FP64 ? 16 : 8;
+  const bool k3 = c.moment_order == 3;
+  if (c.n <= (1LL << 20)) return k3 && c.n <= (1LL << 19) ? 2 : 4;
+  return c.n >= 7LL << 19 && c.precision != VP_FP64 && !k3 ? 16 : 8;
 }
-int threads_of(const vp_handle* h) { return h->tuned ? h->tun.threads : default_threads(h); }
+int threads_of(const vp_handle* h) { return h->tuned ? h->tun.threads : kDefaultThreads; }
 
 // Wait for the stream; every upload has then read its part of the arena.
 vp_status sync_stream(vp_handle* h) {
@@ -331,10 +326,11 @@ vp_status rebuild_tables(vp_handle* h, vpk::UploadArgs u, int only, bool fold) {
     if (h->slots[s].used) h->h_occ.push_back(s);
   // tiles grouped by kind, one fused launch per non-empty group and step: decorated then
   // monopole-only instances; within each, P1 then P2 elements, each without then with
-  // general options or the FFT solver; last the instances with second moments (P2, general, decorated)
+  // general options or the FFT solver; last the instances with second moments (P2, decorated),
+  // without then with those
   auto group_of = [&](int s) {
     const InstDev& d = h->h_inst[s];
-    if (d.k3) return kGroupMoments;
+    if (d.k3) return kGroupMoments + (runs_general(d) ? 1 : 0);
     return (h->slots[s].cfg.monopole_only ? 4 : 0) + (d.order == 2 ? 2 : 0) + (runs_general(d) ? 1 : 0);
   };
   std::vector<int> order;
@@ -416,7 +412,7 @@ hipError_t fused_step(vp_handle* h, int ph) {
   for (int gi = 0; gi < kGroups; ++gi) {
     const int e_ = h->group_end[gi];
     if (e_ > b) {
-      const bool km = gi == kGroupMoments, general = (gi & 1) != 0 || km;
+      const bool km = gi >= kGroupMoments, general = (gi & 1) != 0;
       const hipError_t e = vpk::launch_fused(h->precision, h->threads, h->d_inst, h->d_tiles,
                                              b, e_ - b, h->ppt, h->max_ng,
                                              general && h->any_fft, ph, gi < 4 || km, general,
@@ -800,8 +796,7 @@ vp_status vp_admit(vp_handle* h, int32_t slot, const vp_config* cfg, vp_particle
   d.ext_on = (cfg->ext_mode >= 1 && cfg->ext_amplitude != 0.0) ? 1 : 0;
   d.Mqq = parts.Mqq; d.Mqp = parts.Mqp; d.Mpp = parts.Mpp;
   d.k3 = k3 ? 1 : 0;
-  // second moments run in the kernels' general path
-  d.general = (d.proj != VP_PROJ_ELEM || !d.self_on || d.ext_on || k3) ? 1 : 0;
+  d.general = (d.proj != VP_PROJ_ELEM || !d.self_on || d.ext_on) ? 1 : 0;
   d.ext_a = cfg->ext_amplitude;
   d.ext_k = 6.283185307179586 * (double)cfg->ext_mode / cfg->L;  // 2 pi m / L
   d.ext_ak = d.ext_a * d.ext_k;

@@ -967,21 +967,20 @@ static __device__ void write_record(const InstDev& d, long long step, double K, 
 // float64 modes compute in float64 from the stored values in the oracle's operation order.
 // DIP = false: a monopole-only particle (p* = q* = 0, plain P1 particle-in-cell): the dipole
 // terms are left out, which gives the same values as carrying zeros through them.
-// k3 (an instance with second moments; GEN and P2 launches only): Mr holds the particle's
-// (Mqq, Mqp, Mpp) in storage precision, updated in place.  Mr is only read when k3 holds, so
-// a caller passes its local array unconditionally (a pointer chosen at run time between a
-// local array and nullptr would keep the array out of registers).
+// K3 (a launch of instances with second moments; P2 launches only): Mr holds the particle's
+// (Mqq, Mqp, Mpp) in storage precision, updated in place.
 // PEND: 1 or 0 when the caller knows the (uniform) pending flag at compile time, -1 to test
 // `pend`.  CELL (float64 modes, P1 without general options): *cellr holds the element of Qr
 // on entry (the element the previous push deposited at, from the same stored position) and
 // receives the element of the drifted position; the gather then skips recomputing it.
 template <int MODE, typename T, bool DIP = true, bool GEN = true, bool P2 = GEN, int PEND = -1,
-          bool CELL = false>
+          bool CELL = false, bool K3 = false>
 __device__ __forceinline__ void push_particle(const InstDev& d, const double* fE, const double* fG,
                                               double* sacc, int pend, T& Qr, T& Pr, T& qsr,
                                               T& psr, const T psir, double& Ks, double& Ms,
-                                              double& Cs, double& Us, bool k3in = false,
-                                              T* Mr = nullptr, int* cellr = nullptr) {
+                                              double& Cs, double& Us, T* Mr = nullptr,
+                                              int* cellr = nullptr) {
+  static_assert(!K3 || (P2 && DIP && MODE != kFP32), "second moments: P2 elements, dipoles");
   static_assert(!CELL || (!GEN && !P2 && MODE != kFP32), "CELL: float64 modes, P1, no general options");
   const bool pending = PEND < 0 ? pend != 0 : PEND == 1;
   const int ng = d.ng;
@@ -1054,32 +1053,31 @@ __device__ __forceinline__ void push_particle(const InstDev& d, const double* fE
       general_field(d, fE, fG, i, xq, Q, psi, ps, Ei, gi, u);
       Us += u;
     }
-    // k = 3: the second moments move with the kicks and the drift (uniform per workgroup)
-    const bool k3 = GEN && P2 && DIP && k3in;
+    // k = 3: the second moments move with the kicks and the drift
     double Mqq = 0.0, Mqp = 0.0, Mpp = 0.0, g3 = 0.0;
-    if (k3) {
+    if constexpr (K3) {
       Mqq = Mr[0];
       Mqp = Mr[1];
       Mpp = Mr[2];
-      k3_external(d, Q, Mqq, g3, Us);
+      if constexpr (GEN) k3_external(d, Q, Mqq, g3, Us);  // else no external field: g3 = 0
     }
     if constexpr (DIP) {
       if (pending) {
         P = P + half * Ei;
         qs = qs + half * ps * gi;
-        if (k3) {
-          qs = qs - (0.5 * half) * Mqq * g3;
+        if constexpr (K3) {
+          if constexpr (GEN) qs = qs - (0.5 * half) * Mqq * g3;
           moments_kick(half, gi, Mqq, Mqp, Mpp);
         }
       }
       Ks += 0.5 * psi * P * P + qs * P;
-      if (k3) Ks += 0.5 * Mpp;
+      if constexpr (K3) Ks += 0.5 * Mpp;
       Ms += psi * P + qs;
       Cs += psi;
       P = P + half * Ei;
       qs = qs + half * ps * gi;
-      if (k3) {
-        qs = qs - (0.5 * half) * Mqq * g3;
+      if constexpr (K3) {
+        if constexpr (GEN) qs = qs - (0.5 * half) * Mqq * g3;
         moments_kick(half, gi, Mqq, Mqp, Mpp);
       }
     } else {
@@ -1103,7 +1101,7 @@ __device__ __forceinline__ void push_particle(const InstDev& d, const double* fE
       const double psn = ps - dt * qs;
       const T pss = (T)psn;
       const double psd = pss;
-      if (k3) {
+      if constexpr (K3) {
         // the drift moves the moments; the load takes the stored (rounded) Mqq
         moments_drift(dt, Mqq, Mqp, Mpp);
         const T m0 = (T)Mqq;
@@ -1158,8 +1156,11 @@ __host__ __device__ constexpr size_t fused_lds_doubles(bool fft) { return fft ? 
 // summary, clears ring entry r+2 and advances the step counter.  No workgroup waits for
 // another: the next launch reads what this one deposited.
 // Particles per thread whose loads are in flight together (float64 state at 1024 threads
-// per workgroup holds two, to stay within 128 registers without spilling).
-template <int MODE, int TPB>
-__host__ __device__ constexpr int group_of() { return (MODE == kFP64 && TPB == 1024) ? 2 : 4; }
+// per workgroup holds two, to stay within 128 registers without spilling; KM: with second
+// moments two as well).
+template <int MODE, int TPB, bool KM>
+__host__ __device__ constexpr int group_of() {
+  return KM || (MODE == kFP64 && TPB == 1024) ? 2 : 4;
+}
 
 }  // namespace vpk

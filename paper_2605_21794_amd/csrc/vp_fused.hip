@@ -22,7 +22,7 @@ __global__ __launch_bounds__(TPB) void k_fused(const InstDev* __restrict__ insts
   __shared__ double red[4 * (TPB / 64)];
   __shared__ double sred[kSolveRed];
   using T = typename StateType<MODE>::T;
-  constexpr int kGroup = group_of<MODE, TPB>();
+  constexpr int kGroup = group_of<MODE, TPB, KM>();
   const Tile tl = tiles[tile0 + blockIdx.x];
   const int ppt = min(ppt_max, (tl.count + TPB - 1) / TPB);  // tiles may be smaller
   const InstDev& d = insts[tl.inst];
@@ -47,18 +47,15 @@ __global__ __launch_bounds__(TPB) void k_fused(const InstDev* __restrict__ insts
   const bool first = tl.local == 0;  // the instance's bookkeeping tile (uniform per workgroup)
 
   // one group of particles per thread: thread t takes tile.begin + k * TPB + t, k0 <= k < k0 + kGroup
-  // KM: a launch of k = 3 instances (particles with second moments; P2, general options,
-  // never kFP32), whose moments travel with the group
-  static_assert(!KM || (GEN && P2 && DIP && MODE != kFP32), "second moments need P2 and GEN");
-  constexpr bool kM = KM;
-  constexpr int kMG = kM ? kGroup : 1;
+  // KM: a launch of k = 3 instances (particles with second moments; P2, never kFP32), whose
+  // moments travel with the group
+  constexpr int kMG = KM ? kGroup : 1;
   struct Group {
     T q[kGroup], p[kGroup], a[kGroup], b[kGroup], w[kGroup];
     T m[3][kMG];
     long long idx[kGroup];
     bool v[kGroup];
   };
-  constexpr bool k3 = kM;
   VPG T* __restrict__ Mqp_ = gp<T>(d.Mqq);
   VPG T* __restrict__ Mqpp = gp<T>(d.Mqp);
   VPG T* __restrict__ Mppp = gp<T>(d.Mpp);
@@ -84,12 +81,11 @@ __global__ __launch_bounds__(TPB) void k_fused(const InstDev* __restrict__ insts
         g.a[u] = g.v[u] ? la : z;
         g.b[u] = g.v[u] ? lb : z;
       }
-      if constexpr (kM) {
-        g.m[0][u] = g.m[1][u] = g.m[2][u] = T(0);
-        if (k3 && g.v[u]) {
-          g.m[0][u] = ntld(Mqp_ + g.idx[u]); g.m[1][u] = ntld(Mqpp + g.idx[u]);
-          g.m[2][u] = ntld(Mppp + g.idx[u]);
-        }
+      if constexpr (KM) {
+        const T l0 = ntld(Mqp_ + li), l1 = ntld(Mqpp + li), l2 = ntld(Mppp + li);
+        g.m[0][u] = g.v[u] ? l0 : z;
+        g.m[1][u] = g.v[u] ? l1 : z;
+        g.m[2][u] = g.v[u] ? l2 : z;
       }
     }
   };
@@ -147,10 +143,10 @@ __global__ __launch_bounds__(TPB) void k_fused(const InstDev* __restrict__ insts
 #pragma unroll
     for (int u = 0; u < kGroup; ++u) {
       T Q = g.q[u], P = g.p[u], qs = g.a[u], ps = g.b[u];
-      if constexpr (kM) {
+      if constexpr (KM) {
         T Mv[3] = {g.m[0][u], g.m[1][u], g.m[2][u]};
-        push_particle<MODE, T, DIP, GEN, P2>(d, fE, fG, sacc, pend, Q, P, qs, ps, g.w[u], Ks,
-                                             Ms, Cs, Us, k3, Mv);
+        push_particle<MODE, T, DIP, GEN, P2, -1, false, true>(d, fE, fG, sacc, pend, Q, P, qs, ps,
+                                                              g.w[u], Ks, Ms, Cs, Us, Mv);
         g.m[0][u] = Mv[0]; g.m[1][u] = Mv[1]; g.m[2][u] = Mv[2];
       } else {
         push_particle<MODE, T, DIP, GEN, P2>(d, fE, fG, sacc, pend, Q, P, qs, ps, g.w[u], Ks,
@@ -163,11 +159,10 @@ __global__ __launch_bounds__(TPB) void k_fused(const InstDev* __restrict__ insts
       if (!g.v[u]) continue;
       ntst(Qp + g.idx[u], g.q[u]); ntst(Pp + g.idx[u], g.p[u]);
       if constexpr (DIP) { ntst(qsp + g.idx[u], g.a[u]); ntst(psp + g.idx[u], g.b[u]); }
-      if constexpr (kM)
-        if (k3) {
-          ntst(Mqp_ + g.idx[u], g.m[0][u]); ntst(Mqpp + g.idx[u], g.m[1][u]);
-          ntst(Mppp + g.idx[u], g.m[2][u]);
-        }
+      if constexpr (KM) {
+        ntst(Mqp_ + g.idx[u], g.m[0][u]); ntst(Mqpp + g.idx[u], g.m[1][u]);
+        ntst(Mppp + g.idx[u], g.m[2][u]);
+      }
     }
   };
 
@@ -215,17 +210,17 @@ hipError_t launch_fused_mode(int tpb, const InstDev* d_inst, const Tile* d_tiles
                         int ntiles, int ppt, int max_ng, bool lds_fft, int phase, bool dipoles,
                         bool general, bool p2, bool moments, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-  if (moments && (MODE == kFP32 || !dipoles || !general || !p2)) return hipErrorInvalidValue;
+  if (moments && (MODE == kFP32 || !dipoles || !p2)) return hipErrorInvalidValue;
   const size_t lds = fused_lds_doubles(lds_fft) * (size_t)max_ng * sizeof(double);
-#define VP_FUSED_K(M, TB, D, G, P)                                                           \
-  hipLaunchKernelGGL((k_fused<M, TB, D, G, P>), dim3(ntiles), dim3(TB), lds, s, d_inst,      \
+#define VP_FUSED_K(M, TB, ...)                                                               \
+  hipLaunchKernelGGL((k_fused<M, TB, __VA_ARGS__>), dim3(ntiles), dim3(TB), lds, s, d_inst,  \
                      d_tiles, tile0, ppt, phase)
 #define VP_FUSED(M, TB)                                                                      \
   do {                                                                                       \
     if constexpr (M != kFP32) {                                                              \
       if (moments) {                                                                         \
-        hipLaunchKernelGGL((k_fused<M, TB, true, true, true, true>), dim3(ntiles), dim3(TB),   \
-                           lds, s, d_inst, d_tiles, tile0, ppt, phase);                      \
+        if (general) VP_FUSED_K(M, TB, true, true, true, true);                              \
+        else VP_FUSED_K(M, TB, true, false, true, true);                                     \
         break;                                                                               \
       }                                                                                      \
     }                                                                                        \

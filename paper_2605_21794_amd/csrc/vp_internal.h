@@ -93,7 +93,7 @@ struct InstDev {
   void* Mqq;        // second moments of k = 3 particles (nullptr otherwise)
   void* Mqp;
   void* Mpp;
-  int k3;           // the particles carry second moments (P2, general options)
+  int k3;           // the particles carry second moments (P2)
   int seg;          // the fused and persistent deposits combine runs of equal elements
                     // within each wavefront first (vp_tuning.wave_reduce)
   unsigned spin_limit;  // polls before a persistent wait gives up (<= kSpinLimit)
@@ -124,7 +124,7 @@ size_t particle_lds_bytes(int mode, int max_ng);
 // true when some instance of the launch has general options (InstDev::general) or the FFT
 // solver (with lds_fft, general must hold); `p2` true
 // when its instances have P2 elements; `moments` true when its instances carry second
-// moments (InstDev::k3; then dipoles, general and p2 hold too).
+// moments (InstDev::k3; then dipoles and p2 hold too).
 hipError_t launch_fused(int mode, int tpb, const InstDev* d_inst, const Tile* d_tiles, int tile0,
                         int ntiles, int ppt, int max_ng, bool lds_fft, int phase, bool dipoles,
                         bool general, bool p2, bool moments, hipStream_t s);

@@ -233,8 +233,8 @@ __global__ __launch_bounds__(TPB, (persist_waves<MODE, TPB, PPT, P2>())) void k_
 #pragma unroll
     for (int u = 0; u < PPT; ++u)
       push_particle<MODE, T, true, GEN, P2, -1, kCell>(d, fE, fG, sacc, pend, q[u], p[u], a[u],
-                                                       b[u], w[u], Ks, Ms, Cs, Us, false,
-                                                       nullptr, &cell[u]);
+                                                       b[u], w[u], Ks, Ms, Cs, Us, nullptr,
+                                                       &cell[u]);
     pend = 1;
 
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;

@@ -135,8 +135,8 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(
 #pragma unroll
     for (int u = 0; u < PPT; ++u)
       push_particle<MODE, T, true, GEN, P2, -1, kCell>(d, fE, fG, sacc, pend, q[u], p[u], a[u],
-                                                       b[u], w[u], v[0], v[1], v[2], v[3], false,
-                                                       nullptr, &cell[u]);
+                                                       b[u], w[u], v[0], v[1], v[2], v[3], nullptr,
+                                                       &cell[u]);
     pend = 1;
     wave_sum_n(v);
     if (lane == 0)

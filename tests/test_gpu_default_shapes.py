@@ -2,7 +2,7 @@
 of different depth.  Instances at the sizes where the rule turns run together in one engine and
 agree with runs of an explicit uniform shape to the order of sums (float64 1e-12 relative over
 three steps; float32 states 1e-6: one rounding of the state where a sum's last bit differs),
-also when the engine's shape changes under them (second moments admitted)."""
+with a kind of its own (second moments) admitted and retired between the steps."""
 import numpy as np
 import pytest
 
@@ -41,10 +41,10 @@ def test_tiles_of_several_depths_in_one_launch(vp, prec, sizes):
     for s, st in enumerate(sts):
         eng.admit(s, st, L, 64 << (s % 3), 0.02, hist_cap=8)
     eng.step(2)
-    k3 = state(3000, 1, dt, True)
-    eng.admit(len(sizes), k3, L, 64, 0.02, element_order=2, hist_cap=8)   # another shape
+    k3 = state(600000, 1, dt, True)
+    eng.admit(len(sizes), k3, L, 64, 0.02, element_order=2, hist_cap=8)
     eng.step(1)
-    eng.retire(len(sizes))                                                # and back
+    eng.retire(len(sizes))
     eng.step(1)
     bar = 1e-12 if prec == "fp64" else 1e-6
     for s, st in enumerate(sts):
@@ -66,3 +66,28 @@ def test_get_tuning_keeps_its_defaults(vp):
     t = sim.get_tuning()
     assert (t["threads"], t["ppt"], t["acc_copies"], t["persistent"]) == (1024, 4, 4, 0)
     sim.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32c", "fp32ts"])
+@pytest.mark.parametrize("opt", [{}, {"external": {"amp": 0.2, "mode": 1}}, {"self_field": False},
+                                 {"solver": "fft"}])
+@pytest.mark.parametrize("n", [1, 1023, 2500])
+def test_second_moments_with_and_without_general_options(vp, prec, opt, n):
+    """The kernel of k = 3 instances without general options (no field but the mesh's) and the
+    general one, through a ragged tile, against the primitive steps of the same build."""
+    import torch
+    dt = torch.float64 if prec == "fp64" else torch.float32
+    st = state(n, n, dt, True)
+    a = vp.Simulation(st, L, 64, 0.02, prec, element_order=2, **opt)
+    b = vp.Simulation(st, L, 64, 0.02, prec, element_order=2, **opt)
+    a.step(1)
+    a.sync_state()
+    b.gather_push(0.01, 0.02)
+    b.deposit()
+    b.poisson()
+    b.gather_push(0.01, 0.0)
+    bar = 1e-12 if prec == "fp64" else 1e-6
+    for f in FIELDS + ("Mqq", "Mqp", "Mpp"):
+        assert rel(a.state(0)[f], b.state(0)[f]) <= bar, f
+    a.close()
+    b.close()
