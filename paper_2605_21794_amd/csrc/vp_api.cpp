@@ -126,6 +126,7 @@ struct MeshTables {
 // The scalars of an instance that the host reads: what lies before the barrier's counters.
 static_assert(sizeof(InstDev) % 8 == 0 && sizeof(Tile) % 8 == 0, "uploaded in 64-bit words");
 constexpr size_t kScalHead = offsetof(vpk::InstScal, arrive);
+constexpr size_t kCachedLow = 56u << 20, kCachedHigh = 256u << 20;  // see rebuild_tables
 constexpr size_t kArenaBytes = 256u << 10;  // pinned staging of the table uploads
 
 }  // namespace
@@ -159,6 +160,7 @@ struct vp_handle {
   bool any_fft = false;     // some slot uses the FFT solver (fused launches need more LDS)
   vp_tuning tun{1024, 4, 4, 1, 33, 0, 0};
   bool tuned = false;       // the tuning was set (vp_set_tuning, vp_tune): it is taken as it is
+  bool nontemporal = true;  // fused steps stream the particle arrays past the caches
   int threads = 512, ppt = 4;  // of the launches over the current tiles (ppt: the largest tile's)
   hipGraph_t graph = nullptr;
   hipGraphExec_t gexec = nullptr;
@@ -197,20 +199,22 @@ bool runs_general(const InstDev& d) { return d.general || d.solver == VP_SOLVE_F
 constexpr int kDefaultThreads = 512;
 
 // Particles per thread of a slot's tiles: the tuning's where one was set; by default, at 512
-// threads, 4 up to 2^20 particles (every tile resident at once, two or more to a CU), 8 above,
-// and 16 for the largest float32 states.  us a step at 512 x 4, x 8, x 16 and, before, 1024 x 4
-// (Ng 512, 4 copies): float32 state with float64 sums 2^17 8.1, 10.0, -, 9.6; 2^20 10.7, 10.8,
-// 15.0, 10.6 (11.0 against 10.25 with a ragged tail); 2^21 18.5, 16.0, 17.6, 19.0; 2^22 34.2,
-// 30.2, 29.2, 39.0 (P2 41.0, 34.2, 31.1, 43.6; without dipoles 23.3, 20.3, 18.1, 26.4); 2^23
-// 63.7, 56.7, 57.3, 70.7; float64 2^18 8.8, 11.3, -, 10.8; 2^20 14.4, 16.8, 23.6, 15.5; 2^21
-// 29.0, 27.1, 31.5, 30.9; 2^22 54.2, 52.3, 56.9, 59.1.  Particles with second moments, whose
-// push is longer: 2 up to 2^19 (512 x 2, x 4, x 8; float32 state: 2^18 9.4, 11.0, 14.3; 2^19
-// 11.1, 11.5, 14.6; 2^20 19.0, 15.5, 16.5; 2^21 35.1, 28.9, 27.1), 4 and 8 as the others.
+// threads, 4 while every tile is resident at once (two workgroups to a CU for the float64 state,
+// three for the float32 ones), 8 above, and 16 for the largest float32 states.  us a step at
+// 512 x 4, x 8, x 16 and, before, 1024 x 4 (Ng 512, 4 copies; the accesses as rebuild_tables
+// picks them): float32 state with float64 sums 2^17 8.1, 10.0, -, 9.6; 2^20 10.9, 11.3, 15.2,
+// 10.6 (11.0 against 10.25 with a ragged tail); 3 * 2^19 13.1, 14.3, 15.9, -; 2^21 18.2, 16.1,
+// 17.7, 19.0; 7 * 2^19 27.8, 26.3, 24.9, -; 2^22 31.2, 27.3, 27.2, 39.0; 2^23 54.2, 50.2, 50.4,
+// 70.7 (2^22 P2 41.0, 34.2, 31.1, 43.6; without dipoles -, 19.9, 18.8, 26.4); float64 2^18 8.8,
+// 11.3, -, 10.8; 2^20 14.0, 16.2, 22.6, 15.5; 3 * 2^19 22.7, 21.0, 22.5, -; 2^22 49.9, 47.2,
+// 49.1, 59.1.  Particles with second moments, whose push is longer: 2 up to 2^19 (512 x 2, x 4,
+// x 8; float32 state: 2^18 9.4, 11.0, 14.3; 2^19 11.1, 11.5, 14.6; 2^20 19.0, 15.5, 16.5; 2^21
+// 35.1, 28.9, 27.1), 4 up to 2^20 and 8 above.
 int ppt_of(const vp_handle* h, const vp_config& c) {
   if (h->tuned) return h->tun.ppt;
-  const bool k3 = c.moment_order == 3;
-  if (c.n <= (1LL << 20)) return k3 && c.n <= (1LL << 19) ? 2 : 4;
-  return c.n >= 7LL << 19 && c.precision != VP_FP64 && !k3 ? 16 : 8;
+  if (c.moment_order == 3) return c.n <= 1LL << 19 ? 2 : c.n <= 1LL << 20 ? 4 : 8;
+  if (c.precision == VP_FP64) return c.n <= 1LL << 20 ? 4 : 8;
+  return c.n <= 3LL << 19 ? 4 : c.n < 7LL << 19 ? 8 : 16;
 }
 int threads_of(const vp_handle* h) { return h->tuned ? h->tun.threads : kDefaultThreads; }
 
@@ -366,6 +370,17 @@ vp_status rebuild_tables(vp_handle* h, vpk::UploadArgs u, int only, bool fold) {
     for (int gi = group_of(s); gi < kGroups; ++gi) h->group_end[gi] += nt;
   }
   h->ntiles = (int)h->h_tiles.size();
+  // States that the Infinity Cache (256 MB) can hold from one step to the next are read and
+  // written with plain accesses; larger ones stream past it, and so do small ones, where it makes
+  // no difference or plain accesses cost a little.  us a step, streamed / plain (512 threads, the
+  // default depth): float32 state 2^20 (21 MB) 10.7 / 11.4; 2^21 16.1 / 16.3; 3 * 2^20 (63 MB)
+  // 21.5 / 21.2; 7 * 2^19 28.6 / 24.9; 2^22 29.0 / 27.2; 2^23 56.7 / 50.3; 3 * 2^22 (252 MB) 78.9
+  // / 72.9; 13 * 2^20 (273 MB) 85.9 / 85.5; 2^25 207 / 225; float64 2^20 (42 MB) 14.0 / 14.1; 3 *
+  // 2^19 (63 MB) 21.2 / 21.0; 2^21 26.8 / 25.2; 2^22 51.7 / 47.2.
+  size_t bytes = 0;
+  for (int s : h->h_occ)
+    bytes += (size_t)h->slots[s].cfg.n * state_elem_size(h->precision) * state_arrays(h->slots[s].cfg);
+  h->nontemporal = bytes < kCachedLow || bytes > kCachedHigh;
   h->any_fft = false;
   for (int s : h->h_occ) h->any_fft = h->any_fft || h->slots[s].cfg.solver == VP_SOLVE_FFT;
   if ((size_t)h->ntiles > h->tiles_cap) {
@@ -416,7 +431,8 @@ hipError_t fused_step(vp_handle* h, int ph) {
       const hipError_t e = vpk::launch_fused(h->precision, h->threads, h->d_inst, h->d_tiles,
                                              b, e_ - b, h->ppt, h->max_ng,
                                              general && h->any_fft, ph, gi < 4 || km, general,
-                                             (gi & 2) != 0 || km, km, h->stream);
+                                             (gi & 2) != 0 || km, km, h->nontemporal,
+                                             h->stream);
       if (e != hipSuccess) return e;
     }
     b = e_;

@@ -78,10 +78,17 @@ __device__ __forceinline__ void stx(VPG T* p, T v) {
 
 // Streaming access to the particle arrays: every element is read and written once per step,
 // so the loads and stores are marked non-temporal (they do not displace cached grid data).
-template <typename T>
-__device__ __forceinline__ T ntld(const VPG T* p) { return __builtin_nontemporal_load(p); }
-template <typename T>
-__device__ __forceinline__ void ntst(VPG T* p, T v) { __builtin_nontemporal_store(v, p); }
+// STREAM = false: plain accesses (see launch_fused).
+template <bool STREAM = true, typename T>
+__device__ __forceinline__ T ntld(const VPG T* p) {
+  if constexpr (STREAM) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <bool STREAM = true, typename T>
+__device__ __forceinline__ void ntst(VPG T* p, T v) {
+  if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+  else *p = v;
+}
 
 // Element index of x = Q * Ng / L: floor, clamped to [0, Ng-1] (NaN maps to 0: fmax returns
 // the number when one operand is NaN), so an LDS index is always in range whatever the state

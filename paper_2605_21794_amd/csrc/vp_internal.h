@@ -125,14 +125,16 @@ size_t particle_lds_bytes(int mode, int max_ng);
 // solver (with lds_fft, general must hold); `p2` true
 // when its instances have P2 elements; `moments` true when its instances carry second
 // moments (InstDev::k3; then dipoles and p2 hold too).
+// `stream`: the particle arrays are read and written non-temporally (as they always are with
+// other than 512 threads, or with general options).
 hipError_t launch_fused(int mode, int tpb, const InstDev* d_inst, const Tile* d_tiles, int tile0,
                         int ntiles, int ppt, int max_ng, bool lds_fft, int phase, bool dipoles,
-                        bool general, bool p2, bool moments, hipStream_t s);
+                        bool general, bool p2, bool moments, bool stream, hipStream_t s);
 // The same for one precision mode (vpk::Mode), defined in the unit compiled for that mode.
 template <int MODE>
 hipError_t launch_fused_mode(int tpb, const InstDev* d_inst, const Tile* d_tiles, int tile0,
                              int ntiles, int ppt, int max_ng, bool lds_fft, int phase, bool dipoles,
-                             bool general, bool p2, bool moments, hipStream_t s);
+                             bool general, bool p2, bool moments, bool stream, hipStream_t s);
 hipError_t launch_deposit(int mode, int tpb, const InstDev* d_inst, const Tile* d_tiles, int tile0,
                           int ntiles, int ppt, int max_ng, int phase, hipStream_t s);
 hipError_t launch_gather_push(int mode, int tpb, const InstDev* d_inst, const Tile* d_tiles,

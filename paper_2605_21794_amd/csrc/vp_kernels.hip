@@ -639,20 +639,20 @@ size_t particle_lds_bytes(int /*mode*/, int max_ng) {
 
 hipError_t launch_fused(int mode, int tpb, const InstDev* d_inst, const Tile* d_tiles, int tile0,
                         int ntiles, int ppt, int max_ng, bool lds_fft, int phase, bool dipoles,
-                        bool general, bool p2, bool moments, hipStream_t s) {
+                        bool general, bool p2, bool moments, bool stream, hipStream_t s) {
   switch (mode) {
     case kFP64:
       return launch_fused_mode<kFP64>(tpb, d_inst, d_tiles, tile0, ntiles, ppt, max_ng, lds_fft,
-                                      phase, dipoles, general, p2, moments, s);
+                                      phase, dipoles, general, p2, moments, stream, s);
     case kFP32Comp:
       return launch_fused_mode<kFP32Comp>(tpb, d_inst, d_tiles, tile0, ntiles, ppt, max_ng,
-                                          lds_fft, phase, dipoles, general, p2, moments, s);
+                                          lds_fft, phase, dipoles, general, p2, moments, stream, s);
     case kFP32:
       return launch_fused_mode<kFP32>(tpb, d_inst, d_tiles, tile0, ntiles, ppt, max_ng, lds_fft,
-                                      phase, dipoles, general, p2, moments, s);
+                                      phase, dipoles, general, p2, moments, stream, s);
     default:
       return launch_fused_mode<kFP32TwoSum>(tpb, d_inst, d_tiles, tile0, ntiles, ppt, max_ng,
-                                            lds_fft, phase, dipoles, general, p2, moments, s);
+                                            lds_fft, phase, dipoles, general, p2, moments, stream, s);
   }
 }
 

@@ -32,7 +32,8 @@ def rel(a, b):
 
 @pytest.mark.parametrize("prec,sizes", [
     ("fp64", (1 << 20, (1 << 20) + 1, 9000, 70000)),
-    ("fp32c", ((7 << 19) - 1, 7 << 19, (1 << 20) + 5, 5000))])
+    ("fp32c", ((7 << 19) - 1, 7 << 19, (3 << 19) + 5, 5000)),
+    ("fp32c", ((3 << 19), 3000)), ("fp32c", ((7 << 19) - 2,))])   # streamed; plain accesses
 def test_tiles_of_several_depths_in_one_launch(vp, prec, sizes):
     import torch
     dt = torch.float64 if prec == "fp64" else torch.float32
