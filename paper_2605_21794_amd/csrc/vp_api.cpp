@@ -139,7 +139,7 @@ struct vp_handle {
   std::vector<InstDev> h_inst;
   std::vector<Tile> h_tiles;
   std::vector<int> h_occ;
-  InstDev* d_inst = nullptr;  // one allocation holds d_inst, d_status, d_occ and d_ids
+  InstDev* d_inst = nullptr;  // one allocation holds d_inst, d_status and d_occ
   Tile* d_tiles = nullptr;
   size_t tiles_cap = 0;
   std::vector<Tile> up_tiles;  // what d_tiles and d_occ hold (once the stream gets there)
@@ -154,7 +154,6 @@ struct vp_handle {
   // options, then the instances with second moments
   int group_end[kGroups] = {};
   int* d_occ = nullptr;
-  int* d_ids = nullptr;     // d_ids[i] = i, for single-slot launches
   long long* d_status = nullptr;  // 2 per slot: step, nonfinite (vp_slot_status)
   int max_ng = VP_MIN_NG;   // largest ng of the slots, doubled for P2 (sizes the launches' LDS)
   bool any_fft = false;     // some slot uses the FFT solver (fused launches need more LDS)
@@ -238,13 +237,14 @@ vp_status arena_reserve(vp_handle* h, size_t extra) {
   const size_t bytes = extra + tiles * sizeof(Tile) + slots * (sizeof(InstDev) + sizeof(int)) +
                        sizeof(InstDev) + 5 * 256;
   if (h->arena_off + bytes <= h->arena_bytes) return VP_OK;
-  VP_TRY(sync_stream(h));
+  if (h->arena) VP_TRY(sync_stream(h));
   if (bytes <= h->arena_bytes) return VP_OK;
   if (h->arena) VP_HIP(hipHostFree(h->arena));
   h->arena = nullptr;
   h->arena_bytes = 0;
-  VP_HIP(hipHostMalloc(reinterpret_cast<void**>(&h->arena), 2 * bytes, hipHostMallocDefault));
-  h->arena_bytes = 2 * bytes;
+  const size_t size = std::max(kArenaBytes, 2 * bytes);
+  VP_HIP(hipHostMalloc(reinterpret_cast<void**>(&h->arena), size, hipHostMallocDefault));
+  h->arena_bytes = size;
   return VP_OK;
 }
 
@@ -528,7 +528,7 @@ bool any_p2(const vp_handle* h) {
 vp_status advance_persistent(vp_handle* h, int k) {
   while (k > 0) {
     const int c = std::min(k, kMaxPersistSteps);
-    VP_HIP(vpk::launch_slot_scalars(h->d_inst, h->d_occ, (int)h->h_occ.size(), vpk::kScalPersistStart,
+    VP_HIP(vpk::launch_slot_scalars(h->d_inst, h->d_occ, 0, (int)h->h_occ.size(), vpk::kScalPersistStart,
                                     h->phase, h->stream));
     VP_HIP(vpk::launch_persist(h->precision, h->threads, h->ppt, h->d_inst, h->d_tiles, h->ntiles,
                                h->max_ng, h->any_fft, any_general(h), any_p2(h), h->phase, c,
@@ -598,14 +598,14 @@ vp_status advance(vp_handle* h, int k) {
 
 // Solve the listed slots from the live ring entry and write their field arrays (and the
 // record a fused step still owes).
-vp_status materialise(vp_handle* h, const int* d_slots, int nslots) {
-  VP_HIP(vpk::launch_solve(h->precision, h->d_inst, d_slots, nslots, h->max_ng, h->any_fft, h->phase,
-                           h->stream));
+vp_status materialise(vp_handle* h, const int* d_slots, int first, int nslots) {
+  VP_HIP(vpk::launch_solve(h->precision, h->d_inst, d_slots, first, nslots, h->max_ng, h->any_fft,
+                           h->phase, h->stream));
   return VP_OK;
 }
 
 vp_status materialise_all(vp_handle* h) {
-  VP_TRY(materialise(h, h->d_occ, (int)h->h_occ.size()));
+  VP_TRY(materialise(h, h->d_occ, 0, (int)h->h_occ.size()));
   for (int s : h->h_occ) h->slots[s].solved = true;
   h->field_stale = false;
   return VP_OK;
@@ -614,7 +614,7 @@ vp_status materialise_all(vp_handle* h) {
 // The same for one slot, unless its arrays are those of its live ring entry already.
 vp_status materialise_slot(vp_handle* h, int slot) {
   if (h->slots[slot].solved) return VP_OK;
-  VP_TRY(materialise(h, h->d_ids + slot, 1));
+  VP_TRY(materialise(h, nullptr, slot, 1));
   h->slots[slot].solved = true;
   return VP_OK;
 }
@@ -738,24 +738,16 @@ vp_status vp_engine_create(int32_t precision, int32_t max_slots, void* stream, v
     const unsigned long v = std::strtoul(env, &end, 10);
     if (end != env && *end == '\0' && v < vpk::kSpinLimit) h->spin_limit = (unsigned)v;
   }
-  std::vector<int> ids(max_slots);
-  for (int i = 0; i < max_slots; ++i) ids[i] = i;
   auto pad = [](size_t b) { return (b + 255) & ~size_t(255); };
   const size_t bi = pad(max_slots * sizeof(InstDev)), bst = pad(2 * (size_t)max_slots * sizeof(long long)),
                bo = pad(max_slots * sizeof(int));
   char* block = nullptr;
-  hipError_t e = hipMalloc(&block, bi + bst + 2 * bo);
+  const hipError_t e = hipMalloc(&block, bi + bst + bo);
   if (e == hipSuccess) {
     h->d_inst = reinterpret_cast<InstDev*>(block);
     h->d_status = reinterpret_cast<long long*>(block + bi);
     h->d_occ = reinterpret_cast<int*>(block + bi + bst);
-    h->d_ids = reinterpret_cast<int*>(block + bi + bst + bo);
-    e = hipHostMalloc(reinterpret_cast<void**>(&h->arena), kArenaBytes, hipHostMallocDefault);
-    if (e == hipSuccess) h->arena_bytes = kArenaBytes;
   }
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(h->d_ids, ids.data(), max_slots * sizeof(int), hipMemcpyHostToDevice, h->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) {
     vp_destroy(h);
     return fail(VP_ERR_HIP, "engine allocation: %s", hipGetErrorString(e));
@@ -1006,7 +998,7 @@ vp_status vp_sync_state(vp_handle* h) {
   VP_TRY(materialise_all(h));
   VP_HIP(vpk::launch_settle(h->precision, h->threads, h->d_inst, h->d_tiles, 0, h->ntiles, h->ppt,
                             h->max_ng, h->phase, h->stream));
-  VP_HIP(vpk::launch_slot_scalars(h->d_inst, h->d_occ, (int)h->h_occ.size(), vpk::kScalClearPending,
+  VP_HIP(vpk::launch_slot_scalars(h->d_inst, h->d_occ, 0, (int)h->h_occ.size(), vpk::kScalClearPending,
                                   h->phase, h->stream));
   for (int s : h->h_occ) h->slots[s].pending = false;
   return VP_OK;
@@ -1046,7 +1038,7 @@ vp_status vp_diagnostics(vp_handle* h, int32_t slot, vp_diag* host_out, double* 
   const Slot& sl = h->slots[slot];
   const InstDev& d = h->h_inst[slot];
   VP_TRY(materialise_slot(h, slot));
-  VP_HIP(vpk::launch_slot_scalars(h->d_inst, h->d_ids + slot, 1, vpk::kScalClearDiag, h->phase, h->stream));
+  VP_HIP(vpk::launch_slot_scalars(h->d_inst, nullptr, slot, 1, vpk::kScalClearDiag, h->phase, h->stream));
   VP_HIP(vpk::launch_diag(h->precision, h->threads, h->d_inst, h->d_tiles, sl.tile_begin, sl.ntiles, h->ppt,
                           h->max_ng, h->phase, h->stream));
   vpk::InstScal sc{};

@@ -161,14 +161,15 @@ long long resident_capacity(int mode, bool general, bool p2);
 hipError_t launch_resident(int mode, long long nmax, const InstDev* d_inst, const int* d_slots,
                            int nslots, int max_ng, bool lds_fft, bool general, bool p2, int phase,
                            int nsteps, hipStream_t s);
-// Solve the listed slots from ring entry `phase` and write the field arrays (materialise).
-hipError_t launch_solve(int mode, const InstDev* d_inst, const int* d_slots, int nslots,
+// Solve the listed slots (d_slots NULL: nslots slots from `first` on) from ring entry `phase` and
+// write the field arrays (materialise).
+hipError_t launch_solve(int mode, const InstDev* d_inst, const int* d_slots, int first, int nslots,
                         int max_ng, bool lds_fft, int phase, hipStream_t s);
 // Ring maintenance for the listed slots (RingOp).
 hipError_t launch_ring(int mode, const InstDev* d_inst, const int* d_slots, int nslots, int op,
                        int phase, hipStream_t s);
-hipError_t launch_slot_scalars(const InstDev* d_inst, const int* d_slots, int nslots, int op,
-                               int phase, hipStream_t s);
+hipError_t launch_slot_scalars(const InstDev* d_inst, const int* d_slots, int first, int nslots,
+                               int op, int phase, hipStream_t s);
 // ---------------------------------------------------------------- initialisation (Algorithm 1)
 constexpr int kClusterMinMaxBlocks = 1024;  // partial min / max blocks of the velocity range
 constexpr int kRadixChunk = 1024;           // elements per workgroup in the radix sort

@@ -313,13 +313,14 @@ __global__ __launch_bounds__(TPB) void k_diag(const InstDev* __restrict__ insts,
 // One workgroup per listed slot: solve the field of ring entry `phase` and write the field
 // arrays and the field summary (materialise); when the instance's last pass was a fused
 // step, also write that step's record (the next fused pass would write the same record).
+// slots NULL: the slots first, first + 1, ...
 template <int MODE>
 __global__ __launch_bounds__(kSolveThreads) void k_solve(const InstDev* __restrict__ insts,
-                                                         const int* __restrict__ slots,
+                                                         const int* __restrict__ slots, int first,
                                                          int phase) {
   extern __shared__ double smem[];
   __shared__ double sred[kSolveRed];
-  const InstDev& d = insts[slots[blockIdx.x]];
+  const InstDev& d = insts[slots ? slots[blockIdx.x] : first + (int)blockIdx.x];
   const int ng = d.ng;
   const bool p2 = d.order == 2;
   double* fE = smem;
@@ -444,10 +445,10 @@ __global__ __launch_bounds__(256) void k_ring(const InstDev* __restrict__ insts,
 }
 
 __global__ void k_slot_scalars(const InstDev* __restrict__ insts, const int* __restrict__ slots,
-                               int nslots, int op, int phase) {
+                               int first, int nslots, int op, int phase) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= nslots) return;
-  VPG InstScal* sc = gp(insts[slots[t]].scal);
+  VPG InstScal* sc = gp(insts[slots ? slots[t] : first + t].scal);
   if (op == kScalClearDiag) {
     sc->Kd = 0.0;
     sc->Ud = 0.0;
@@ -692,19 +693,19 @@ hipError_t launch_diag(int mode, int tpb, const InstDev* d_inst, const Tile* d_t
   return hipGetLastError();
 }
 
-hipError_t launch_solve(int mode, const InstDev* d_inst, const int* d_slots, int nslots,
+hipError_t launch_solve(int mode, const InstDev* d_inst, const int* d_slots, int first, int nslots,
                         int max_ng, bool lds_fft, int phase, hipStream_t s) {
   if (nslots <= 0) return hipSuccess;
   const size_t lds = fused_lds_doubles(lds_fft) * (size_t)max_ng * sizeof(double);
   if (mode == kFP64 || mode == kFP32TwoSum)
-    hipLaunchKernelGGL(k_solve<kFP64>, dim3(nslots), dim3(kSolveThreads), lds, s, d_inst, d_slots,
-                       phase);
+    hipLaunchKernelGGL(k_solve<kFP64>, dim3(nslots), dim3(kSolveThreads), lds, s, d_inst,
+                       d_slots, first, phase);
   else if (mode == kFP32Comp)
     hipLaunchKernelGGL(k_solve<kFP32Comp>, dim3(nslots), dim3(kSolveThreads), lds, s, d_inst,
-                       d_slots, phase);
+                       d_slots, first, phase);
   else
-    hipLaunchKernelGGL(k_solve<kFP32>, dim3(nslots), dim3(kSolveThreads), lds, s, d_inst, d_slots,
-                       phase);
+    hipLaunchKernelGGL(k_solve<kFP32>, dim3(nslots), dim3(kSolveThreads), lds, s, d_inst,
+                       d_slots, first, phase);
   return hipGetLastError();
 }
 
@@ -718,11 +719,11 @@ hipError_t launch_ring(int mode, const InstDev* d_inst, const int* d_slots, int 
   return hipGetLastError();
 }
 
-hipError_t launch_slot_scalars(const InstDev* d_inst, const int* d_slots, int nslots, int op,
-                               int phase, hipStream_t s) {
+hipError_t launch_slot_scalars(const InstDev* d_inst, const int* d_slots, int first, int nslots,
+                               int op, int phase, hipStream_t s) {
   if (nslots <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_slot_scalars, dim3((nslots + 63) / 64), dim3(64), 0, s, d_inst, d_slots,
-                     nslots, op, phase);
+                     first, nslots, op, phase);
   return hipGetLastError();
 }
 
