@@ -34,6 +34,9 @@ namespace {
 
 constexpr double kTwoPi = 6.283185307179586;
 
+// Cells of the search grid per centre over the markers' bounding box.
+constexpr double kCellsPerCentre = 1.0;
+
 struct Grid {
   int gx, gp;
   double sx, sp, pmin;  // cell width in q, height in p, lower edge in p
@@ -48,6 +51,14 @@ __device__ __forceinline__ int grid_cell(const Grid& g, double q, double p, int*
   *cy = y;
   return y * g.gx + x;
 }
+
+// A marker as the passes visit it: in cell order, 32 bytes, so that placing one and fetching one
+// out of order each touch a single 32-byte sector (as four arrays they touched four).
+struct alignas(32) Marker {
+  double q, p, w;
+  int id;  // marker index (position in the batch)
+  int pad;
+};
 
 // ---------------------------------------------------------------- small helpers
 __global__ void k_fill_int(int* p, long long n, int v) {
@@ -165,12 +176,12 @@ __device__ __forceinline__ void scan_tile(int* __restrict__ in, int n, long long
     }
 }
 
-template <bool ZERO>
+template <int PER, bool ZERO>
 __global__ __launch_bounds__(1024) void k_scan_one(int* __restrict__ in, int n,
                                                    int* __restrict__ out) {
   __shared__ int wt[16];
   int total;
-  scan_tile<16, ZERO>(in, n, 16LL * threadIdx.x, 0, out, wt, &total);
+  scan_tile<PER, ZERO>(in, n, (long long)PER * threadIdx.x, 0, out, wt, &total);
   if (threadIdx.x == 0) out[n] = total;
 }
 
@@ -282,56 +293,46 @@ __global__ void k_marker_count(const double* __restrict__ q, const double* __res
   slot[t] = bin_centre(g, q[i], p[i], cnt);
 }
 
-// perm[place] = t.  With sq: the copies of q, p, w at the place (BATCH_ORDER: at t).
-template <bool BATCH_ORDER>
+// RUNS: the markers' records in cell order; else perm[place] = t, and for a batch (idx) its
+// copies of q, p, w at t.
+template <bool RUNS>
 __global__ void k_marker_place(const double* __restrict__ q, const double* __restrict__ p,
                                const double* __restrict__ w, const int* __restrict__ idx,
                                long long m, Grid g, const int* __restrict__ off,
-                               const int* __restrict__ slot, int* __restrict__ perm,
-                               double* __restrict__ sq, double* __restrict__ sp,
-                               double* __restrict__ sw) {
+                               const int* __restrict__ slot, Marker* __restrict__ rec,
+                               int* __restrict__ perm, double* __restrict__ bq,
+                               double* __restrict__ bp, double* __restrict__ bw) {
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= m) return;
   const long long i = idx ? idx[t] : t;
   const double qi = q[i], pi = p[i];
   int cx, cy;
   const int at = off[grid_cell(g, qi, pi, &cx, &cy)] + slot[t];
-  perm[at] = (int)t;
-  if (sq) {
-    const long long to = BATCH_ORDER ? t : at;
-    sq[to] = qi;
-    sp[to] = pi;
-    sw[to] = w[i];
+  if constexpr (RUNS) {
+    rec[at] = Marker{qi, pi, w[i], (int)t, 0};
+  } else {
+    perm[at] = (int)t;
+    if (idx) {
+      bq[t] = qi;
+      bp[t] = pi;
+      bw[t] = w[i];
+    }
   }
 }
 
-// Nearest centre of each marker (see the file comment).  Markers are taken in cell order, so
-// that neighbouring lanes search the same cells.  SORTED: q, p and assign are in that order
-// too; else they are in marker order, reached through perm.  cnt (SORTED): the marker also
-// counts on its cluster, and slot receives the count before it.
-// prev: assign holds the previous iteration's labels; the distance to that label's centre, as
-// moved since, bounds the search from the start (the centre itself is found again in the
-// lists).
-// The search: the own cell and the ring around it, less the cells beyond the best distance;
-// where the ring's outer edge is nearer than that distance, every further grid row the circle
-// reaches, as one run of cells (an empty cell costs nothing in a run, and the markers in the
-// thin tails of the velocity distribution have circles of thousands of empty cells: taken
-// cell by cell, their wavefronts alone held the pass at 1069 us).  Without any distance to go
-// by (first pass, no centre in the ring) the block doubles until it holds a centre.
-// Bound by the float64 distances and the latency of the centre loads from L2.  4194304 markers
-// and 419430 centres (ten markers a centre): 248 us a pass, against 1515 us with cell lists
-// read through two indirections and square rings searched cell by cell.
-template <bool SORTED>
-__global__ __launch_bounds__(256) void k_assign(
-    const double* __restrict__ q, const double* __restrict__ p, long long m,
-    const int* __restrict__ perm, const double* __restrict__ cq, const double* __restrict__ cp,
-    Grid g, const int* __restrict__ coff, const double2* __restrict__ cc,
+// The label of the centre nearest to (qi, pi).  prev: the marker's label before, or -1; the
+// distance to that label's centre, as moved since, bounds the search from the start (the centre
+// itself is found again in the lists).
+// The search: the own cell and the ring around it, less the cells beyond the best distance; where
+// the ring's outer edge is nearer than that distance, every further grid row the circle reaches,
+// as one run of cells (an empty cell costs nothing in a run, and the markers in the thin tails of
+// the velocity distribution have circles of thousands of empty cells: taken cell by cell, their
+// wavefronts alone held a pass at 1069 us).
+__device__ __forceinline__ int nearest_centre(
+    double qi, double pi, int prev, const double* __restrict__ cq, const double* __restrict__ cp,
+    const Grid& g, const int* __restrict__ coff, const double2* __restrict__ cc,
     const int* __restrict__ clab, const int* __restrict__ origid, const int* __restrict__ lab0,
-    int prev, int* __restrict__ assign, int* __restrict__ cnt, int* __restrict__ slot) {
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= m) return;
-  const long long at = SORTED ? t : perm[t];
-  const double qi = q[at], pi = p[at];
+    int k) {
   int cx, cy;
   grid_cell(g, qi, pi, &cx, &cy);
   // list bounds of the own row and its neighbours, cells cx-1 .. cx+1 (all loads at once)
@@ -347,8 +348,8 @@ __global__ __launch_bounds__(256) void k_assign(
     o[j][3] = row[xr + 1];
   }
   double lim = INFINITY;
-  if (prev) {
-    const int l = assign[at];
+  if (prev >= 0) {
+    const int l = prev;
     const double dq = qi - cq[l], dp = pi - cp[l];
     const double d0 = dq * dq + dp * dp;
     if (d0 < INFINITY) lim = d0;
@@ -403,23 +404,26 @@ __global__ __launch_bounds__(256) void k_assign(
     if (cy + r < g.gp - 1) d = fmin(d, low(g.pmin + (cy + r + 1) * g.sp - pi, my));
     return d;
   };
-  double d1 = edge(1);
-  if (lim == INFINITY) {
-    for (int r = 2; lim == INFINITY && d1 < INFINITY; r *= 2) {
-      const int xa = max(cx - r, 0), xb = min(cx + r, g.gx - 1);
-      for (int y = max(cy - r, 0); y <= min(cy + r, g.gp - 1); ++y) {
-        const int* row = coff + (long long)y * g.gx;
-        scan(row[xa], row[xb + 1]);
-      }
-      d1 = edge(r);
-      if (r > g.gx && r > g.gp) break;
-    }
+  const double d1 = edge(1);
+  if (lim == INFINITY && d1 < INFINITY) {
+    // nothing to go by: the centres before and after the (empty) own cell in cell order, one of
+    // which is in the own row where that holds any
+    const int s = o[0][1];
+    if (s > 0) take(cc[s - 1], s - 1);
+    if (s < k) take(cc[s], s);
+    lim = fmin(lim, best);
   }
-  if (lim < INFINITY && !(lim < d1 * d1)) {
-    for (int dy = 0; dy < g.gp; ++dy) {
+  if (d1 < INFINITY && !(lim < d1 * d1)) {
+    // rows cy, then cy + 1, cy - 1, cy + 2, ... four at a time: their list bounds are loaded
+    // together (in the tails a circle takes dozens of rows, mostly empty, and the loads of one
+    // after another were the pass's longest chain)
+    for (int k0 = 0;; k0 += 4) {
+      int s0[4], s1[4];
       bool reached = false;
-      for (int up = 0; up < (dy ? 2 : 1); ++up) {
-        const int y = up ? cy - dy : cy + dy;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = k0 + u, dy = (k + 1) >> 1, y = (k & 1) ? cy + dy : cy - dy;
+        s0[u] = s1[u] = 0;
         if (y < 0 || y >= g.gp) continue;
         const double gy = row_gap(y), rest = lim - gy * gy;
         if (rest < 0.0) continue;
@@ -429,16 +433,74 @@ __global__ __launch_bounds__(256) void k_assign(
         const int xa = fa > 0.0 ? (int)fmin(fa, (double)(g.gx - 1)) : 0;
         const int xb = fb < (double)(g.gx - 1) ? (int)fmax(fb, 0.0) : g.gx - 1;
         const int* row = coff + (long long)y * g.gx;
-        scan(row[min(xa, cx)], row[max(xb, cx) + 1]);
+        s0[u] = row[min(xa, cx)];
+        s1[u] = row[max(xb, cx) + 1];
       }
       if (!reached) break;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) scan(s0[u], s1[u]);
     }
   }
   // every centre is binned, so the whole grid holds one, unless every distance was NaN
   // (non-finite or zero-weight input): keep the index in range even then
-  const int l = bs < 0 ? *lab0 : clab[bs];
-  assign[at] = l;
-  if constexpr (SORTED) slot[t] = atomicAdd(cnt + l, 1);
+  return bs < 0 ? *lab0 : clab[bs];
+}
+
+// Nearest centre of each marker, taken in cell order, so that neighbouring lanes search the same
+// cells.  RUNS: from the records, assign is in that order too, the marker also counts on its
+// cluster (cnt), and slot receives the count before it; else q, p and assign are in marker order,
+// reached through perm.  prev: assign holds the previous iteration's labels.
+// Bound by the latency of the list and centre loads from L2 (finer grids, with fewer centres to
+// compare, are no faster).  4194304 markers and 419430 centres, ten markers a centre: 148 us a
+// pass, against 1515 us with cell lists read through two indirections, square rings searched cell
+// by cell and the clusters counted in a pass of their own (159 us).
+// RUNS: a workgroup counts its markers per label in an LDS table and adds each label's count to
+// the global counter once (neighbouring markers share labels; one device atomic per marker, 26
+// per ns over the whole chip, took 150 us of the pass).  ccnt: ncells counters to clear (the next
+// binning's, see k_scan_cells).
+constexpr int kAssignThreads = 256;  // 512 the same within 2%, 1024 5% slower
+template <bool RUNS>
+__global__ __launch_bounds__(kAssignThreads) void k_assign(
+    const Marker* __restrict__ rec, const double* __restrict__ q, const double* __restrict__ p,
+    long long m, const int* __restrict__ perm, const double* __restrict__ cq,
+    const double* __restrict__ cp, Grid g, const int* __restrict__ coff,
+    const double2* __restrict__ cc, const int* __restrict__ clab, const int* __restrict__ origid,
+    const int* __restrict__ lab0, int prev, int* __restrict__ assign, int* __restrict__ cnt,
+    int* __restrict__ slot, int* __restrict__ ccnt, int ncells, int k) {
+  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if constexpr (!RUNS) {
+    if (t >= m) return;
+    const int i = perm[t];
+    assign[i] = nearest_centre(q[i], p[i], prev ? assign[i] : -1, cq, cp, g, coff, cc, clab,
+                               origid, lab0, k);
+  } else {
+    constexpr int kTable = 2 * kAssignThreads;  // twice the labels a workgroup can meet
+    __shared__ int key[kTable], num[kTable];
+    for (long long j = t; j < ncells; j += (long long)gridDim.x * kAssignThreads) ccnt[j] = 0;
+    for (int j = threadIdx.x; j < kTable; j += kAssignThreads) {
+      key[j] = -1;
+      num[j] = 0;
+    }
+    __syncthreads();
+    int h = 0, mine = 0;
+    if (t < m) {
+      const int l = nearest_centre(rec[t].q, rec[t].p, prev ? assign[t] : -1, cq, cp, g, coff, cc,
+                                   clab, origid, lab0, k);
+      assign[t] = l;
+      h = (int)(((unsigned)l * 2654435761u) >> 16) & (kTable - 1);
+      for (;;) {  // at most half of the places are taken: an empty one is met
+        const int was = atomicCAS(key + h, -1, l);
+        if (was == -1 || was == l) break;
+        h = (h + 1) & (kTable - 1);
+      }
+      mine = atomicAdd(num + h, 1);
+    }
+    __syncthreads();
+    for (int j = threadIdx.x; j < kTable; j += kAssignThreads)
+      if (key[j] >= 0) num[j] = atomicAdd(cnt + key[j], num[j]);
+    __syncthreads();
+    if (t < m) slot[t] = num[h] + mine;
+  }
 }
 
 // Members of each cluster, in any order: mem[off[label] + slot] = place of the marker.
@@ -446,6 +508,66 @@ __global__ void k_member_fill(const int* __restrict__ assign, const int* __restr
                               long long m, const int* __restrict__ off, int* __restrict__ mem) {
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (t < m) mem[off[assign[t]] + slot[t]] = (int)t;
+}
+
+// The scan of the counters and the fill that needs it as one launch, for up to kFusedScan
+// counters: every workgroup scans all of them into LDS for itself (they lie in L2), the first
+// writes the offsets out, and the counters are cleared by the next kernel that may.  A pass over a
+// small marker set is bound by its launches; 40960 markers in 4096 clusters took 7 us for each
+// scan and 3 for each fill.
+constexpr int kFusedScan = 8192;  // 1024 threads x 8
+
+__device__ __forceinline__ void scan_lds(const int* __restrict__ in, int n, int* sh, int* wt,
+                                         int* __restrict__ out) {
+  constexpr int PER = kFusedScan / 1024;
+  const int base = PER * threadIdx.x;
+  int x[PER], t = 0, total;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    x[u] = base + u < n ? in[base + u] : 0;
+    t += x[u];
+  }
+  int run = block_excl(t, wt, &total);
+#pragma unroll
+  for (int u = 0; u < PER; ++u)
+    if (base + u < n) {
+      sh[base + u] = run;
+      if (blockIdx.x == 0) out[base + u] = run;
+      run += x[u];
+    }
+  if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = total;
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(1024) void k_scan_members(const int* __restrict__ cnt, int k,
+                                                       int* __restrict__ off,
+                                                       const int* __restrict__ assign,
+                                                       const int* __restrict__ slot, long long m,
+                                                       int* __restrict__ mem) {
+  __shared__ int sh[kFusedScan], wt[16];
+  scan_lds(cnt, k, sh, wt, off);
+  const long long stride = (long long)gridDim.x * 1024;
+  for (long long t = (long long)blockIdx.x * 1024 + threadIdx.x; t < m; t += stride)
+    mem[sh[assign[t]] + slot[t]] = (int)t;
+}
+
+__global__ __launch_bounds__(1024) void k_scan_cells(const int* __restrict__ ccnt, int ncells,
+                                                     int* __restrict__ coff,
+                                                     const double* __restrict__ cq,
+                                                     const double* __restrict__ cp, int k, Grid g,
+                                                     const int* __restrict__ cslot,
+                                                     double2* __restrict__ cc,
+                                                     int* __restrict__ clab) {
+  __shared__ int sh[kFusedScan], wt[16];
+  scan_lds(ccnt, ncells, sh, wt, coff);
+  const int stride = gridDim.x * 1024;
+  for (int l = blockIdx.x * 1024 + threadIdx.x; l < k; l += stride) {
+    const double qa = cq[l], pa = cp[l];
+    int cx, cy;
+    const int s = sh[grid_cell(g, qa, pa, &cx, &cy)] + cslot[l];
+    cc[s] = make_double2(qa, pa);
+    clab[s] = l;
+  }
 }
 
 // Where a kernel of one thread per cluster leaves a centre that moved (or, without members,
@@ -472,7 +594,7 @@ struct CentreOut {
 // It replaces three passes of a stable radix sort (430 us), the counting of the clusters in
 // marker order (159 us) and one thread per cluster gathering from the markers at random
 // (251 us; 687 us for the moments).
-constexpr int kGroupCap = 1024;
+constexpr int kGroupCap = 512;  // 1024: 3 to 5% slower (fewer workgroups to a CU)
 constexpr int kGroupThreads = 256;
 // Mean members per cluster up to which the runs are used: a member compares itself with its
 // whole cluster, and a cluster has to fit a run with room for uneven ones.
@@ -490,10 +612,9 @@ struct MomentOut {
 
 template <int WORK>
 __global__ __launch_bounds__(kGroupThreads) void k_group(
-    const double* __restrict__ q, const double* __restrict__ p, const double* __restrict__ w,
-    const int* __restrict__ perm, const int* __restrict__ assign, const int* __restrict__ off,
+    const Marker* __restrict__ rec, const int* __restrict__ assign, const int* __restrict__ off,
     const int* __restrict__ mem, int k, int per, Grid g, double L, CentreOut co, MomentOut mo,
-    const int* __restrict__ origid, int* __restrict__ over) {
+    const int* __restrict__ origid, int* __restrict__ over, int* __restrict__ cnt) {
   constexpr int kSlots = kGroupCap / kGroupThreads;
   __shared__ int soff[kGroupThreads + 1];
   __shared__ int sidx[kGroupCap];
@@ -503,6 +624,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_group(
   __shared__ double zp[WORK == kGroupMoments ? kGroupThreads : 1];
   const int tid = threadIdx.x;
   const int a0 = (int)blockIdx.x * per, na = min(per, k - a0);
+  if (cnt && tid < na) cnt[a0 + tid] = 0;  // counted out by k_scan_members
   if (tid <= na) soff[tid] = off[a0 + tid];
   if (tid == 0 && na == kGroupThreads) soff[na] = off[a0 + na];
   __syncthreads();
@@ -520,12 +642,17 @@ __global__ __launch_bounds__(kGroupThreads) void k_group(
       continue;
     }
     const int n = soff[e] - base;
-    int at[kSlots];
+    Marker mk[kSlots];
+    int lab[kSlots];
 #pragma unroll
     for (int u = 0; u < kSlots; ++u) {
       const int j = u * kGroupThreads + tid;
-      at[u] = j < n ? mem[base + j] : 0;
-      if (j < n) sidx[j] = perm[at[u]];
+      if (j < n) {
+        const int at = mem[base + j];
+        mk[u] = rec[at];
+        lab[u] = assign[at];
+        sidx[j] = mk[u].id;
+      }
     }
     __syncthreads();
     int pos[kSlots], own[kSlots];
@@ -534,15 +661,15 @@ __global__ __launch_bounds__(kGroupThreads) void k_group(
       const int j = u * kGroupThreads + tid;
       pos[u] = own[u] = 0;
       if (j < n) {
-        const int l = assign[at[u]] - a0, i = sidx[j];
+        const int l = lab[u] - a0, i = mk[u].id;
         const int b = soff[l] - base, f = soff[l + 1] - base;
         int r = b;
         for (int x = b; x < f; ++x) r += sidx[x] < i;
         own[u] = l;
         pos[u] = r;
-        lq[r] = q[at[u]];
-        lp[r] = p[at[u]];
-        lw[r] = w[at[u]];
+        lq[r] = mk[u].q;
+        lp[r] = mk[u].p;
+        lw[r] = mk[u].w;
       }
     }
     __syncthreads();
@@ -817,12 +944,12 @@ __global__ void k_compact(const int* __restrict__ pos, int k, MomentOut mo,
   psi[j] = mo.psi[a];
 }
 
-// The caller's cluster number of each marker (perm NULL: assign is in marker order).
-__global__ void k_assign_out(const int* __restrict__ assign, const int* __restrict__ perm,
+// The caller's cluster number of each marker (rec NULL: assign is in marker order).
+__global__ void k_assign_out(const int* __restrict__ assign, const Marker* __restrict__ rec,
                              const int* __restrict__ origid, long long m,
                              int* __restrict__ out) {
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < m) out[perm ? perm[t] : t] = origid[assign[t]];
+  if (t < m) out[rec ? rec[t].id : t] = origid[assign[t]];
 }
 
 __global__ void k_absorbed_out(const double* __restrict__ v, const int* __restrict__ origid,
@@ -856,7 +983,8 @@ size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
 template <bool ZERO>
 hipError_t scan_int(int* in, int n, int* out, int* tmp, hipStream_t s) {
   if (n <= kScanOne) {
-    hipLaunchKernelGGL(k_scan_one<ZERO>, dim3(1), dim3(1024), 0, s, in, n, out);
+    if (n <= 4096) hipLaunchKernelGGL((k_scan_one<4, ZERO>), dim3(1), dim3(1024), 0, s, in, n, out);
+    else hipLaunchKernelGGL((k_scan_one<16, ZERO>), dim3(1), dim3(1024), 0, s, in, n, out);
     return hipGetLastError();
   }
   const int nt = (n - 1) / kScanTile + 1;
@@ -928,13 +1056,12 @@ ClusterWs cluster_layout(long long m, int k, int batch, bool runs) {
   w.bcnt = o;    o = a256(o + (batch > 0 ? (size_t)gmax : 0) * sizeof(int));
   w.boff = o;    o = a256(o + (batch > 0 ? (size_t)gmax + 1 : 0) * sizeof(int));
   w.bad = o;     o = a256(o + 8 * sizeof(int));
-  // the runs' regions: the sorted copies of q and p lie where the radix sort would keep its
-  // keys and values (two regions of 4 m bytes each hold one of 8 m)
-  w.sq = w.keys_a;
-  w.sp = w.keys_b;
-  w.slot = o;    o = a256(o + (runs ? (size_t)m : 0) * sizeof(int));
-  w.mem = o;     o = a256(o + (runs ? (size_t)m : 0) * sizeof(int));
-  w.sw = o;      o = a256(o + (runs ? (size_t)m : 0) * sizeof(double));
+  // the runs' regions: the slots and members lie where the radix sort would keep its keys and
+  // values; the markers' records, and a batch's
+  w.slot = w.keys_a;
+  w.mem = w.vals_a;
+  w.rec = o;     o = a256(o + (runs ? (size_t)m : 0) * sizeof(Marker));
+  w.brec = o;    o = a256(o + (runs ? nb : 0) * sizeof(Marker));
   w.total = o;
   return w;
 }
@@ -1067,18 +1194,19 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
   int* over = ints(lay.bad) + 3;
   int* res = ints(lay.bad) + 4;
   double2* cc = reinterpret_cast<double2*>(base + lay.cc);
-  double *sq = doubles(lay.sq), *sp = doubles(lay.sp), *sw = doubles(lay.sw);
+  Marker* rec = reinterpret_cast<Marker*>(base + lay.rec);
+  Marker* brec = reinterpret_cast<Marker*>(base + lay.brec);
   int *slot = ints(lay.slot), *mem = ints(lay.mem);
   const CentreOut co{doubles(lay.cq), doubles(lay.cp), doubles(lay.v), ccnt, ints(lay.flag)};
   const MomentOut mo{doubles(lay.tQ), doubles(lay.tP), doubles(lay.tqs), doubles(lay.tps),
                      doubles(lay.tpsi), ints(lay.flag)};
   int* order = nullptr;
 
-  // grid of about one centre per cell over [0, L) x [pmin, pmax]
+  // grid over [0, L) x [pmin, pmax] (see kCellsPerCentre)
   Grid g{};
   const double span = pmax > pmin ? pmax - pmin : 1.0;
   const long long gmax = cluster_max_cells(k);
-  double cell = sqrt(L * span / (double)k);
+  double cell = sqrt(L * span / (kCellsPerCentre * (double)k));
   for (;;) {
     const double gx = ceil(L / cell), gp = ceil(span / cell);
     if (gx * gp <= (double)gmax) {
@@ -1094,6 +1222,7 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
   const int G = g.gx * g.gp;
 
   const dim3 tb(256), mb(blocks_for(m, 256)), kb(blocks_for(k, 256));
+  const dim3 ta(kAssignThreads), ma(blocks_for(m, kAssignThreads));
   hipError_t e = hipSuccess;
 #define VP_LAUNCH(kernel, grid, block, ...)                                     \
   do {                                                                         \
@@ -1111,14 +1240,26 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
   // the markers in grid-cell order (the grid stays fixed): the assignment's visiting order
   VP_LAUNCH(k_marker_count, mb, tb, q, p, (const int*)nullptr, m, g, ccnt, assign);
   VP_CALL(scan_int<true>(ccnt, G, coff, stmp, s));
-  VP_LAUNCH(k_marker_place<false>, mb, tb, q, p, w, (const int*)nullptr, m, g, coff, assign, perm,
-            runs ? sq : nullptr, sp, sw);
+  if (runs)
+    VP_LAUNCH(k_marker_place<true>, mb, tb, q, p, w, (const int*)nullptr, m, g, coff, assign, rec,
+              perm, nullptr, nullptr, nullptr);
+  else
+    VP_LAUNCH(k_marker_place<false>, mb, tb, q, p, w, (const int*)nullptr, m, g, coff, assign, rec,
+              perm, nullptr, nullptr, nullptr);
   // the centres, renumbered in cell order
   VP_LAUNCH(k_init_bin, kb, tb, q, p, init_idx, k, g, ccnt, co.cslot);
   VP_CALL(scan_int<true>(ccnt, G, coff, stmp, s));
   VP_LAUNCH(k_init_labels, kb, tb, q, p, init_idx, k, g, coff, co.cslot, co.cq, co.cp, origid, cc,
             clab, lab0);
+  const bool fused = runs && k <= kFusedScan && G <= kFusedScan;
+  int* const cnt0 = fused ? cnt : nullptr;  // cleared by k_group
+  const int cells0 = fused ? G : 0;         // cleared by k_assign
   auto bin_centres = [&]() -> hipError_t {  // counted by the kernel that moved the centres
+    if (fused) {
+      VP_LAUNCH(k_scan_cells, dim3(blocks_for(k, 1024)), dim3(1024), ccnt, G, coff, co.cq, co.cp, k,
+                g, co.cslot, cc, clab);
+      return hipSuccess;
+    }
     VP_CALL(scan_int<true>(ccnt, G, coff, stmp, s));
     VP_LAUNCH(k_cell_fill, kb, tb, co.cq, co.cp, k, g, coff, co.cslot, cc, clab);
     return hipSuccess;
@@ -1129,6 +1270,12 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
     return (int)(a < 1 ? 1 : (a > kGroupThreads ? kGroupThreads : a));
   };
   auto group_runs = [&](long long n) -> hipError_t {  // counts and slots are in place
+    if (fused) {
+      const unsigned nb = blocks_for(n, 1024);
+      VP_LAUNCH(k_scan_members, dim3(nb < 512 ? nb : 512), dim3(1024), cnt, k, off, assign, slot, n,
+                mem);
+      return hipSuccess;
+    }
     VP_CALL(scan_int<true>(cnt, k, off, stmp, s));
     VP_LAUNCH(k_member_fill, dim3(blocks_for(n, 256)), tb, assign, slot, n, off, mem);
     return hipSuccess;
@@ -1140,7 +1287,7 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
     // mini-batch updates; the batch's assignment and grouping use the marker arrays (b <= m)
     double *bq = doubles(lay.bq), *bp = doubles(lay.bp), *bw = doubles(lay.bw);
     int *bperm = ints(lay.bperm), *bcnt = ints(lay.bcnt), *boff = ints(lay.boff);
-    const dim3 bb(blocks_for(batch, 256));
+    const dim3 bb(blocks_for(batch, 256)), ba(blocks_for(batch, kAssignThreads));
     const long long nb = batch;
     VP_CALL(launch_fill_zero(co.v, (size_t)k * sizeof(double), s));
     VP_CALL(fill_int(bcnt, G, 0, s));
@@ -1151,18 +1298,18 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
       VP_LAUNCH(k_marker_count, bb, tb, q, p, idx, nb, g, bcnt, assign);
       VP_CALL(scan_int<true>(bcnt, G, boff, stmp, s));
       if (runs) {
-        VP_LAUNCH(k_marker_place<false>, bb, tb, q, p, w, idx, nb, g, boff, assign, bperm, bq, bp,
-                  bw);
-        VP_LAUNCH(k_assign<true>, bb, tb, bq, bp, nb, bperm, co.cq, co.cp, g, coff, cc, clab,
-                  origid, lab0, 0, assign, cnt, slot);
+        VP_LAUNCH(k_marker_place<true>, bb, tb, q, p, w, idx, nb, g, boff, assign, brec, bperm, bq,
+                  bp, bw);
+        VP_LAUNCH(k_assign<true>, ba, ta, brec, bq, bp, nb, bperm, co.cq, co.cp, g, coff, cc, clab,
+                  origid, lab0, 0, assign, cnt, slot, ccnt, cells0, k);
         VP_CALL(group_runs(nb));
-        VP_LAUNCH(k_group<kGroupBatch>, gb, gt, bq, bp, bw, bperm, assign, off, mem, k, per_b, g,
-                  L, co, mo, origid, over);
+        VP_LAUNCH(k_group<kGroupBatch>, gb, gt, brec, assign, off, mem, k, per_b, g, L, co, mo,
+                  origid, over, cnt0);
       } else {
-        VP_LAUNCH(k_marker_place<true>, bb, tb, q, p, w, idx, nb, g, boff, assign, bperm, bq, bp,
-                  bw);
-        VP_LAUNCH(k_assign<false>, bb, tb, bq, bp, nb, bperm, co.cq, co.cp, g, coff, cc, clab,
-                  origid, lab0, 0, assign, cnt, slot);
+        VP_LAUNCH(k_marker_place<false>, bb, tb, q, p, w, idx, nb, g, boff, assign, brec, bperm, bq,
+                  bp, bw);
+        VP_LAUNCH(k_assign<false>, ba, ta, brec, bq, bp, nb, bperm, co.cq, co.cp, g, coff, cc, clab,
+                  origid, lab0, 0, assign, cnt, slot, ccnt, cells0, k);
         VP_CALL(group_markers(nb, k, assign, cnt, off, keys_a, vals_a, keys_b, vals_b, hist, hoff,
                               stmp, &order, s));
         VP_LAUNCH(k_minibatch_update, dim3(blocks_for(k, 64)), dim3(64), bq, bp, bw, off, order, k,
@@ -1175,18 +1322,18 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
   for (int it = 0; it <= iters; ++it) {
     const bool last = it == iters;  // the last pass only assigns, and gives the moments
     if (runs) {
-      VP_LAUNCH(k_assign<true>, mb, tb, sq, sp, m, perm, co.cq, co.cp, g, coff, cc, clab, origid,
-                lab0, it > 0 ? 1 : 0, assign, cnt, slot);
+      VP_LAUNCH(k_assign<true>, ma, ta, rec, q, p, m, perm, co.cq, co.cp, g, coff, cc, clab, origid,
+                lab0, it > 0 ? 1 : 0, assign, cnt, slot, ccnt, cells0, k);
       VP_CALL(group_runs(m));
       if (last)
-        VP_LAUNCH(k_group<kGroupMoments>, gm, gt, sq, sp, sw, perm, assign, off, mem, k, per_m, g,
-                  L, co, mo, origid, over);
+        VP_LAUNCH(k_group<kGroupMoments>, gm, gt, rec, assign, off, mem, k, per_m, g, L, co, mo,
+                  origid, over, cnt0);
       else
-        VP_LAUNCH(k_group<kGroupMean>, gm, gt, sq, sp, sw, perm, assign, off, mem, k, per_m, g, L,
-                  co, mo, origid, over);
+        VP_LAUNCH(k_group<kGroupMean>, gm, gt, rec, assign, off, mem, k, per_m, g, L, co, mo,
+                  origid, over, cnt0);
     } else {
-      VP_LAUNCH(k_assign<false>, mb, tb, q, p, m, perm, co.cq, co.cp, g, coff, cc, clab, origid,
-                lab0, it > 0 ? 1 : 0, assign, cnt, slot);
+      VP_LAUNCH(k_assign<false>, ma, ta, rec, q, p, m, perm, co.cq, co.cp, g, coff, cc, clab, origid,
+                lab0, it > 0 ? 1 : 0, assign, cnt, slot, ccnt, cells0, k);
       VP_CALL(group_markers(m, k, assign, cnt, off, keys_a, vals_a, keys_b, vals_b, hist, hoff,
                             stmp, &order, s));
       if (last)
@@ -1200,7 +1347,7 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
   VP_CALL(scan_int<false>(mo.flag, k, pos, stmp, s));
   VP_LAUNCH(k_compact, kb, tb, pos, k, mo, Q, P, qs, ps, psi, over, res);
   if (assign_out)
-    VP_LAUNCH(k_assign_out, mb, tb, assign, runs ? perm : (const int*)nullptr, origid, m,
+    VP_LAUNCH(k_assign_out, mb, tb, assign, runs ? rec : (const Marker*)nullptr, origid, m,
               assign_out);
 #undef VP_LAUNCH
 #undef VP_CALL

@@ -183,7 +183,7 @@ inline long long radix_blocks(long long m) { return (m + kRadixChunk - 1) / kRad
 struct ClusterWs {
   size_t cq, cp, assign, cnt, off, perm, keys_a, vals_a, keys_b, vals_b, hist, hoff, origid, ccnt,
       coff, cc, clist, mm, tQ, tP, tqs, tps, tpsi, flag, pos, scan, v, bq, bp, bw, bperm, bcnt,
-      boff, bad, sq, sp, slot, mem, sw, total;
+      boff, bad, slot, mem, rec, brec, total;
 };
 ClusterWs cluster_layout(long long m, int k, int batch, bool runs);
 // The clusters are small enough on average to be grouped by runs.

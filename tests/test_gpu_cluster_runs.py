@@ -22,7 +22,7 @@ def test_runs_and_radix_match_oracle(vp, m, k, iters):
     compare(vp, q, p, w, k, L, iters, init)
 
 
-@pytest.mark.parametrize("bunch", [1023, 1024, 1025, 4000])
+@pytest.mark.parametrize("bunch", [511, 512, 513, 1023, 1025, 4000])
 def test_one_large_cluster(vp, bunch):
     """`bunch` markers at one place, with one starting centre there: their cluster fills a run
     exactly, or does not fit one.  The other clusters are small (mean below 96)."""
@@ -45,3 +45,27 @@ def test_empty_clusters_and_repeated_centres(vp):
     init = np.concatenate([np.arange(150), np.arange(150)])
     got, ref = compare(vp, q, p, w, 300, L, 0, init)
     assert got["Q"].shape[0] == 150
+
+
+@pytest.mark.parametrize("m,k", [(20000, 8192), (20000, 8193), (60000, 7000)])
+def test_scans_fused_with_their_fills(vp, m, k):
+    """At the largest number of counters whose scan runs inside the fills, and one above; the
+    mini-batch form at the same sizes (a batch counts, and clears, the same counters)."""
+    q, p, w, L = landau_markers(m, seed=m + k)
+    rng = np.random.default_rng(k)
+    init = rng.choice(m, k, replace=False)
+    compare(vp, q, p, w, k, L, 2, init)
+    compare_minibatch(vp, q, p, w, k, L, init, rng.integers(0, m, (3, k + 100)))
+
+
+def test_markers_far_from_every_centre(vp):
+    """Markers in empty corners of the grid (the search starts from the neighbours in cell
+    order), some at the very edge, all centres in one thin row."""
+    rng = np.random.default_rng(7)
+    L = 10.0
+    q = np.concatenate([rng.uniform(0, L, 900), [0.0, np.nextafter(L, 0), 0.0, np.nextafter(L, 0), 5.0]])
+    p = np.concatenate([rng.normal(0, 0.01, 900), [-40.0, -40.0, 40.0, 40.0, 39.0]])
+    w = rng.uniform(0.5, 1.5, q.size)
+    init = rng.choice(900, 200, replace=False)
+    for iters in (0, 3):
+        compare(vp, q, p, w, 200, L, iters, init)
