@@ -438,9 +438,15 @@ __device__ __forceinline__ Cplx operator*(Cplx a, Cplx b) {
   return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
 
+// Where the FFT keeps point i and twiddle k in LDS: a double of padding after every 16 points, a
+// pair after every 16 twiddles.  The passes walk both at power-of-two strides, which without
+// padding put 8 to 32 lanes on one bank.
+__host__ __device__ constexpr int fp(int i) { return i + (i >> 4); }
+__host__ __device__ constexpr int ft(int k) { return 2 * (k + (k >> 4)); }
+
 // x <- IDFT(il . DFT(x)) of ng real values by the whole workgroup (unscaled; the result is
-// real and lands in re).  x: the input; re, im: LDS scratch of ng doubles each; tw: cos / sin
-// of 2 pi k / ng, k < ng/2 (LDS); il4: il at the bit-reversed places 4 tid .. 4 tid + 3
+// real and lands in re).  x: the input; re, im: LDS scratch of fp(ng) doubles each; tw: cos / sin
+// of 2 pi k / ng, k < ng/2, at ft(k) (LDS); il4: il at the bit-reversed places 4 tid .. 4 tid + 3
 // (threads below ng/4).  The forward transform decimates in frequency (natural order in,
 // bit-reversed out) and the inverse in time, so no reordering pass is needed; two radix-2
 // levels are taken at a time, four points per thread in registers, and the innermost pair of
@@ -449,7 +455,8 @@ __device__ __forceinline__ Cplx operator*(Cplx a, Cplx b) {
 // call this, and the result does not depend on the workgroup size.
 // Bound by its chain of passes (nine for ng = 1024), each an LDS round trip and a barrier.
 // A fused P2 step of 2^18 float64 particles at ng = 1024: 45.5 us with one wavefront taking
-// the transforms radix 2 with two reordering passes, 19.5 us so.
+// the transforms radix 2 with two reordering passes, 19.5 us so (1024 threads); 17.2 us at 512
+// threads, 16.4 with the padding.
 template <int TPB>
 __device__ void fft_diagonal(const double* x, double* re, double* im, const double* tw, int ng,
                              int m, const double (&il4)[4]) {
@@ -460,10 +467,10 @@ __device__ void fft_diagonal(const double* x, double* re, double* im, const doub
   if (m & 1) {
     for (int i = b; i < half; i += TPB) {
       const double u = x[i], v = x[i + half], d = u - v;
-      re[i] = u + v;
-      im[i] = 0.0;
-      re[i + half] = d * tw[2 * i];
-      im[i + half] = -(d * tw[2 * i + 1]);
+      re[fp(i)] = u + v;
+      im[fp(i)] = 0.0;
+      re[fp(i + half)] = d * tw[ft(i)];
+      im[fp(i + half)] = -(d * tw[ft(i) + 1]);
     }
     __syncthreads();
     real_in = false;
@@ -476,8 +483,8 @@ __device__ void fft_diagonal(const double* x, double* re, double* im, const doub
       Cplx z[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u)
-        z[u] = real_in ? Cplx{x[i + u * q], 0.0} : Cplx{re[i + u * q], im[i + u * q]};
-      const Cplx w1{tw[2 * k], -tw[2 * k + 1]}, w2{tw[4 * k], -tw[4 * k + 1]};
+        z[u] = real_in ? Cplx{x[i + u * q], 0.0} : Cplx{re[fp(i + u * q)], im[fp(i + u * q)]};
+      const Cplx w1{tw[ft(k)], -tw[ft(k) + 1]}, w2{tw[ft(2 * k)], -tw[ft(2 * k) + 1]};
       const Cplx a0 = z[0] + z[2], a1 = z[1] + z[3], a2 = (z[0] - z[2]) * w1;
       const Cplx d = (z[1] - z[3]) * w1, a3{d.im, -d.re};
       z[0] = a0 + a1;
@@ -486,8 +493,8 @@ __device__ void fft_diagonal(const double* x, double* re, double* im, const doub
       z[3] = (a2 - a3) * w2;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        re[i + u * q] = z[u].re;
-        im[i + u * q] = z[u].im;
+        re[fp(i + u * q)] = z[u].re;
+        im[fp(i + u * q)] = z[u].im;
       }
     }
     __syncthreads();
@@ -497,7 +504,7 @@ __device__ void fft_diagonal(const double* x, double* re, double* im, const doub
     const int i = 4 * b;
     Cplx z[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) z[u] = {re[i + u], im[i + u]};
+    for (int u = 0; u < 4; ++u) z[u] = {re[fp(i + u)], im[fp(i + u)]};
     const Cplx a0 = z[0] + z[2], a1 = z[1] + z[3], a2 = z[0] - z[2], d = z[1] - z[3];
     const Cplx a3{d.im, -d.re};
     z[0] = a0 + a1;
@@ -514,8 +521,8 @@ __device__ void fft_diagonal(const double* x, double* re, double* im, const doub
     z[3] = c1 - c3;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      re[i + u] = z[u].re;
-      im[i + u] = z[u].im;
+      re[fp(i + u)] = z[u].re;
+      im[fp(i + u)] = z[u].im;
     }
   }
   __syncthreads();
@@ -525,8 +532,8 @@ __device__ void fft_diagonal(const double* x, double* re, double* im, const doub
       const int k = pos * (ng / (4 * len));
       Cplx z[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) z[u] = {re[i + u * q], im[i + u * q]};
-      const Cplx w1{tw[2 * k], tw[2 * k + 1]}, w2{tw[4 * k], tw[4 * k + 1]};
+      for (int u = 0; u < 4; ++u) z[u] = {re[fp(i + u * q)], im[fp(i + u * q)]};
+      const Cplx w1{tw[ft(k)], tw[ft(k) + 1]}, w2{tw[ft(2 * k)], tw[ft(2 * k) + 1]};
       const Cplx t1 = z[1] * w2, t3 = z[3] * w2;
       const Cplx c0 = z[0] + t1, c1 = z[0] - t1, c2 = (z[2] + t3) * w1, e = (z[2] - t3) * w1;
       const Cplx c3{-e.im, e.re};
@@ -536,17 +543,17 @@ __device__ void fft_diagonal(const double* x, double* re, double* im, const doub
       z[3] = c1 - c3;
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        re[i + u * q] = z[u].re;
-        im[i + u * q] = z[u].im;
+        re[fp(i + u * q)] = z[u].re;
+        im[fp(i + u * q)] = z[u].im;
       }
     }
     __syncthreads();
   }
   if (m & 1) {
     for (int i = b; i < half; i += TPB) {
-      const double u = re[i], t = tw[2 * i] * re[i + half] - tw[2 * i + 1] * im[i + half];
-      re[i] = u + t;
-      re[i + half] = u - t;
+      const double u = re[fp(i)], t = tw[ft(i)] * re[fp(i + half)] - tw[ft(i) + 1] * im[fp(i + half)];
+      re[fp(i)] = u + t;
+      re[fp(i + half)] = u - t;
     }
     __syncthreads();
   }
@@ -715,7 +722,7 @@ __device__ __forceinline__ double solve_total(const double* red, int slot) {
 // and, with want_sum, sum[0..2] = W = (1/2) h sum_e E_e^2 and
 // E1 = (1/Ng) sum_e E_e exp(-2 pi i e / Ng), sum[3..6] = K, momentum, charge, U of the
 // previous pass (its per-tile sums in tile order), in every thread.
-// `fft` is LDS scratch of 3 Ng doubles (FFT solver only).  The FFT is compiled into the GEN
+// `fft` is LDS scratch of 2 fp(Ng) + ft(Ng/2) doubles (FFT solver only).  The FFT is compiled into the GEN
 // instances alone (its registers would cost the scan solver's instances a wave per SIMD).  All threads of the workgroup call
 // it (it holds workgroup barriers; want_sum must be uniform); on return bt, E, g (and phi)
 // are visible to all threads.
@@ -762,7 +769,8 @@ __device__ void solve_compute(const InstDev& d, const SolveIn& in, bool want_sum
   double il4[4] = {0.0, 0.0, 0.0, 0.0};
   if (use_fft) {  // twiddles, and this thread's inverse eigenvalues in bit-reversed places
     const VPG double* tw_g = gp(d.tw);
-    for (int j = tid; j < ng; j += TPB) fft[2 * ng + j] = tw_g[j];
+    double* tw = fft + 2 * fp(ng);
+    for (int j = tid; j < ng; j += TPB) tw[ft(j >> 1) + (j & 1)] = tw_g[j];
     const VPG double* il_g = gp(d.inv_lam);
     if (tid < (ng >> 2))
 #pragma unroll
@@ -831,10 +839,10 @@ __device__ void solve_compute(const InstDev& d, const SolveIn& in, bool want_sum
   } else {
     __syncthreads();  // b~ and the twiddles in LDS
     double* re = fft;
-    fft_diagonal<TPB>(bt, re, fft + ng, fft + 2 * ng, ng, d.log2ng, il4);
+    fft_diagonal<TPB>(bt, re, fft + fp(ng), fft + 2 * fp(ng), ng, d.log2ng, il4);
     const double inv_h = d.inv_h;
     for (int e = tid; e < ng; e += TPB) {
-      const double p0 = re[e] * inv_ng, p1 = re[(e + 1) & mask] * inv_ng;  // Phi
+      const double p0 = re[fp(e)] * inv_ng, p1 = re[fp((e + 1) & mask)] * inv_ng;  // Phi
       E[e] = -(p1 - p0) * inv_h;
       if (phi) phi[e] = p0;
     }
@@ -1148,10 +1156,13 @@ __device__ __forceinline__ T pad_position(const InstDev& d) {
 }
 
 // LDS of the fused kernel, in doubles: E [0, Ng), g [Ng, 2Ng), deposit grid [2Ng, 3Ng),
-// b~ [3Ng, 4Ng), FFT scratch [4Ng, 7Ng) (FFT solver only).  A P2 instance's deposit grid
+// b~ [3Ng, 4Ng), then the FFT scratch (FFT solver only: points and twiddles with their padding,
+// below 3.2 Ng).  A P2 instance's deposit grid
 // has 2Ng nodes, which moves b~ and the scratch up by Ng: the launch sizes its LDS for
 // twice its largest P2 mesh (the `max_ng` of the launch functions).
-__host__ __device__ constexpr size_t fused_lds_doubles(bool fft) { return fft ? 7 : 4; }
+constexpr size_t fused_lds_bytes(bool fft, int max_ng) {
+  return (4 * (size_t)max_ng + (fft ? 2 * fp(max_ng) + ft(max_ng / 2) : 0)) * sizeof(double);
+}
 
 // One fused step of every tile, in phase r:
 //   solve the field of the current positions from ring entry r (every workgroup, redundantly,

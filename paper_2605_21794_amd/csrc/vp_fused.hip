@@ -213,7 +213,7 @@ hipError_t launch_fused_mode(int tpb, const InstDev* d_inst, const Tile* d_tiles
                         bool general, bool p2, bool moments, bool stream, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
   if (moments && (MODE == kFP32 || !dipoles || !p2)) return hipErrorInvalidValue;
-  const size_t lds = fused_lds_doubles(lds_fft) * (size_t)max_ng * sizeof(double);
+  const size_t lds = fused_lds_bytes(lds_fft, max_ng);
 #define VP_FUSED_K(M, TB, ...)                                                               \
   hipLaunchKernelGGL((k_fused<M, TB, __VA_ARGS__>), dim3(ntiles), dim3(TB), lds, s, d_inst,  \
                      d_tiles, tile0, ppt, phase)

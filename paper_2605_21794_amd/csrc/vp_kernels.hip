@@ -329,7 +329,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_solve(const InstDev* __restri
   double* bt = smem + 3 * ng;
   double* fft = smem + 4 * ng;
   // P2: b~ of vertices and midpoints, after the FFT scratch when this instance uses it
-  double* p2b = smem + (d.solver == VP_SOLVE_FFT ? 7 : 4) * ng;
+  double* p2b = smem + (d.solver == VP_SOLVE_FFT ? 8 : 4) * ng;
   SolveIn sin_;
   solve_load<MODE>(d, phase, true, sin_);
   double sum[7];
@@ -696,7 +696,7 @@ hipError_t launch_diag(int mode, int tpb, const InstDev* d_inst, const Tile* d_t
 hipError_t launch_solve(int mode, const InstDev* d_inst, const int* d_slots, int first, int nslots,
                         int max_ng, bool lds_fft, int phase, hipStream_t s) {
   if (nslots <= 0) return hipSuccess;
-  const size_t lds = fused_lds_doubles(lds_fft) * (size_t)max_ng * sizeof(double);
+  const size_t lds = fused_lds_bytes(lds_fft, max_ng);
   if (mode == kFP64 || mode == kFP32TwoSum)
     hipLaunchKernelGGL(k_solve<kFP64>, dim3(nslots), dim3(kSolveThreads), lds, s, d_inst,
                        d_slots, first, phase);

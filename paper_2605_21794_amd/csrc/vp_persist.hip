@@ -333,7 +333,7 @@ int persist_capacity(int mode, int tpb, int ppt, int max_ng, bool lds_fft, bool 
                      bool p2) {
   const void* fn = persist_fn(mode, tpb, ppt, general, p2);
   if (!fn) return 0;
-  const size_t lds = fused_lds_doubles(lds_fft) * (size_t)max_ng * sizeof(double);
+  const size_t lds = fused_lds_bytes(lds_fft, max_ng);
   int per_cu = 0, cus = 0, dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
@@ -347,7 +347,7 @@ hipError_t launch_persist(int mode, int tpb, int ppt, const InstDev* d_inst, con
   if (ntiles <= 0 || nsteps <= 0) return hipSuccess;
   const void* fn = persist_fn(mode, tpb, ppt, general, p2);
   if (!fn) return hipErrorInvalidValue;
-  const size_t lds = fused_lds_doubles(lds_fft) * (size_t)max_ng * sizeof(double);
+  const size_t lds = fused_lds_bytes(lds_fft, max_ng);
   void* args[] = {(void*)&d_inst, (void*)&d_tiles, (void*)&phase, (void*)&nsteps};
   return hipLaunchCooperativeKernel(fn, dim3(ntiles), dim3(tpb), args, (unsigned)lds, s);
 }

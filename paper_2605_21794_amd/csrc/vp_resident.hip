@@ -233,7 +233,7 @@ hipError_t launch_resident(int mode, long long nmax, const InstDev* d_inst, cons
   if (nslots <= 0 || nsteps <= 0) return hipSuccess;
   if (nmax > resident_capacity(mode, general, p2) || (p2 && mode == kFP32))
     return hipErrorInvalidValue;
-  const size_t lds = fused_lds_doubles(lds_fft) * (size_t)max_ng * sizeof(double);
+  const size_t lds = fused_lds_bytes(lds_fft, max_ng);
   const int ppt = nmax <= kResidentThreads ? 1 : nmax <= 2 * kResidentThreads ? 2
                   : nmax <= 4 * kResidentThreads ? 4 : 8;
 #define VP_RES_CASE(M, PP)                                                                   \
