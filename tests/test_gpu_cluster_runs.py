@@ -69,3 +69,19 @@ def test_markers_far_from_every_centre(vp):
     init = rng.choice(900, 200, replace=False)
     for iters in (0, 3):
         compare(vp, q, p, w, 200, L, iters, init)
+
+
+@pytest.mark.parametrize("m,k,batch,nbatch", [
+    (6000, 500, 900, 8),      # six batches ordered at once, then two
+    (6000, 500, 6000, 2),     # a batch of every marker: one at a time
+    (6000, 500, 3000, 2),     # two exactly
+    (3000, 2900, 700, 4),     # about as many cells as markers: no room for two
+    (20000, 1500, 1700, 11),  # eleven at once
+    (2000, 150, 1, 40),       # batches of one marker
+    (4100, 40, 600, 5)])      # above the runs' mean size: one at a time, by the radix sort
+def test_batches_ordered_together(vp, m, k, batch, nbatch):
+    """Several mini-batches are put in cell order at once where their records fit."""
+    q, p, w, L = landau_markers(m, seed=m + batch)
+    rng = np.random.default_rng(batch + nbatch)
+    init = rng.choice(m, k, replace=False)
+    compare_minibatch(vp, q, p, w, k, L, init, rng.integers(0, m, (nbatch, batch)))
