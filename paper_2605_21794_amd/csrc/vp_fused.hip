@@ -9,6 +9,13 @@
 
 namespace vpk {
 
+// Wavefronts per SIMD the registers must leave room for: at six, the float32 state with float64
+// sums and P1 elements keeps three workgroups of 512 threads on a CU (two at 82 registers).
+template <int MODE, int TPB, bool GEN, bool P2>
+constexpr int fused_waves() {
+  return TPB <= 512 && MODE == kFP32Comp && !GEN && !P2 ? 6 : 1;
+}
+
 // DIP = false: every tile of the launch belongs to a monopole-only instance; p* and q* are
 // neither read nor written (20 bytes of particle traffic per update instead of 36).
 // GEN = false: no instance of the launch has general options (d.general) or the FFT solver, so
@@ -17,7 +24,8 @@ namespace vpk {
 // STREAM = false: plain accesses to the particle arrays.  (As a template parameter: chosen by a
 // branch around the loads, the step of 2^20 float64 particles took 15.2 us instead of 14.1.)
 template <int MODE, int TPB, bool DIP, bool GEN, bool P2, bool KM = false, bool STREAM = true>
-__global__ __launch_bounds__(TPB) void k_fused(const InstDev* __restrict__ insts,
+__global__ __launch_bounds__(TPB, (fused_waves<MODE, TPB, GEN, P2>())) void k_fused(
+                                               const InstDev* __restrict__ insts,
                                                const Tile* __restrict__ tiles, int tile0,
                                                int ppt_max, int phase) {
   extern __shared__ double smem[];
@@ -174,35 +182,20 @@ __global__ __launch_bounds__(TPB) void k_fused(const InstDev* __restrict__ insts
     run_group(g);
   }
 
-  // kinetic sums: wave trees, one barrier, one thread stores the workgroup totals in this
-  // tile's slot (the next pass's first tile adds the slots in tile order)
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  Ks = wave_sum(Ks);
-  Ms = wave_sum(Ms);
-  Cs = wave_sum(Cs);
-  if constexpr (GEN) Us = wave_sum(Us);
-  if (lane == 0) {
-    red[4 * wid] = Ks;
-    red[4 * wid + 1] = Ms;
-    red[4 * wid + 2] = Cs;
-    if constexpr (GEN) red[4 * wid + 3] = Us;
-  }
+  // kinetic sums: one tree per wavefront for all of them, one barrier, one thread per sum
+  // stores the workgroup total in this tile's slot while the flush is under way (the next
+  // pass's first tile adds the slots in tile order)
+  constexpr int kSums = GEN ? kKinFields : 3;  // U stays zero (no potential in this instance)
+  double sums[kSums] = {Ks, Ms, Cs};
+  if constexpr (GEN) sums[3] = Us;
+  wave_totals_to(sums, red + kSums * (threadIdx.x >> 6), 1);
   __syncthreads();  // also completes every LDS deposit of the workgroup
-  if (threadIdx.x == 0) {
-    double kb = 0.0, mb = 0.0, cbs = 0.0, ub = 0.0;
-    for (int w = 0; w < TPB / 64; ++w) {
-      kb += red[4 * w];
-      mb += red[4 * w + 1];
-      cbs += red[4 * w + 2];
-      if constexpr (GEN) ub += red[4 * w + 3];
-    }
-    VPG double* slot = gp(d.kin) + ((size_t)r0 * d.kin_cap + tl.local) * kKinFields;
-    slot[0] = kb;
-    slot[1] = mb;
-    slot[2] = cbs;
-    if constexpr (GEN) slot[3] = ub;  // else it stays zero (no potential in this instance)
-  }
   flush<MODE, TPB>(d, sacc, r1, tl.local % d.acc_copies);
+  if (threadIdx.x < kSums) {
+    double t = 0.0;
+    for (int w = 0; w < TPB / 64; ++w) t += red[kSums * w + threadIdx.x];
+    gp(d.kin)[((size_t)r0 * d.kin_cap + tl.local) * kKinFields + threadIdx.x] = t;
+  }
 }
 
 

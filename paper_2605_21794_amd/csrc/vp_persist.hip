@@ -98,19 +98,19 @@ __device__ void persist_bookkeeping(const InstDev& d, const double* fE, const do
 }
 
 // Wavefronts per SIMD the registers must leave room for: two workgroups per CU at 512 x 2, and
-// at 512 x 4 for the float32 state with float64 sums and P1 elements (the number of tiles a
-// launch can hold is part of what persistent tuning accepts); else one.
-template <int MODE, int TPB, int PPT, bool P2>
+// at 512 x 4 for the float32 state with float64 sums, but for P2 elements with general options
+// (the number of tiles a launch can hold is part of what persistent tuning accepts); else one.
+template <int MODE, int TPB, int PPT, bool GEN, bool P2>
 constexpr int persist_waves() {
-  return TPB == 1024 || PPT == 2 || (PPT == 4 && MODE == kFP32Comp && !P2) ? 4 : 2;
+  return TPB == 1024 || PPT == 2 || (PPT == 4 && MODE == kFP32Comp && !(GEN && P2)) ? 4 : 2;
 }
 
 template <int MODE, int TPB, int PPT, bool GEN, bool P2>
-__global__ __launch_bounds__(TPB, (persist_waves<MODE, TPB, PPT, P2>())) void k_persist(const InstDev* __restrict__ insts,
+__global__ __launch_bounds__(TPB, (persist_waves<MODE, TPB, PPT, GEN, P2>())) void k_persist(const InstDev* __restrict__ insts,
                                                  const Tile* __restrict__ tiles, int phase0,
                                                  int nsteps) {
   extern __shared__ double smem[];
-  __shared__ double red[4 * (TPB / 64)];
+  __shared__ double red[kKinFields * (TPB / 64)];
   __shared__ double sred[kSolveRed];
   __shared__ double stw[VP_MAX_NG];                     // first tile: Fourier weights of E1
   __shared__ double skin[kKinFields * kSolveThreads];  // first tile: previous pass's partials
@@ -237,34 +237,16 @@ __global__ __launch_bounds__(TPB, (persist_waves<MODE, TPB, PPT, P2>())) void k_
                                                        &cell[u]);
     pend = 1;
 
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    Ks = wave_sum(Ks);
-    Ms = wave_sum(Ms);
-    Cs = wave_sum(Cs);
-    if constexpr (GEN) Us = wave_sum(Us);
-    if (lane == 0) {
-      red[4 * wid] = Ks;
-      red[4 * wid + 1] = Ms;
-      red[4 * wid + 2] = Cs;
-      red[4 * wid + 3] = Us;
-    }
+    const double sums[kKinFields] = {Ks, Ms, Cs, Us};
+    wave_totals_to(sums, red + kKinFields * (threadIdx.x >> 6), 1);
     __syncthreads();  // also completes every LDS deposit of the workgroup
-    if (threadIdx.x == 0) {
-      double kb = 0.0, mb = 0.0, cbs = 0.0, ub = 0.0;
-      for (int ww = 0; ww < TPB / 64; ++ww) {
-        kb += red[4 * ww];
-        mb += red[4 * ww + 1];
-        cbs += red[4 * ww + 2];
-        if constexpr (GEN) ub += red[4 * ww + 3];
-      }
-      VPG double* slot = gp(d.kin) + ((size_t)r0 * d.kin_cap + tl.local) * kKinFields;
-      gst(slot, kb);
-      gst(slot + 1, mb);
-      gst(slot + 2, cbs);
-      gst(slot + 3, ub);
-      if (first) sc->pend[r1] = 1;
-    }
     flush<MODE, TPB>(d, sacc, r1, tl.local % d.acc_copies);
+    if (threadIdx.x < kKinFields) {  // one thread per sum, while the flush is under way
+      double t = 0.0;
+      for (int ww = 0; ww < TPB / 64; ++ww) t += red[kKinFields * ww + threadIdx.x];
+      gst(gp(d.kin) + ((size_t)r0 * d.kin_cap + tl.local) * kKinFields + threadIdx.x, t);
+      if (first && threadIdx.x == 0) sc->pend[r1] = 1;
+    }
     if (st + 1 < nsteps) {
       __builtin_amdgcn_s_waitcnt(0);  // this wave's flush, slot and clear are performed
       __syncthreads();

@@ -138,10 +138,7 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(
                                                        b[u], w[u], v[0], v[1], v[2], v[3], nullptr,
                                                        &cell[u]);
     pend = 1;
-    wave_sum_n(v);
-    if (lane == 0)
-#pragma unroll
-      for (int f = 0; f < kSums; ++f) red[f * kWaves + wid] = v[f];
+    wave_totals_to(v, red + wid, kWaves);
     __syncthreads();  // also completes every LDS deposit
     if (wid == kWaves - 1) {
       tot = 0.0;
