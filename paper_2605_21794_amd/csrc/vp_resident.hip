@@ -29,8 +29,9 @@ __device__ __forceinline__ double grid_value(const double* sacc, int j) {
 // GEN, P2: as for k_persist.
 //
 // Bound by the push's float64 issue (4096 particles on one CU) and the solve's barriers, with no
-// launch, flush or accumulator load in the step.  4096 float64 particles, Ng 64: 4.2 us a step,
-// against 9.4 us with one launch per step (7.5 us in tiles of 512 x 4).
+// launch, flush or accumulator load in the step.  4096 float64 particles, Ng 64: 3.7 us a step
+// (4.2 before a wavefront's sums shared one tree, wave_totals), against 9.4 us with one launch
+// per step of one tile, 7.5 us in tiles of 512 x 4.
 template <int MODE, int PPT, bool GEN, bool P2>
 __global__ __launch_bounds__(kResidentThreads) void k_resident(
     const InstDev* __restrict__ insts, const int* __restrict__ slots, int phase0, int nsteps) {
@@ -197,7 +198,8 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(
 // registers hold; float32 state with float64 sums 8192 6.6 / 7.1, but with general options or P2
 // elements (which then spill) 4096 6.1 / 8.1 and 8192 10.9 / 8.2; the (hi, lo) pairs 2048 11.9 /
 // 14.7 and 4096 18.4 / 14.7, the naive mode 1024 4.7 / 10.3 and 2048 12.5 / 10.5 (their LDS
-// updates are slow and one CU takes them all).
+// updates are slow and one CU takes them all).  (Measured before wave_totals, which since took
+// 0.5 us off the resident steps and 0.2 off the fused.)
 long long resident_capacity(int mode, bool general, bool p2) {
   switch (mode) {
     case kFP64: return 4LL * kResidentThreads;
