@@ -465,7 +465,8 @@ __device__ __forceinline__ int nearest_centre(
 // RUNS: a workgroup counts its markers per label in an LDS table and adds each label's count to
 // the global counter once (neighbouring markers share labels; one device atomic per marker, 26
 // per ns over the whole chip, took 150 us of the pass).  ccnt: ncells counters to clear (the next
-// binning's, see k_scan_cells).
+// binning's, see k_scan_cells).  over: set once a cluster did not fit a run; the results are void
+// then (cluster_run), and neither labels nor counts change any more.
 constexpr int kAssignThreads = 256;  // 512 the same within 2%, 1024 5% slower
 template <bool RUNS>
 __global__ __launch_bounds__(kAssignThreads) void k_assign(
@@ -474,7 +475,8 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign(
     const double* __restrict__ cp, Grid g, const int* __restrict__ coff,
     const double2* __restrict__ cc, const int* __restrict__ clab, const int* __restrict__ origid,
     const int* __restrict__ lab0, int prev, int* __restrict__ assign, int* __restrict__ cnt,
-    int* __restrict__ slot, int* __restrict__ ccnt, int ncells, int k) {
+    int* __restrict__ slot, int* __restrict__ ccnt, int ncells, int k,
+    const int* __restrict__ over) {
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if constexpr (!RUNS) {
     if (t >= m) return;
@@ -484,6 +486,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign(
   } else {
     constexpr int kTable = 2 * kAssignThreads;  // twice the labels a workgroup can meet
     __shared__ int key[kTable], num[kTable];
+    const bool on = t < m && *over == 0;
     for (long long j = t; j < ncells; j += (long long)gridDim.x * kAssignThreads) ccnt[j] = 0;
     for (int j = threadIdx.x; j < kTable; j += kAssignThreads) {
       key[j] = -1;
@@ -491,7 +494,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign(
     }
     __syncthreads();
     int h = 0, mine = 0;
-    if (t < m) {
+    if (on) {
       const int l = nearest_centre(rec[t].q, rec[t].p, prev ? assign[t] : -1, cq, cp, g, coff, cc,
                                    clab, origid, lab0, k);
       assign[t] = l;
@@ -507,15 +510,17 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign(
     for (int j = threadIdx.x; j < kTable; j += kAssignThreads)
       if (key[j] >= 0) num[j] = atomicAdd(cnt + key[j], num[j]);
     __syncthreads();
-    if (t < m) slot[t] = num[h] + mine;
+    if (on) slot[t] = num[h] + mine;
   }
 }
 
-// Members of each cluster, in any order: mem[off[label] + slot] = place of the marker.
+// Members of each cluster, in any order: mem[off[label] + slot] = place of the marker.  (Nothing
+// once `over` is set: assign may then hold no labels.)
 __global__ void k_member_fill(const int* __restrict__ assign, const int* __restrict__ slot,
-                              long long m, const int* __restrict__ off, int* __restrict__ mem) {
+                              long long m, const int* __restrict__ off, int* __restrict__ mem,
+                              const int* __restrict__ over) {
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < m) mem[off[assign[t]] + slot[t]] = (int)t;
+  if (t < m && *over == 0) mem[off[assign[t]] + slot[t]] = (int)t;
 }
 
 // The scan of the counters and the fill that needs it as one launch, for up to kFusedScan
@@ -551,9 +556,11 @@ __global__ __launch_bounds__(1024) void k_scan_members(const int* __restrict__ c
                                                        int* __restrict__ off,
                                                        const int* __restrict__ assign,
                                                        const int* __restrict__ slot, long long m,
-                                                       int* __restrict__ mem) {
+                                                       int* __restrict__ mem,
+                                                       const int* __restrict__ over) {
   __shared__ int sh[kFusedScan], wt[16];
   scan_lds(cnt, k, sh, wt, off);
+  if (*over) return;  // as k_member_fill
   const long long stride = (long long)gridDim.x * 1024;
   for (long long t = (long long)blockIdx.x * 1024 + threadIdx.x; t < m; t += stride)
     mem[sh[assign[t]] + slot[t]] = (int)t;
@@ -592,8 +599,8 @@ struct CentreOut {
 // `per` consecutive labels, in runs whose members fit kGroupCap; each member's rank in its
 // cluster is the number of members with a smaller marker index (markers are unique), which
 // puts the run's q, p, w into marker order in LDS; one thread per cluster then adds its terms
-// in that order.  A single cluster above kGroupCap is not taken: `over` is set, and the caller
-// runs everything again with the radix sort.
+// in that order.  A single cluster above kGroupCap is not taken: `over` is set, the passes that
+// follow find no members, and the caller runs everything again with the radix sort.
 //   kGroupMean   the centre moves to the weighted mean; a cluster with no members keeps it
 //   kGroupBatch  the mini-batch update (see k_minibatch_update)
 //   kGroupMoments the decorated particle (see k_moments)
@@ -932,7 +939,9 @@ __global__ void k_moments(const double* __restrict__ q, const double* __restrict
   mo.psi[o] = W;
 }
 
-// res[0] = number of decorated particles, res[1] = a run was too large (`over`).
+// res[0] = number of decorated particles, res[1] = a run was too large (`over`): nothing is
+// written then, here and in the two kernels below, so that the caller's arrays, which may be the
+// inputs', are as they were for the second take.
 __global__ void k_compact(const int* __restrict__ pos, int k, MomentOut mo,
                           double* __restrict__ Q, double* __restrict__ P,
                           double* __restrict__ qs, double* __restrict__ ps,
@@ -943,7 +952,7 @@ __global__ void k_compact(const int* __restrict__ pos, int k, MomentOut mo,
     res[0] = pos[k];
     res[1] = *over;
   }
-  if (a >= k || !mo.flag[a]) return;
+  if (a >= k || !mo.flag[a] || *over) return;
   const int j = pos[a];
   Q[j] = mo.Q[a];
   P[j] = mo.P[a];
@@ -955,15 +964,15 @@ __global__ void k_compact(const int* __restrict__ pos, int k, MomentOut mo,
 // The caller's cluster number of each marker (rec NULL: assign is in marker order).
 __global__ void k_assign_out(const int* __restrict__ assign, const Marker* __restrict__ rec,
                              const int* __restrict__ origid, long long m,
-                             int* __restrict__ out) {
+                             int* __restrict__ out, const int* __restrict__ over) {
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < m) out[rec ? rec[t].id : t] = origid[assign[t]];
+  if (t < m && *over == 0) out[rec ? rec[t].id : t] = origid[assign[t]];
 }
 
 __global__ void k_absorbed_out(const double* __restrict__ v, const int* __restrict__ origid,
-                               int k, double* __restrict__ out) {
+                               int k, double* __restrict__ out, const int* __restrict__ over) {
   const int l = blockIdx.x * blockDim.x + threadIdx.x;
-  if (l < k) out[origid[l]] = v[l];
+  if (l < k && *over == 0) out[origid[l]] = v[l];
 }
 
 __global__ void k_copy_int(const int* __restrict__ in, long long n, int* __restrict__ out) {
@@ -1286,11 +1295,11 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
     if (fused) {
       const unsigned nb = blocks_for(n, 1024);
       VP_LAUNCH(k_scan_members, dim3(nb < 512 ? nb : 512), dim3(1024), cnt, k, off, assign, slot, n,
-                mem);
+                mem, over);
       return hipSuccess;
     }
     VP_CALL(scan_int<true>(cnt, k, off, stmp, s));
-    VP_LAUNCH(k_member_fill, dim3(blocks_for(n, 256)), tb, assign, slot, n, off, mem);
+    VP_LAUNCH(k_member_fill, dim3(blocks_for(n, 256)), tb, assign, slot, n, off, mem, over);
     return hipSuccess;
   };
   const int per_m = per_group(m), per_b = per_group(batch);
@@ -1337,13 +1346,13 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
         const Marker* const r = orec + (size_t)t * batch;
         if (runs) {
           VP_LAUNCH(k_assign<true>, ba, ta, r, bq, bp, nb, bperm, co.cq, co.cp, g, coff, cc, clab,
-                    origid, lab0, 0, assign, cnt, slot, ccnt, cells0, k);
+                    origid, lab0, 0, assign, cnt, slot, ccnt, cells0, k, over);
           VP_CALL(group_runs(nb));
           VP_LAUNCH(k_group<kGroupBatch>, gb, gt, r, assign, off, mem, k, per_b, g, L, co, mo,
                     origid, over, cnt0);
         } else {
           VP_LAUNCH(k_assign<false>, ba, ta, r, bq, bp, nb, bperm, co.cq, co.cp, g, coff, cc, clab,
-                    origid, lab0, 0, assign, cnt, slot, ccnt, cells0, k);
+                    origid, lab0, 0, assign, cnt, slot, ccnt, cells0, k, over);
           VP_CALL(group_markers(nb, k, assign, cnt, off, keys_a, vals_a, keys_b, vals_b, hist, hoff,
                                 stmp, &order, s));
           VP_LAUNCH(k_minibatch_update, dim3(blocks_for(k, 64)), dim3(64), bq, bp, bw, off, order,
@@ -1352,7 +1361,6 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
         VP_CALL(bin_centres());
       }
     }
-    if (absorbed_out) VP_LAUNCH(k_absorbed_out, kb, tb, co.v, origid, k, absorbed_out);
     VP_CALL(fill_int(bcnt, G, 0, s));
     VP_CALL(order_markers(bcnt, boff));
   }
@@ -1360,7 +1368,7 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
     const bool last = it == iters;  // the last pass only assigns, and gives the moments
     if (runs) {
       VP_LAUNCH(k_assign<true>, ma, ta, rec, q, p, m, perm, co.cq, co.cp, g, coff, cc, clab, origid,
-                lab0, it > 0 ? 1 : 0, assign, cnt, slot, ccnt, cells0, k);
+                lab0, it > 0 ? 1 : 0, assign, cnt, slot, ccnt, cells0, k, over);
       VP_CALL(group_runs(m));
       if (last)
         VP_LAUNCH(k_group<kGroupMoments>, gm, gt, rec, assign, off, mem, k, per_m, g, L, co, mo,
@@ -1370,7 +1378,7 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
                   origid, over, cnt0);
     } else {
       VP_LAUNCH(k_assign<false>, ma, ta, rec, q, p, m, perm, co.cq, co.cp, g, coff, cc, clab, origid,
-                lab0, it > 0 ? 1 : 0, assign, cnt, slot, ccnt, cells0, k);
+                lab0, it > 0 ? 1 : 0, assign, cnt, slot, ccnt, cells0, k, over);
       VP_CALL(group_markers(m, k, assign, cnt, off, keys_a, vals_a, keys_b, vals_b, hist, hoff,
                             stmp, &order, s));
       if (last)
@@ -1383,9 +1391,11 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
   }
   VP_CALL(scan_int<false>(mo.flag, k, pos, stmp, s));
   VP_LAUNCH(k_compact, kb, tb, pos, k, mo, Q, P, qs, ps, psi, over, res);
+  if (nbatch > 0 && absorbed_out)
+    VP_LAUNCH(k_absorbed_out, kb, tb, co.v, origid, k, absorbed_out, over);
   if (assign_out)
     VP_LAUNCH(k_assign_out, mb, tb, assign, runs ? rec : (const Marker*)nullptr, origid, m,
-              assign_out);
+              assign_out, over);
 #undef VP_LAUNCH
 #undef VP_CALL
   if ((e = hipMemcpyAsync(host_res, res, 2 * sizeof(int), hipMemcpyDeviceToHost, s)) != hipSuccess)
