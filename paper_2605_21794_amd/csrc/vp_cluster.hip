@@ -486,7 +486,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign(
   } else {
     constexpr int kTable = 2 * kAssignThreads;  // twice the labels a workgroup can meet
     __shared__ int key[kTable], num[kTable];
-    const bool on = t < m && *over == 0;
+    const int stop = *over;  // used behind the barrier below, which hides the load
     for (long long j = t; j < ncells; j += (long long)gridDim.x * kAssignThreads) ccnt[j] = 0;
     for (int j = threadIdx.x; j < kTable; j += kAssignThreads) {
       key[j] = -1;
@@ -494,6 +494,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_assign(
     }
     __syncthreads();
     int h = 0, mine = 0;
+    const bool on = t < m && !stop;
     if (on) {
       const int l = nearest_centre(rec[t].q, rec[t].p, prev ? assign[t] : -1, cq, cp, g, coff, cc,
                                    clab, origid, lab0, k);
@@ -520,7 +521,9 @@ __global__ void k_member_fill(const int* __restrict__ assign, const int* __restr
                               long long m, const int* __restrict__ off, int* __restrict__ mem,
                               const int* __restrict__ over) {
   const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < m && *over == 0) mem[off[assign[t]] + slot[t]] = (int)t;
+  if (t >= m) return;
+  const int a = assign[t], at = slot[t], stop = *over;  // one latency for the three
+  if (!stop) mem[off[a] + at] = (int)t;
 }
 
 // The scan of the counters and the fill that needs it as one launch, for up to kFusedScan
@@ -559,8 +562,9 @@ __global__ __launch_bounds__(1024) void k_scan_members(const int* __restrict__ c
                                                        int* __restrict__ mem,
                                                        const int* __restrict__ over) {
   __shared__ int sh[kFusedScan], wt[16];
+  const int stop = *over;
   scan_lds(cnt, k, sh, wt, off);
-  if (*over) return;  // as k_member_fill
+  if (stop) return;  // as k_member_fill
   const long long stride = (long long)gridDim.x * 1024;
   for (long long t = (long long)blockIdx.x * 1024 + threadIdx.x; t < m; t += stride)
     mem[sh[assign[t]] + slot[t]] = (int)t;
