@@ -1196,7 +1196,7 @@ static vp_status cluster_check(int64_t m, int32_t k) {
 vp_status vp_cluster_workspace_bytes(int64_t m, int32_t k, size_t* bytes_out) {
   if (!bytes_out) return fail(VP_ERR_ARG, "NULL argument");
   VP_TRY(cluster_check(m, k));
-  *bytes_out = vpk::cluster_layout(m, k, 0, vpk::cluster_runs(m, k)).total;
+  *bytes_out = vpk::cluster_bytes(m, k, 0);
   return VP_OK;
 }
 
@@ -1261,9 +1261,10 @@ static vp_status cluster_impl(const double* Qm, const double* Pm, const double* 
   if (nbatch > 0 && (!batch_idx || !aligned(batch_idx, 4)))
     return fail(VP_ERR_ARG, "batch_idx NULL or misaligned");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const bool runs = vpk::cluster_runs(m, k);
-  const vpk::ClusterWs lay = vpk::cluster_layout(m, k, nbatch > 0 ? batch : 0, runs);
-  return cluster_checked(Qm, Pm, wm, m, k, init_idx, batch_idx, nbatch > 0 ? batch : 0, nbatch,
+  const int b = nbatch > 0 ? batch : 0;
+  const bool runs = vpk::cluster_runs(m, k, b);
+  const vpk::ClusterWs lay = vpk::cluster_layout(m, k, b, runs);
+  return cluster_checked(Qm, Pm, wm, m, k, init_idx, batch_idx, b, nbatch,
                          iters, L, workspace, lay, runs, s, Q, P, qs, ps, psi, assign_out,
                          absorbed_out, n_out, true);
 }
@@ -1298,7 +1299,7 @@ vp_status vp_cluster_markers_static(const double* Qm, const double* Pm, const do
                 "holds %zu (vp_cluster_markers takes a workspace of any size)",
                 (long long)m, k, lay.total, (size_t)VP_CLUSTER_STATIC_BYTES);
   const vpk::ClusterWs wide = vpk::cluster_layout(m, k, 0, true);
-  const bool runs = vpk::cluster_runs(m, k) && wide.total <= (size_t)VP_CLUSTER_STATIC_BYTES;
+  const bool runs = vpk::cluster_runs(m, k, 0) && wide.total <= (size_t)VP_CLUSTER_STATIC_BYTES;
   if (runs) lay = wide;
   void* ws = nullptr;
   VP_HIP(vpk::cluster_static_workspace(&ws));
@@ -1322,7 +1323,7 @@ vp_status vp_cluster_minibatch_workspace_bytes(int64_t m, int32_t k, int32_t bat
                                                size_t* bytes_out) {
   if (!bytes_out) return fail(VP_ERR_ARG, "NULL argument");
   VP_TRY(minibatch_check(m, k, batch, 1));
-  *bytes_out = vpk::cluster_layout(m, k, batch, vpk::cluster_runs(m, k)).total;
+  *bytes_out = vpk::cluster_bytes(m, k, batch);
   return VP_OK;
 }
 

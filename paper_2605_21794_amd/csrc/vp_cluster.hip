@@ -1029,17 +1029,48 @@ long long scan_tmp_ints(long long n) { return 2 * (n / kScanTile + 2); }
 
 }  // namespace
 
-bool cluster_runs(long long m, int k) { return m <= (long long)kGroupMeanMax * k; }
-
+// What either grouping of the members needs (the runs 40 bytes a marker, the radix sort 22) lies
+// over what the other needs: a call that is taken again by the radix sort starts afresh.  The
+// mini-batches' cell counts lie over the moments of the last pass.
 ClusterWs cluster_layout(long long m, int k, int batch, bool runs) {
   ClusterWs w{};
   const long long gmax = cluster_max_cells(k);
+  const size_t nb = batch > 0 ? (size_t)batch : 0;
   size_t o = 0;
   w.cq = o;      o = a256(o + (size_t)k * sizeof(double));
   w.cp = o;      o = a256(o + (size_t)k * sizeof(double));
   w.assign = o;  o = a256(o + (size_t)m * sizeof(int));
   w.cnt = o;     o = a256(o + (size_t)k * sizeof(int));
   w.off = o;     o = a256(o + (size_t)(k + 1) * sizeof(int));
+  w.origid = o;  o = a256(o + (size_t)k * sizeof(int));
+  w.ccnt = o;    o = a256(o + (size_t)gmax * sizeof(int));
+  w.coff = o;    o = a256(o + (size_t)(gmax + 1) * sizeof(int));
+  w.cc = o;      o = a256(o + (size_t)gmax * sizeof(int));  // >= 16 k bytes
+  w.clist = o;   o = a256(o + (size_t)k * sizeof(int));
+  w.mm = o;      o = a256(o + (size_t)(2 * kClusterMinMaxBlocks + 2) * sizeof(double));
+  w.bcnt = o;    // batches (batch <= m): cells counted, and scanned, before the moments are used
+  w.boff = a256(w.bcnt + (size_t)gmax * sizeof(int));
+  w.tQ = o;      o = a256(o + (size_t)k * sizeof(double));
+  w.tP = o;      o = a256(o + (size_t)k * sizeof(double));
+  w.tqs = o;     o = a256(o + (size_t)k * sizeof(double));
+  w.tps = o;     o = a256(o + (size_t)k * sizeof(double));
+  w.tpsi = o;    o = a256(o + (size_t)k * sizeof(double));
+  if (batch > 0) {
+    const size_t cells = a256(w.boff + (size_t)(gmax + 1) * sizeof(int));
+    o = o < cells ? cells : o;
+  }
+  w.flag = o;    o = a256(o + (size_t)k * sizeof(int));  // the centres' places in their cells before
+  w.pos = o;     o = a256(o + (size_t)(k + 1) * sizeof(int));
+  {
+    long long nmax = 256 * radix_blocks(m);
+    if (nmax < k) nmax = k;
+    if (nmax < gmax) nmax = gmax;
+    if (runs && nmax < m) nmax = m;  // several batches' cells at once
+    w.scan = o;  o = a256(o + (size_t)scan_tmp_ints(nmax) * sizeof(int));
+  }
+  w.v = o;       o = a256(o + (batch > 0 ? (size_t)k : 0) * sizeof(double));
+  w.bad = o;     o = a256(o + 8 * sizeof(int));
+  const size_t o0 = o;
   w.perm = o;    o = a256(o + (size_t)m * sizeof(int));
   w.keys_a = o;  o = a256(o + (size_t)m * sizeof(int));
   w.vals_a = o;  o = a256(o + (size_t)m * sizeof(int));
@@ -1047,44 +1078,39 @@ ClusterWs cluster_layout(long long m, int k, int batch, bool runs) {
   w.vals_b = o;  o = a256(o + (size_t)m * sizeof(int));
   w.hist = o;    o = a256(o + (size_t)256 * radix_blocks(m) * sizeof(int));
   w.hoff = o;    o = a256(o + ((size_t)256 * radix_blocks(m) + 1) * sizeof(int));
-  w.origid = o;  o = a256(o + (size_t)k * sizeof(int));
-  w.ccnt = o;    o = a256(o + (size_t)gmax * sizeof(int));
-  w.coff = o;    o = a256(o + (size_t)(gmax + 1) * sizeof(int));
-  w.cc = o;      o = a256(o + (size_t)gmax * sizeof(int));  // >= 16 k bytes
-  w.clist = o;   o = a256(o + (size_t)k * sizeof(int));
-  w.mm = o;      o = a256(o + (size_t)(2 * kClusterMinMaxBlocks + 2) * sizeof(double));
-  w.tQ = o;      o = a256(o + (size_t)k * sizeof(double));
-  w.tP = o;      o = a256(o + (size_t)k * sizeof(double));
-  w.tqs = o;     o = a256(o + (size_t)k * sizeof(double));
-  w.tps = o;     o = a256(o + (size_t)k * sizeof(double));
-  w.tpsi = o;    o = a256(o + (size_t)k * sizeof(double));
-  w.flag = o;    o = a256(o + (size_t)k * sizeof(int));  // the centres' places in their cells before
-  w.pos = o;     o = a256(o + (size_t)(k + 1) * sizeof(int));
-  {
-    long long nmax = 256 * radix_blocks(m);
-    if (nmax < k) nmax = k;
-    if (nmax < gmax) nmax = gmax;
-    w.scan = o;  o = a256(o + (size_t)scan_tmp_ints(nmax) * sizeof(int));
-  }
-  // mini-batch regions (batch <= m: the batch's assignment and grouping reuse the marker
-  // arrays above)
-  const size_t nb = batch > 0 ? (size_t)batch : 0;
-  w.v = o;       o = a256(o + (batch > 0 ? (size_t)k : 0) * sizeof(double));
   w.bq = o;      o = a256(o + nb * sizeof(double));
   w.bp = o;      o = a256(o + nb * sizeof(double));
   w.bw = o;      o = a256(o + nb * sizeof(double));
   w.bperm = o;   o = a256(o + nb * sizeof(int));
-  w.bcnt = o;    o = a256(o + (batch > 0 ? (size_t)gmax : 0) * sizeof(int));
-  w.boff = o;    o = a256(o + (batch > 0 ? (size_t)gmax + 1 : 0) * sizeof(int));
-  w.bad = o;     o = a256(o + 8 * sizeof(int));
-  // the runs' regions: the slots and members lie where the radix sort would keep its keys and
-  // values; the markers' records, and a batch's
-  w.slot = w.keys_a;
-  w.mem = w.vals_a;
-  w.rec = o;     o = a256(o + (runs ? (size_t)m : 0) * sizeof(Marker));
-  w.brec = o;    o = a256(o + (runs ? nb : 0) * sizeof(Marker));
   w.total = o;
+  if (runs) {
+    o = o0;
+    w.slot = o;  o = a256(o + (size_t)m * sizeof(int));
+    w.mem = o;   o = a256(o + (size_t)m * sizeof(int));
+    w.rec = o;   o = a256(o + (size_t)m * sizeof(Marker));
+    w.brec = o;  o = a256(o + nb * sizeof(Marker));
+    w.total = w.total < o ? o : w.total;
+  }
   return w;
+}
+
+// Up to here a workspace may grow for the runs' sake (their records make it about 1.7 times the
+// radix sort's): a sixteenth of the card.  Beyond, marker sets that fill the card keep the
+// smaller one, and the radix sort.
+constexpr size_t kRunsBytesMax = size_t(16) << 30;
+
+bool cluster_runs(long long m, int k, int batch) {
+  return m <= (long long)kGroupMeanMax * k && cluster_layout(m, k, batch, true).total <= kRunsBytesMax;
+}
+
+// Never less for more markers, clusters or batch markers, though the runs are left at both of
+// their bounds: a workspace of the largest call serves every smaller one.
+size_t cluster_bytes(long long m, int k, int batch) {
+  const size_t radix = cluster_layout(m, k, batch, false).total;
+  const long long mr = m < (long long)kGroupMeanMax * k ? m : (long long)kGroupMeanMax * k;
+  const size_t wide = cluster_layout(mr, k, batch, true).total;
+  const size_t most = wide < kRunsBytesMax ? wide : kRunsBytesMax;
+  return radix < most ? most : radix;
 }
 
 // ---------------------------------------------------------------- allocation-free workspace
@@ -1319,8 +1345,7 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
     // A batch is visited in grid-cell order (a random batch in its own order would send the lanes
     // of a wavefront to unrelated cells); the order does not change any result.  It depends on no
     // centre, so with runs as many batches as fit are ordered at once: their records where the
-    // markers' go later, their counts and offsets where the radix sort would keep keys and
-    // values.  Eight batches of 162500 among 1.3 million markers, 130000 cells: 326 us one at a
+    // markers' go later, their counts and offsets where a batch's slots and members go after.  Eight batches of 162500 among 1.3 million markers, 130000 cells: 326 us one at a
     // time (four launches each, most of them too small to fill the card), 156 us at once.
     long long several = 1;
     if (runs) {
@@ -1328,18 +1353,17 @@ hipError_t cluster_run(const double* q, const double* p, const double* w, long l
       several = several < nbatch ? several : nbatch;
       several = several < 1 ? 1 : (several > 32768 ? 32768 : several);
     }
-    int* const ocnt = several > 1 ? keys_b : bcnt;
-    int* const ooff = several > 1 ? vals_b : boff;
-    int* const otmp = several > 1 ? hist : stmp;  // m / 4 ints at least: scan_tmp_ints(m) and more
+    int* const ocnt = several > 1 ? slot : bcnt;
+    int* const ooff = several > 1 ? mem : boff;
     Marker* const orec = several > 1 ? rec : brec;
-    VP_CALL(fill_int(ocnt, several * G, 0, s));
     for (long long t0 = 0; t0 < nbatch; t0 += several) {
       const int n = (int)(nbatch - t0 < several ? nbatch - t0 : several);
       const int* idx = batch_idx + t0 * batch;
       const dim3 bb(blocks_for(batch, 256), (unsigned)n);
+      if (t0 == 0 || several > 1) VP_CALL(fill_int(ocnt, (long long)n * G, 0, s));
       // the places: in assign, which holds a batch's labels only once they are used
       VP_LAUNCH(k_marker_count, bb, tb, q, p, idx, nb, g, ocnt, assign);
-      VP_CALL(scan_int<true>(ocnt, n * G, ooff, otmp, s));
+      VP_CALL(scan_int<true>(ocnt, n * G, ooff, stmp, s));
       if (runs)
         VP_LAUNCH(k_marker_place<true>, bb, tb, q, p, w, idx, nb, g, ooff, assign, orec, bperm, bq,
                   bp, bw);

@@ -179,15 +179,19 @@ inline long long radix_blocks(long long m) { return (m + kRadixChunk - 1) / kRad
 // Byte offsets of the regions of the caller's clustering workspace (256-byte aligned).
 // `batch` > 0 adds the mini-batch regions (absorbed weights v, the gathered batch, its
 // visiting order) for batches of that many markers (batch <= m).  `runs` adds what grouping
-// the members by runs takes (cluster_run).
+// the members by runs takes (cluster_run); the radix sort's regions are there as well.
 struct ClusterWs {
   size_t cq, cp, assign, cnt, off, perm, keys_a, vals_a, keys_b, vals_b, hist, hoff, origid, ccnt,
       coff, cc, clist, mm, tQ, tP, tqs, tps, tpsi, flag, pos, scan, v, bq, bp, bw, bperm, bcnt,
       boff, bad, slot, mem, rec, brec, total;
 };
 ClusterWs cluster_layout(long long m, int k, int batch, bool runs);
-// The clusters are small enough on average to be grouped by runs.
-bool cluster_runs(long long m, int k);
+// The members are grouped by runs: the clusters are small enough on average, and so is the
+// workspace that takes.
+bool cluster_runs(long long m, int k, int batch);
+// Bytes of the caller's workspace; enough for every call with no more markers, clusters and
+// batch markers.
+size_t cluster_bytes(long long m, int k, int batch);
 // The library's own workspace of vp_cluster_markers_static on the current device (a file-scope
 // device array of VP_CLUSTER_STATIC_BYTES, its address looked up once per device).
 hipError_t cluster_static_workspace(void** ptr_out);
