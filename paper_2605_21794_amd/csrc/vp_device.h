@@ -771,6 +771,8 @@ __device__ __forceinline__ double solve_total(const double* red, int slot) {
 // and, with want_sum, sum[0..2] = W = (1/2) h sum_e E_e^2 and
 // E1 = (1/Ng) sum_e E_e exp(-2 pi i e / Ng), sum[3..6] = K, momentum, charge, U of the
 // previous pass (its per-tile sums in tile order), in every thread.
+// `huge` (LDS, when given) is set to 4 where a value of the field or a midpoint load is 1e150 or
+// more, so that the sum of their squares may overflow.
 // `fft` is LDS scratch of 2 fp(Ng) + ft(Ng/2) doubles (FFT solver only).  The FFT is compiled into the GEN
 // instances alone (its registers would cost the scan solver's instances a wave per SIMD).  All threads of the workgroup call
 // it (it holds workgroup barriers; want_sum must be uniform); on return bt, E, g (and phi)
@@ -788,7 +790,10 @@ __device__ __forceinline__ double solve_total(const double* red, int slot) {
 template <int TPB, bool GEN = true, bool P2 = GEN>
 __device__ void solve_compute(const InstDev& d, const SolveIn& in, bool want_sum, double* bt,
                               double* E, double* g, double* red, double* fft, double* phi,
-                              double* sum, double* p2b = nullptr) {
+                              double* sum, double* p2b = nullptr, int* huge = nullptr) {
+  const auto note = [&](double v) {
+    if (huge && !(fabs(v) < 1e150)) *huge = 4;
+  };
   const int ng = d.ng, mask = ng - 1, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int per = solve_per(ng), j0 = tid * per;
   const bool solver_thread = tid < kSolveThreads;           // whole waves
@@ -839,6 +844,7 @@ __device__ void solve_compute(const InstDev& d, const SolveIn& in, bool want_sum
         x = (in.b[k] + 0.5 * (g[(j - 1) & mask] + g[j])) - mean;
         const double bmt = in.bm[k] - (2.0 / 3.0) * mean;
         wmid += bmt * bmt;
+        note(bmt);
         if (p2b) {
           p2b[j] = in.b[k] - mean / 3.0;
           p2b[ng + j] = bmt;
@@ -872,6 +878,7 @@ __device__ void solve_compute(const InstDev& d, const SolveIn& in, bool want_sum
         if (k < per) {
           const double Ee = (S[k] + off) + C;
           E[j0 + k] = Ee;
+          note(Ee);
           wp += Ee * Ee;
           er += Ee * in.c[k];
           ei -= Ee * in.s[k];
@@ -890,6 +897,7 @@ __device__ void solve_compute(const InstDev& d, const SolveIn& in, bool want_sum
     for (int e = tid; e < ng; e += TPB) {
       const double p0 = re[fp(e)] * inv_ng, p1 = re[fp((e + 1) & mask)] * inv_ng;  // Phi
       E[e] = -(p1 - p0) * inv_h;
+      note(E[e]);
       if (phi) phi[e] = p0;
     }
     if (want_sum) {
@@ -979,8 +987,8 @@ __device__ void solve_compute(const InstDev& d, const SolveIn& in, bool want_sum
 
 // Record of integer step `step` (kinetic and potential sums of that step's pass, field
 // summary of its field) into slot `slot` of the history ring, which the caller keeps equal
-// to step mod hist_cap; flags non-finite values.  One thread.
-static __device__ void write_record_at(const InstDev& d, int slot, long long step, double K,
+// to step mod hist_cap.  One thread.
+static __device__ void store_record_at(const InstDev& d, int slot, long long step, double K,
                                        double mom, double chg, double U, double W, double e1r,
                                        double e1i) {
   if (!d.self_on) W = e1r = e1i = 0.0;  // no field of their own acts on the particles
@@ -997,6 +1005,12 @@ static __device__ void write_record_at(const InstDev& d, int slot, long long ste
   r[9] = e1i;
   r[10] = U;
   r[11] = (double)wall_clock64();  // device constant-rate clock when the record is written
+}
+// The same, and non-finite values are flagged.
+static __device__ void write_record_at(const InstDev& d, int slot, long long step, double K,
+                                       double mom, double chg, double U, double W, double e1r,
+                                       double e1i) {
+  store_record_at(d, slot, step, K, mom, chg, U, W, e1r, e1i);
   if (!isfinite(K) || !isfinite(W) || !isfinite(U)) gp(d.scal)->nonfinite = 1;
 }
 // The same, the slot computed here.

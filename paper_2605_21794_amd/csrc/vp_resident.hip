@@ -25,7 +25,11 @@ __device__ __forceinline__ double grid_value(const double* sacc, int j) {
 // next phase, the per-tile sums and the scalars are left as a fused pass leaves them, so the two
 // can follow one another.  The record of a step is written in that step (its field summary and
 // kinetic sums are both here), by the last wavefront while the others go on to the next solve.
-// An instance that turns non-finite stops where the fused steps would have frozen it.
+// An instance that turns non-finite stops where the fused steps would have frozen it: before the
+// next pass when W (or E) did, after it when K or U did, which is then flagged (in the last pass
+// it is left to whoever takes the owed record).  W is known after its pass only; waiting for it
+// in every pass took 0.12 to 0.2 us a step, so a pass whose field is near overflow waits, others
+// do not.
 // GEN, P2: as for k_persist.
 //
 // Bound by the push's float64 issue (4096 particles on one CU) and the solve's barriers, with no
@@ -40,7 +44,9 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(
   extern __shared__ double smem[];
   __shared__ double red[kSums * kWaves];
   __shared__ double sred[kSolveRed];
-  __shared__ int nonfinite_k;  // the kinetic sums of the pass before came out NaN or Inf
+  // of the last pass: nonfinite: 1 its kinetic sums came out NaN or Inf, 2 its W; huge: 4 its field
+  // was near overflow
+  __shared__ int nonfinite, huge;
   using T = typename StateType<MODE>::T;
   const InstDev& d = insts[slots[blockIdx.x]];
   const int ng = d.ng, n = (int)d.n, tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -79,7 +85,7 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(
   }
   const long long step0 = sc->step;
   int pend = sc->pend[phase0];
-  if (tid == 0) nonfinite_k = 0;
+  if (tid == 0) nonfinite = huge = 0;
   __syncthreads();
   if (tid == TPB - 64 && pend && step0 >= 1) {  // the record the previous pass still owes
     const int r2 = ring_prev(phase0);
@@ -88,73 +94,85 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(
     for (int t = 0; t < d.ntiles; ++t)
       for (int f = 0; f < kKinFields; ++f) s[f] += kin[t * kKinFields + f];
     write_record(d, step0 - 1, s[0], s[1], s[2], s[3], sc->W[r2], sc->e1r[r2], sc->e1i[r2]);
-    if (!isfinite(s[0]) || !isfinite(s[3])) nonfinite_k = 1;
+    if (!isfinite(s[0]) || !isfinite(s[3])) nonfinite = 1;
   }
 
   const int per = solve_per(ng), j0 = tid * per;
   const bool owner = tid < kSolveThreads && j0 < ng;  // of nodes j0 .. j0 + per - 1
-  const double wp2 = 0.1875 * ((4.0 / 9.0) * d.h * d.h);  // P2: W from phi_h'' (see k_persist)
   double tot = 0.0;  // last wavefront, lane f: sum f of the last pass
   int done = 0;
-  for (bool stop = false; done < nsteps && !stop;) {
-    // nothing is hoisted out of the step loop: keeps the step's registers per step
-    __asm__ __volatile__("" ::: "memory");
-    SolveIn in;
-    if (done == 0) {
-      solve_load<MODE, false, GEN, P2>(d, phase0, false, in);
-      for (int j = tid; j < nacc; j += TPB) sacc[j] = 0.0;
-    } else {
+  int stop = 0;
+  for (;;) {
+    while (done < nsteps && !stop) {
+      // nothing is hoisted out of the step loop: keeps the step's registers per step
+      __asm__ __volatile__("" ::: "memory");
+      SolveIn in;
+      if (done == 0) {
+        solve_load<MODE, false, GEN, P2>(d, phase0, false, in);
+        for (int j = tid; j < nacc; j += TPB) sacc[j] = 0.0;
+      } else {
 #pragma unroll
-      for (int k = 0; k < kSolvePer; ++k) {
-        in.b[k] = in.bm[k] = 0.0;
-        if (owner && k < per) {
-          in.b[k] = grid_value<MODE>(sacc, j0 + k);
-          if (P2 && d.order == 2) in.bm[k] = grid_value<MODE>(sacc, ng + j0 + k);
+        for (int k = 0; k < kSolvePer; ++k) {
+          in.b[k] = in.bm[k] = 0.0;
+          if (owner && k < per) {
+            in.b[k] = grid_value<MODE>(sacc, j0 + k);
+            if (P2 && d.order == 2) in.bm[k] = grid_value<MODE>(sacc, ng + j0 + k);
+          }
+        }
+        if constexpr (MODE == kFP32) __syncthreads();  // floats: nodes share a 64-bit word
+        if (owner)
+#pragma unroll
+          for (int k = 0; k < kSolvePer; ++k)
+            if (k < per) {
+              sacc[j0 + k] = 0.0;
+              if (P2 && d.order == 2) sacc[ng + j0 + k] = 0.0;
+            }
+      }
+      double unused[7];
+      solve_compute<TPB, GEN, P2>(d, in, false, bt, fE, fG, sred, fft, nullptr, unused,
+                                  nullptr, &huge);
+      // a non-finite load makes every E NaN through its mean
+      stop = (isfinite(fE[0]) ? 0 : 1) | nonfinite | huge;
+      double v[kSums] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+      if (tid < ng) {
+        const double Ee = fE[tid];
+        v[4] = Ee * Ee;
+        v[5] = Ee * c1;
+        v[6] = -(Ee * s1);
+        if (P2 && d.order == 2) {  // the midpoint load's part (see solve_compute): h g = -3 b~_m / 2
+          const double hg = d.h * fG[tid];
+          v[4] += 0.1875 * (4.0 / 9.0) * (hg * hg);
         }
       }
-      if constexpr (MODE == kFP32) __syncthreads();  // floats: nodes share a 64-bit word
-      if (owner)
 #pragma unroll
-        for (int k = 0; k < kSolvePer; ++k)
-          if (k < per) {
-            sacc[j0 + k] = 0.0;
-            if (P2 && d.order == 2) sacc[ng + j0 + k] = 0.0;
-          }
-    }
-    double unused[7];
-    solve_compute<TPB, GEN, P2>(d, in, false, bt, fE, fG, sred, fft, nullptr, unused);
-    // a non-finite load makes every E NaN through its mean
-    stop = !isfinite(fE[0]) || nonfinite_k;
-    double v[kSums] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (tid < ng) {
-      const double Ee = fE[tid];
-      v[4] = Ee * Ee;
-      v[5] = Ee * c1;
-      v[6] = -(Ee * s1);
-      if (P2 && d.order == 2) v[4] += wp2 * (fG[tid] * fG[tid]);
-    }
-#pragma unroll
-    for (int u = 0; u < PPT; ++u)
-      push_particle<MODE, T, true, GEN, P2, -1, kCell>(d, fE, fG, sacc, pend, q[u], p[u], a[u],
-                                                       b[u], w[u], v[0], v[1], v[2], v[3], nullptr,
-                                                       &cell[u]);
-    pend = 1;
-    wave_totals_to(v, red + wid, kWaves);
-    __syncthreads();  // also completes every LDS deposit
-    if (wid == kWaves - 1) {
-      tot = 0.0;
-      if (lane < kSums)
-        for (int x = 0; x < kWaves; ++x) tot += red[lane * kWaves + x];
-      if (lane == 4) tot = 0.5 * d.h * tot;
-      if (lane == 5 || lane == 6) tot = tot * inv_pow2(d.log2ng);
-      const double K = __shfl(tot, 0), mom = __shfl(tot, 1), chg = __shfl(tot, 2);
-      const double U = __shfl(tot, 3), W = __shfl(tot, 4), er = __shfl(tot, 5), ei = __shfl(tot, 6);
-      if (lane == 0) {
-        write_record(d, step0 + done, K, mom, chg, GEN ? U : 0.0, W, er, ei);
-        nonfinite_k = !isfinite(K) || (GEN && !isfinite(U));
+      for (int u = 0; u < PPT; ++u)
+        push_particle<MODE, T, true, GEN, P2, -1, kCell>(d, fE, fG, sacc, pend, q[u], p[u], a[u],
+                                                         b[u], w[u], v[0], v[1], v[2], v[3],
+                                                         nullptr, &cell[u]);
+      pend = 1;
+      wave_totals_to(v, red + wid, kWaves);
+      __syncthreads();  // also completes every LDS deposit
+      if (wid == kWaves - 1) {
+        tot = 0.0;
+        if (lane < kSums)
+          for (int x = 0; x < kWaves; ++x) tot += red[lane * kWaves + x];
+        if (lane == 4) tot = 0.5 * d.h * tot;
+        if (lane == 5 || lane == 6) tot = tot * inv_pow2(d.log2ng);
+        const double K = __shfl(tot, 0), mom = __shfl(tot, 1), chg = __shfl(tot, 2);
+        const double U = __shfl(tot, 3), W = __shfl(tot, 4), er = __shfl(tot, 5), ei = __shfl(tot, 6);
+        if (lane == 0) {
+          store_record_at(d, (int)((step0 + done) % d.hist_cap), step0 + done, K, mom, chg,
+                          GEN ? U : 0.0, W, er, ei);
+          nonfinite = (!isfinite(K) || (GEN && !isfinite(U)) ? 1 : 0) | (!isfinite(W) ? 2 : 0);
+        }
       }
+      ++done;
     }
-    ++done;
+    if (stop != 4 || done == nsteps) break;
+    __syncthreads();  // the last wavefront's verdict on the pass near overflow
+    if (nonfinite & 2) break;
+    if (tid == 0) huge = 0;
+    stop = 0;
   }
 
   const int rf = (phase0 + done) % kRing, rl = ring_prev(rf);  // next phase, last pass's
@@ -179,7 +197,7 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(
       sc->W[rl] = tot;
       sc->step = step0 + done;
       sc->pend[rf] = 1;
-      if (!isfinite(tot)) sc->nonfinite = 1;
+      if (!isfinite(tot) || (stop & 3)) sc->nonfinite = 1;
     }
     if (lane == 5) sc->e1r[rl] = tot;
     if (lane == 6) sc->e1i[rl] = tot;
