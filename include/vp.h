@@ -179,12 +179,15 @@ typedef struct vp_diag {
                        of the engine took; 0 from vp_diagnostics */
 } vp_diag;
 
-/* Launch shape of the particle kernels; chosen by vp_tune or set by the caller.  A handle on
- * which neither was called picks its shapes by each instance's size (and runs instances that fit
- * one workgroup many steps per launch); vp_get_tuning then returns {1024, 4, 4, 1, 33, 0, 0}. */
+/* Launch shape of the particle kernels; chosen by vp_tune or set by the caller.  With threads and
+ * ppt 0 the library picks the shapes by each instance's size (and runs instances that fit one
+ * workgroup many steps per launch): so does a handle on which neither vp_tune nor vp_set_tuning
+ * was called, for which vp_get_tuning returns {1024, 4, 4, 1, 33, 0, 0} all the same.  To change
+ * another field there, set threads and ppt to 0. */
 typedef struct vp_tuning {
-  int32_t threads;      /* threads per workgroup of the particle kernels: 256, 512 or 1024 */
-  int32_t ppt;          /* particles per thread per tile: 1, 2, 4, 8, 16, 32 or 64 */
+  int32_t threads;      /* threads per workgroup of the particle kernels: 256, 512 or 1024; 0 (with
+                         * ppt 0, not persistent): chosen by size */
+  int32_t ppt;          /* particles per thread per tile: 1, 2, 4, 8, 16, 32 or 64; 0 with threads 0 */
   int32_t acc_copies;   /* copies of each instance's global load accumulator, 1..8 */
   int32_t use_graph;    /* 1: vp_step replays captured HIP graphs (captured by vp_prepare_step,
                          * or once the slots and the tuning have stood for several graph
@@ -352,6 +355,13 @@ vp_status vp_history(vp_handle* h, int32_t slot, int64_t first_step, int32_t cou
 /* ---------------------------------------------------------------- tuning and misc */
 vp_status vp_set_tuning(vp_handle* h, const vp_tuning* t);
 vp_status vp_get_tuning(const vp_handle* h, vp_tuning* t);
+
+/* The launch shape in which vp_step(h, nsteps) takes the slot's particles now: threads per
+ * workgroup, particles per thread, and steps per launch (1: one launch a step; more: the
+ * persistent steps of a persistent tuning, or one workgroup an instance where the shapes are
+ * chosen by size).  Host arguments.  Errors: VP_ERR_ARG, VP_ERR_STATE. */
+vp_status vp_step_launch(const vp_handle* h, int32_t slot, int32_t nsteps, int32_t* threads_out,
+                         int32_t* ppt_out, int32_t* steps_out);
 
 /* Time each candidate launch shape on the handle's current slots (the particle arrays
  * are advanced and then restored from a device copy the caller provides: scratch of

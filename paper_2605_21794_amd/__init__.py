@@ -195,6 +195,7 @@ class Engine:
                 "vp_engine_create")
         self.h = h
         self.slots = {}
+        self._tuned = False   # set_tuning or tune was called
         _open_engines.add(self)
 
     # ---------------------------------------------------------------- slots
@@ -352,10 +353,26 @@ class Engine:
         return tu.as_dict()
 
     def set_tuning(self, **kw):
+        """Change the given fields of the tuning.  The launch shapes stay chosen by size unless
+        threads, ppt or persistent is given (threads=0, ppt=0 goes back to that); a shape field
+        left out is then 1024 threads, 4 per thread."""
         cur = self.get_tuning()
+        if "threads" in kw or "ppt" in kw or kw.get("persistent"):
+            if not cur["threads"]:
+                cur.update(threads=1024, ppt=4)
+        elif not self._tuned:
+            cur.update(threads=0, ppt=0)
         cur.update(kw)
         tu = L.vp_tuning(**cur)
         L.check(self.lib.vp_set_tuning(self.h, byref(tu)), "vp_set_tuning")
+        self._tuned = True
+
+    def step_launch(self, nsteps: int, slot: int = 0) -> dict:
+        """The launch shape step(nsteps) runs the slot in: threads, ppt, steps_per_launch."""
+        v = [c_int32() for _ in range(3)]
+        L.check(self.lib.vp_step_launch(self.h, int(slot), int(nsteps), *map(byref, v)),
+                "vp_step_launch")
+        return dict(zip(("threads", "ppt", "steps_per_launch"), (x.value for x in v)))
 
     def tune(self, steps_per_trial: int = 20):
         """Time every candidate launch shape on the current slots, keep the fastest."""
@@ -367,6 +384,7 @@ class Engine:
         us = c_double()
         L.check(self.lib.vp_tune(self.h, c_void_p(scratch.data_ptr()), int(steps_per_trial),
                                  byref(best), byref(us)), "vp_tune")
+        self._tuned = True
         return best.as_dict(), float(us.value)
 
     def occupancy(self):

@@ -75,6 +75,8 @@ SIGNATURES = {
     "vp_history": (c_int32, [H, c_int32, c_int64, c_int32, POINTER(vp_diag)]),
     "vp_set_tuning": (c_int32, [H, POINTER(vp_tuning)]),
     "vp_get_tuning": (c_int32, [H, POINTER(vp_tuning)]),
+    "vp_step_launch": (c_int32, [H, c_int32, c_int32, POINTER(c_int32), POINTER(c_int32),
+                                 POINTER(c_int32)]),
     "vp_tune_scratch_bytes": (c_int32, [H, POINTER(c_size_t)]),
     "vp_tune": (c_int32, [H, c_void_p, c_int32, POINTER(vp_tuning), POINTER(c_double)]),
     "vp_occupancy": (c_int32, [H, POINTER(c_int32), POINTER(c_int64)]),

@@ -157,8 +157,8 @@ struct vp_handle {
   long long* d_status = nullptr;  // 2 per slot: step, nonfinite (vp_slot_status)
   int max_ng = VP_MIN_NG;   // largest ng of the slots, doubled for P2 (sizes the launches' LDS)
   bool any_fft = false;     // some slot uses the FFT solver (fused launches need more LDS)
-  vp_tuning tun{1024, 4, 4, 1, 33, 0, 0};
-  bool tuned = false;       // the tuning was set (vp_set_tuning, vp_tune): it is taken as it is
+  vp_tuning tun{0, 0, 4, 1, 33, 0, 0};  // threads = ppt = 0: shapes by size (by_size)
+  bool tuned = false;       // vp_set_tuning or vp_tune set it (vp_get_tuning)
   bool nontemporal = true;  // fused steps stream the particle arrays past the caches
   int threads = 512, ppt = 4;  // of the launches over the current tiles (ppt: the largest tile's)
   hipGraph_t graph = nullptr;
@@ -197,6 +197,10 @@ bool runs_general(const InstDev& d) { return d.general || d.solver == VP_SOLVE_F
 
 constexpr int kDefaultThreads = 512;
 
+// The launch shapes are the library's choice, by each instance's size; else tun.threads and
+// tun.ppt are taken as they are.
+bool by_size(const vp_handle* h) { return h->tun.threads == 0; }
+
 // Particles per thread of a slot's tiles: the tuning's where one was set; by default, at 512
 // threads, 4 while every tile is resident at once (two workgroups to a CU for the float64 state,
 // three for the float32 ones), 8 above, and 16 for the largest float32 states.  us a step at
@@ -210,12 +214,12 @@ constexpr int kDefaultThreads = 512;
 // x 8; float32 state: 2^18 9.4, 11.0, 14.3; 2^19 11.1, 11.5, 14.6; 2^20 19.0, 15.5, 16.5; 2^21
 // 35.1, 28.9, 27.1), 4 up to 2^20 and 8 above.
 int ppt_of(const vp_handle* h, const vp_config& c) {
-  if (h->tuned) return h->tun.ppt;
+  if (!by_size(h)) return h->tun.ppt;
   if (c.moment_order == 3) return c.n <= 1LL << 19 ? 2 : c.n <= 1LL << 20 ? 4 : 8;
   if (c.precision == VP_FP64) return c.n <= 1LL << 20 ? 4 : 8;
   return c.n <= 3LL << 19 ? 4 : c.n < 7LL << 19 ? 8 : 16;
 }
-int threads_of(const vp_handle* h) { return h->tuned ? h->tun.threads : kDefaultThreads; }
+int threads_of(const vp_handle* h) { return by_size(h) ? kDefaultThreads : h->tun.threads; }
 
 // Wait for the stream; every upload has then read its part of the arena.
 vp_status sync_stream(vp_handle* h) {
@@ -539,20 +543,25 @@ vp_status advance_persistent(vp_handle* h, int k) {
   return VP_OK;
 }
 
-// Whether k steps run as one workgroup per instance: the tuning is the default (an explicit one
-// is taken as it is), every instance is small enough (resident_capacity), and there is more than
-// one step to share the launch.
+// Whether k steps run as one workgroup per instance: the shapes are chosen by size, every instance
+// is small enough (resident_capacity), and there is more than one step to share the launch.
 bool steps_resident(const vp_handle* h, int k) {
-  if (h->tuned || k < 2) return false;
+  if (!by_size(h) || k < 2) return false;
   const long long cap = vpk::resident_capacity(h->precision, any_general(h), any_p2(h));
   for (int s : h->h_occ)
     if (h->slots[s].cfg.n > cap || h->h_inst[s].k3) return false;
   return true;
 }
 
-vp_status advance_resident(vp_handle* h, int k) {
+// The largest occupied slot's particles.
+long long largest(const vp_handle* h) {
   long long nmax = 0;
   for (int s : h->h_occ) nmax = std::max<long long>(nmax, h->slots[s].cfg.n);
+  return nmax;
+}
+
+vp_status advance_resident(vp_handle* h, int k) {
+  const long long nmax = largest(h);
   while (k > 0) {
     const int c = std::min(k, kMaxPersistSteps);
     VP_HIP(vpk::launch_resident(h->precision, nmax, h->d_inst, h->d_occ, (int)h->h_occ.size(),
@@ -1111,9 +1120,10 @@ vp_status vp_history(vp_handle* h, int32_t slot, int64_t first_step, int32_t cou
 
 vp_status vp_set_tuning(vp_handle* h, const vp_tuning* t) {
   if (!h || !t) return fail(VP_ERR_ARG, "NULL argument");
-  if (!(t->threads == 256 || t->threads == 512 || t->threads == 1024))
-    return fail(VP_ERR_ARG, "threads must be 256, 512 or 1024");
-  if (!(t->ppt == 1 || t->ppt == 2 || t->ppt == 4 || t->ppt == 8 || t->ppt == 16 || t->ppt == 32 ||
+  const bool chosen = t->threads == 0 && t->ppt == 0;  // by size
+  if (!chosen && !(t->threads == 256 || t->threads == 512 || t->threads == 1024))
+    return fail(VP_ERR_ARG, "threads must be 256, 512 or 1024 (or threads and ppt 0)");
+  if (!chosen && !(t->ppt == 1 || t->ppt == 2 || t->ppt == 4 || t->ppt == 8 || t->ppt == 16 || t->ppt == 32 ||
         t->ppt == 64))
     return fail(VP_ERR_ARG, "ppt must be 1, 2, 4, 8, 16, 32 or 64");
   if (t->acc_copies < 1 || t->acc_copies > VP_MAX_ACC_COPIES) return fail(VP_ERR_ARG, "acc_copies out of range");
@@ -1154,6 +1164,25 @@ vp_status vp_set_tuning(vp_handle* h, const vp_tuning* t) {
 vp_status vp_get_tuning(const vp_handle* h, vp_tuning* t) {
   if (!h || !t) return fail(VP_ERR_ARG, "NULL argument");
   *t = h->tun;
+  if (!h->tuned) {  // as documented
+    t->threads = 1024;
+    t->ppt = 4;
+  }
+  return VP_OK;
+}
+
+vp_status vp_step_launch(const vp_handle* h, int32_t slot, int32_t nsteps, int32_t* threads_out,
+                         int32_t* ppt_out, int32_t* steps_out) {
+  VP_TRY(check_slot(h, slot));
+  if (nsteps < 1) return fail(VP_ERR_ARG, "nsteps < 1");
+  if (!threads_out || !ppt_out || !steps_out) return fail(VP_ERR_ARG, "NULL argument");
+  int k = nsteps;  // of one call of advance (vp_step)
+  for (int s : h->h_occ)
+    if (h->slots[s].cfg.sort_every > 0) k = std::min(k, (int)h->slots[s].cfg.sort_every);
+  const bool resident = !h->tun.persistent && steps_resident(h, k);
+  *threads_out = resident ? vpk::kResidentThreads : h->threads;
+  *ppt_out = resident ? vpk::resident_ppt(largest(h)) : ppt_of(h, h->slots[slot].cfg);
+  *steps_out = resident || h->tun.persistent ? std::min(k, kMaxPersistSteps) : 1;
   return VP_OK;
 }
 
@@ -1475,13 +1504,7 @@ vp_status vp_tune(vp_handle* h, void* dev_scratch, int32_t steps_per_trial, vp_t
   h->acc_stale = saved_as;
   vp_status s2 = tune_copy(h, scratch, false);
   vp_status s3 = vp_set_tuning(h, st == VP_OK ? &best : &orig);
-  if (st != VP_OK && !orig_tuned) {  // back to the default shapes
-    h->tuned = false;
-    const vp_status keep = st;
-    VP_TRY(arena_reserve(h, 0));
-    VP_TRY(rebuild_tables(h, vpk::UploadArgs{}, -1, true));
-    st = keep;
-  }
+  if (st != VP_OK) h->tuned = orig_tuned;
   if (st != VP_OK) return st;
   if (s2 != VP_OK) return s2;
   if (s3 != VP_OK) return s3;

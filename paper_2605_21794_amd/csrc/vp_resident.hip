@@ -4,8 +4,6 @@
 
 namespace vpk {
 
-constexpr int kResidentThreads = 1024;
-
 // Value of node j of the LDS deposit grid, as the flush would add it to a cleared accumulator.
 template <int MODE>
 __device__ __forceinline__ double grid_value(const double* sacc, int j) {
@@ -227,6 +225,11 @@ long long resident_capacity(int mode, bool general, bool p2) {
   }
 }
 
+int resident_ppt(long long nmax) {
+  return nmax <= kResidentThreads ? 1 : nmax <= 2 * kResidentThreads ? 2
+         : nmax <= 4 * kResidentThreads ? 4 : 8;
+}
+
 template <int MODE, int PPT>
 static void launch_resident_ppt(const InstDev* d_inst, const int* d_slots, int nslots, size_t lds,
                                 bool general, bool p2, int phase, int nsteps, hipStream_t s) {
@@ -251,8 +254,7 @@ hipError_t launch_resident(int mode, long long nmax, const InstDev* d_inst, cons
   if (nmax > resident_capacity(mode, general, p2) || (p2 && mode == kFP32))
     return hipErrorInvalidValue;
   const size_t lds = fused_lds_bytes(lds_fft, max_ng);
-  const int ppt = nmax <= kResidentThreads ? 1 : nmax <= 2 * kResidentThreads ? 2
-                  : nmax <= 4 * kResidentThreads ? 4 : 8;
+  const int ppt = resident_ppt(nmax);
 #define VP_RES_CASE(M, PP)                                                                   \
   if (mode == M && ppt == PP) {                                                              \
     launch_resident_ppt<M, PP>(d_inst, d_slots, nslots, lds, general, p2, phase, nsteps, s); \
