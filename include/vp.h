@@ -365,7 +365,8 @@ vp_status vp_step_launch(const vp_handle* h, int32_t slot, int32_t nsteps, int32
 
 /* Time each candidate launch shape on the handle's current slots (the particle arrays
  * are advanced and then restored from a device copy the caller provides: scratch of
- * vp_tune_scratch_bytes), keep the fastest and report it. */
+ * vp_tune_scratch_bytes), keep the fastest and report it.  The shapes the library chooses by
+ * size are one of the candidates (threads and ppt 0 in the result). */
 vp_status vp_tune_scratch_bytes(const vp_handle* h, size_t* bytes_out);
 vp_status vp_tune(vp_handle* h, void* dev_scratch, int32_t steps_per_trial, vp_tuning* best_out,
                   double* best_us_per_step_out);

@@ -375,7 +375,8 @@ class Engine:
         return dict(zip(("threads", "ppt", "steps_per_launch"), (x.value for x in v)))
 
     def tune(self, steps_per_trial: int = 20):
-        """Time every candidate launch shape on the current slots, keep the fastest."""
+        """Time every candidate launch shape on the current slots, the shapes chosen by size
+        (threads = ppt = 0) among them, and keep the fastest."""
         t = self._torch
         b = c_size_t()
         L.check(self.lib.vp_tune_scratch_bytes(self.h, byref(b)), "vp_tune_scratch_bytes")

@@ -47,6 +47,7 @@ vp_status fail(vp_status s, const char* fmt, ...) {
 
 constexpr int kGroups = 10;       // kinds of tiles, one fused launch each (see rebuild_tables)
 constexpr int kGroupMoments = 8;  // the two kinds of instances with second moments
+constexpr int kDefaultCopies = 4;  // accumulator copies of a handle that was never tuned
 
 bool is_pow2(int x) { return x > 0 && (x & (x - 1)) == 0; }
 int ilog2(int x) { int m = 0; while ((1 << m) < x) ++m; return m; }
@@ -157,7 +158,7 @@ struct vp_handle {
   long long* d_status = nullptr;  // 2 per slot: step, nonfinite (vp_slot_status)
   int max_ng = VP_MIN_NG;   // largest ng of the slots, doubled for P2 (sizes the launches' LDS)
   bool any_fft = false;     // some slot uses the FFT solver (fused launches need more LDS)
-  vp_tuning tun{0, 0, 4, 1, 33, 0, 0};  // threads = ppt = 0: shapes by size (by_size)
+  vp_tuning tun{0, 0, kDefaultCopies, 1, 33, 0, 0};  // threads = ppt = 0: shapes by size (by_size)
   bool tuned = false;       // vp_set_tuning or vp_tune set it (vp_get_tuning)
   bool nontemporal = true;  // fused steps stream the particle arrays past the caches
   int threads = 512, ppt = 4;  // of the launches over the current tiles (ppt: the largest tile's)
@@ -1425,9 +1426,10 @@ vp_status vp_tune(vp_handle* h, void* dev_scratch, int32_t steps_per_trial, vp_t
   vp_tuning best = orig;
   double best_us = 1e300;
   struct Cand { int threads, ppt, acc, persistent; };
-  std::vector<Cand> cands;
-  long long nmax = 0;
-  for (int s : h->h_occ) nmax = std::max<long long>(nmax, h->slots[s].cfg.n);
+  // the shapes by size (tiles of several depths, or one workgroup an instance) are no others'
+  // equal, so they are tried themselves
+  std::vector<Cand> cands{{0, 0, kDefaultCopies, 0}};
+  const long long nmax = largest(h);
   for (int th : {512, 1024})
     for (int pp : {1, 2, 4, 8, 16, 32})
       if (pp <= 8 || (long long)th * pp * 512 <= nmax)  // big tiles only for big instances
