@@ -110,8 +110,17 @@ def launch_key(tun: dict) -> list:
 
 
 def kernel_of(tun: dict) -> str:
-    """The step kernel a tuning runs: the persistent one or one fused launch per step."""
-    return "k_persist" if int(tun.get("persistent", 0)) else "k_fused"
+    """The step kernel a tuning runs: the persistent one, the resident one (shapes chosen by
+    size, several steps per launch: see launch_of) or one fused launch per step."""
+    if int(tun.get("persistent", 0)):
+        return "k_persist"
+    return "k_resident" if int(tun.get("steps_per_launch", 1)) > 1 else "k_fused"
+
+
+def launch_of(sim, steps: int) -> dict:
+    """The engine's tuning with the shape that step(steps) runs its first slot in (the tuning's
+    own threads and ppt may be 0: shapes chosen by size)."""
+    return dict(sim.get_tuning(), **sim.step_launch(steps))
 
 
 def pmc_path(workload: str, launch: list, kernel: str = "k_fused") -> str:
@@ -279,7 +288,7 @@ def run_sweep(args):
     if not args.no_tune:
         best, us = eng.tune(steps_per_trial=99)
         log(f"batched: tuned launch shape {best} ({us:.2f} us/step)")
-    tun = eng.get_tuning()
+    tun, ran = eng.get_tuning(), launch_of(eng, steps)
     eng.step(args.warmup)
     torch.cuda.synchronize()
     ev0, ev1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -305,8 +314,9 @@ def run_sweep(args):
     for w, st in zip(ws, sts):
         sim = vp.Simulation(st, w.L, w.ng, w.dt, prec, stream=stream,
                             hist_cap=max(64, steps + args.warmup + 8))
-        sim.set_tuning(threads=tun["threads"], ppt=tun["ppt"], acc_copies=tun["acc_copies"],
-                       graph_steps=tun["graph_steps"])
+        if args.launch or not args.no_tune:  # else the shapes by size, as the engine above
+            sim.set_tuning(threads=tun["threads"], ppt=tun["ppt"], acc_copies=tun["acc_copies"],
+                           graph_steps=tun["graph_steps"])
         sims.append(sim)
     for sim in sims:
         sim.step(args.warmup)
@@ -340,14 +350,14 @@ def run_sweep(args):
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": arith_dtype(prec), "data": "synthetic",
         "config": {"workload": "landau_sweep", "instances": len(ws), "n_total": ntot,
-                   "precision": prec, "launch": tun,
+                   "precision": prec, "launch": ran,
                    "plain_value": upd_p / el_p,
                    "batched_over_plain": (upd_b / el_b) / max(upd_p / el_p, 1e-300),
                    "max_rel_W_difference_batched_vs_plain": rel,
                    "nonfinite_instances": nonfinite},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS, "traffic": None,
-                     "kernel": "k_persist" if tun.get("persistent") else "k_fused",
+                     "kernel": kernel_of(ran),
                      "bytes_per_launch": bytes_per_launch,
                      "kernel_us": kern_avg_s * 1e6},
     }
@@ -432,7 +442,7 @@ def run_served(args):
         srv.backend.engine.set_tuning(**parse_launch(args.launch))
     if args.use_graph is not None:
         srv.backend.engine.set_tuning(use_graph=args.use_graph)
-    log(f"served: engine tuning {srv.backend.engine.get_tuning()}")
+    log("served: launch shapes " + (args.launch or "chosen by size"))
     full_budget = srv.budget
     w0 = base[0][1]
     srv.run([Job(state=states[0], L=w0.L, ng=w0.ng, dt=w0.dt, horizon=66, name="warm")])
@@ -978,17 +988,19 @@ def main():
     if not args.no_tune:
         best, tuning_us = sim.tune(steps_per_trial=99)
         log(f"tuned launch shape {best} ({tuning_us:.2f} us/step)")
-    tun = sim.get_tuning()
-    persistent = bool(tun.get("persistent", 0))
-    if not persistent and tun["use_graph"]:
+    tun = launch_of(sim, args.steps)
+    kernel = kernel_of(tun)
+    persistent, resident = kernel == "k_persist", kernel == "k_resident"
+    if kernel == "k_fused" and tun["use_graph"]:
         # a graph no longer than the timed steps (a multiple of the ring period of 3), and
         # every graph the timed steps replay captured now, outside the timed region
         gs = max(3, min(int(tun["graph_steps"]), 3 * (args.steps // 3)))
         if gs != tun["graph_steps"]:
             sim.set_tuning(graph_steps=gs)
         sim.prepare_step(args.steps)
-        tun = sim.get_tuning()
+        tun = launch_of(sim, args.steps)
     timed_launches = ("persistent launches" if persistent else
+                      "resident launches" if resident else
                       "graph replays" if tun["use_graph"] else "direct launches")
 
     sim.step(args.warmup)
@@ -1028,12 +1040,12 @@ def main():
     finite = bool(np.isfinite(diag["H"]))
     n = w.n
     value = n * args.steps / elapsed
-    # the persistent kernel carries monopole-only particles through the decorated path
+    # the persistent and resident kernels carry monopole-only particles through the decorated path
     table = (MOMENT_BYTES if args.moments else
-             MONOPOLE_BYTES if args.monopole and not persistent else FUSED_BYTES)
+             MONOPOLE_BYTES if args.monopole and kernel == "k_fused" else FUSED_BYTES)
     bytes_per_step = table[prec] * n
-    # a launch is one step, or up to 1024 steps of the persistent kernel
-    steps_per_launch = min(args.steps, 1024) if persistent else 1
+    # a launch is one step, or up to 1024 steps of the persistent or resident kernel
+    steps_per_launch = int(tun["steps_per_launch"])
     launches = -(-args.steps // steps_per_launch)
     bytes_per_launch = bytes_per_step * steps_per_launch
     launch_s = ev0.elapsed_time(ev1) * 1e-3 / launches
@@ -1043,7 +1055,7 @@ def main():
     suffix = (("_monopole" if args.monopole else "") + ("_p2" if args.element_order == 2 else "")
               + ("_k3" if args.moments else ""))
     traffic_key = args.workload + suffix
-    traffic = load_traffic(traffic_key, n, prec, launch_key(tun), kernel_of(tun),
+    traffic = load_traffic(traffic_key, n, prec, launch_key(tun), kernel,
                            steps_per_launch)
     out = {
         "metric": METRIC,
@@ -1068,17 +1080,17 @@ def main():
         "roofline": {
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
-            "kernel": "k_persist" if persistent else "k_fused",
+            "kernel": kernel,
             "bytes_per_launch": bytes_per_launch, "steps_per_launch": steps_per_launch,
             "kernel_us": launch_s * 1e6, "us_per_step": kern_avg_s * 1e6,
             "direct_launch_us": direct_us,
         },
     }
-    if persistent:
+    if kernel != "k_fused":
         out["roofline"]["note"] = (
-            "persistent kernel: each thread keeps its particles in registers for all the steps "
-            "of a launch; achieved counts the algorithmic bytes per update, traffic the bytes "
-            "the counters measured per launch")
+            f"{'resident' if resident else 'persistent'} kernel: each thread keeps its particles "
+            "in registers for all the steps of a launch; achieved counts the algorithmic bytes per "
+            "update, traffic the bytes the counters measured per launch")
     sim.close()
     if not args.no_served:
         out["served"] = served_block(prec)
