@@ -10,6 +10,8 @@
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -128,7 +130,9 @@ struct MeshTables {
 static_assert(sizeof(InstDev) % 8 == 0 && sizeof(Tile) % 8 == 0, "uploaded in 64-bit words");
 constexpr size_t kScalHead = offsetof(vpk::InstScal, arrive);
 constexpr size_t kCachedLow = 56u << 20, kCachedHigh = 256u << 20;  // see rebuild_tables
-constexpr size_t kArenaBytes = 256u << 10;  // pinned staging of the table uploads
+// Pinned staging of the table uploads and read-backs: what is taken first, and the most.  An upload
+// above that, or where pinned memory is not to be had, goes by plain copies.
+constexpr size_t kArenaBytes = 256u << 10, kArenaMax = 4u << 20;
 
 }  // namespace
 
@@ -147,6 +151,9 @@ struct vp_handle {
   std::vector<int> up_occ;
   char* arena = nullptr;      // pinned host memory that uploads in flight read from
   size_t arena_bytes = 0, arena_off = 0;
+  bool no_pinned = false;     // pinned memory was refused: not asked for again
+  std::unique_ptr<char[]> stage;  // of an upload by plain copies, in the arena's place
+  size_t stage_off = 0;
   MeshTables mesh[11];        // by log2 of ng, made when first needed
   long long steps_since_tables = 0;  // steps run since the tables last changed
   int ntiles = 0;
@@ -229,11 +236,12 @@ vp_status sync_stream(vp_handle* h) {
   return VP_OK;
 }
 
-// Room in the arena for the parts of one upload: `extra` bytes and the tables of the slots in
-// use.  Waits for the stream when what earlier uploads may still read fills it.
-vp_status arena_reserve(vp_handle* h, size_t extra) {
+// Room for the parts of one upload: `extra` bytes and (`tables`) the tables of the slots in use.
+// In the arena (waits for the stream when what earlier uploads may still read fills it), or else in
+// a block of the upload's own (h->stage).
+vp_status arena_reserve(vp_handle* h, size_t extra, bool tables = true) {
   size_t tiles = 0, slots = 0;
-  for (int s = 0; s < h->max_slots; ++s)
+  for (int s = 0; tables && s < h->max_slots; ++s)
     if (h->slots[s].used) {
       const long long tile_n = (long long)threads_of(h) * ppt_of(h, h->slots[s].cfg);
       tiles += (size_t)((h->slots[s].cfg.n + tile_n - 1) / tile_n);
@@ -241,23 +249,51 @@ vp_status arena_reserve(vp_handle* h, size_t extra) {
     }
   const size_t bytes = extra + tiles * sizeof(Tile) + slots * (sizeof(InstDev) + sizeof(int)) +
                        sizeof(InstDev) + 5 * 256;
-  if (h->arena_off + bytes <= h->arena_bytes) return VP_OK;
-  if (h->arena) VP_TRY(sync_stream(h));
-  if (bytes <= h->arena_bytes) return VP_OK;
-  if (h->arena) VP_HIP(hipHostFree(h->arena));
-  h->arena = nullptr;
-  h->arena_bytes = 0;
-  const size_t size = std::max(kArenaBytes, 2 * bytes);
-  VP_HIP(hipHostMalloc(reinterpret_cast<void**>(&h->arena), size, hipHostMallocDefault));
-  h->arena_bytes = size;
+  if (bytes <= kArenaMax && !h->no_pinned) {
+    h->stage.reset();
+    if (h->arena_off + bytes <= h->arena_bytes) return VP_OK;
+    if (h->arena) VP_TRY(sync_stream(h));
+    if (bytes <= h->arena_bytes) return VP_OK;
+    if (h->arena) VP_HIP(hipHostFree(h->arena));
+    h->arena = nullptr;
+    h->arena_bytes = 0;
+    const size_t size = std::min(std::max(kArenaBytes, 2 * bytes), kArenaMax);
+    if (hipHostMalloc(reinterpret_cast<void**>(&h->arena), size, hipHostMallocDefault) == hipSuccess) {
+      h->arena_bytes = size;
+      return VP_OK;
+    }
+    (void)hipGetLastError();  // not the next call's error
+    h->arena = nullptr;
+    h->no_pinned = true;
+  }
+  h->stage.reset(new (std::nothrow) char[bytes]);
+  h->stage_off = 0;
+  if (!h->stage) return fail(VP_ERR_HIP, "no host memory for %zu bytes of tables", bytes);
   return VP_OK;
 }
 
 // `bytes` of the reserved room; they stay as written until the stream has been waited for.
 char* arena_take(vp_handle* h, size_t bytes) {
-  char* p = h->arena + h->arena_off;
-  h->arena_off += (bytes + 255) & ~size_t(255);
+  size_t& off = h->stage ? h->stage_off : h->arena_off;
+  char* p = (h->stage ? h->stage.get() : h->arena) + off;
+  off += (bytes + 255) & ~size_t(255);
   return p;
+}
+
+// The upload whose parts were taken from the reserved room.
+vp_status upload(vp_handle* h, const vpk::UploadArgs& u) {
+  if (!h->stage) {
+    VP_HIP(vpk::launch_upload(u, h->stream));
+    return VP_OK;
+  }
+  for (int k = 0; k < u.nseg; ++k)
+    VP_HIP(hipMemcpyAsync(u.seg[k].dst, u.seg[k].src, u.seg[k].n8 * 8, hipMemcpyHostToDevice,
+                          h->stream));
+  for (int k = 0; k < u.nzero; ++k)
+    VP_HIP(vpk::launch_fill_zero(u.zero[k].dst, u.zero[k].n8 * 8, h->stream));
+  VP_TRY(sync_stream(h));
+  h->stage.reset();
+  return VP_OK;
 }
 
 // Add to u the upload of new_[0..n) over device array d, which holds old: the elements from
@@ -289,17 +325,23 @@ struct ReadPart {
 
 // The parts, n of them (at most six), after everything enqueued before; waits for the stream.
 // One launch writes them all into pinned memory (a copy of its own for each takes about 10 us
-// of host time); large ones, whose bytes count, are left to the copy engines.
+// of host time); large ones, whose bytes count, are left to the copy engines, and so are all
+// where the arena is not to be had.
 vp_status read_back(vp_handle* h, const ReadPart* parts, int n) {
   size_t total = 0;
   for (int k = 0; k < n; ++k) total += (parts[k].bytes + 255) & ~size_t(255);
-  if (total > kArenaBytes) {
+  bool pinned = total <= kArenaBytes && !h->no_pinned;
+  if (pinned) {
+    VP_TRY(arena_reserve(h, total, false));
+    pinned = !h->stage;
+    h->stage.reset();
+  }
+  if (!pinned) {
     for (int k = 0; k < n; ++k)
       VP_HIP(hipMemcpyAsync(parts[k].host, parts[k].dev, parts[k].bytes, hipMemcpyDeviceToHost,
                             h->stream));
     return sync_stream(h);
   }
-  VP_TRY(arena_reserve(h, total));
   char* at[6] = {};
   vpk::UploadArgs u{};
   for (int k = 0; k < n; ++k) {
@@ -406,7 +448,7 @@ vp_status rebuild_tables(vp_handle* h, vpk::UploadArgs u, int only, bool fold) {
   }
   add_upload(h, u, h->d_tiles, h->up_tiles, h->h_tiles);
   add_upload(h, u, h->d_occ, h->up_occ, h->h_occ);
-  VP_HIP(vpk::launch_upload(u, h->stream));
+  VP_TRY(upload(h, u));
   if (!fold) return VP_OK;
   // the live ring entry of every slot into copy 0
   for (int s : h->h_occ) h->slots[s].solved = false;
