@@ -149,6 +149,7 @@ struct vp_handle {
   size_t tiles_cap = 0;
   std::vector<Tile> up_tiles;  // what d_tiles and d_occ hold (once the stream gets there)
   std::vector<int> up_occ;
+  bool tables_lost = false;    // an upload failed: the device's tables are sent whole before use
   char* arena = nullptr;      // pinned host memory that uploads in flight read from
   size_t arena_bytes = 0, arena_off = 0;
   bool no_pinned = false;     // pinned memory was refused: not asked for again
@@ -300,7 +301,7 @@ vp_status upload(vp_handle* h, const vpk::UploadArgs& u) {
 // the first that differs on (an admission or a retirement leaves the tiles before it alone).
 // Elements are whole 64-bit words, or 32-bit ones in an array padded to 64 bits.
 template <typename E>
-void add_upload(vp_handle* h, vpk::UploadArgs& u, E* d, std::vector<E>& old,
+void add_upload(vp_handle* h, vpk::UploadArgs& u, E* d, const std::vector<E>& old,
                 const std::vector<E>& new_) {
   size_t i = 0;
   const size_t n = new_.size();
@@ -313,7 +314,6 @@ void add_upload(vp_handle* h, vpk::UploadArgs& u, E* d, std::vector<E>& old,
     std::memcpy(p, &new_[i], (n - i) * sizeof(E));
     u.seg[u.nseg++] = {d + i, p, bytes / 8};
   }
-  old = new_;
 }
 
 // Device memory read back to the host (whole 64-bit words).
@@ -359,8 +359,16 @@ vp_status read_back(vp_handle* h, const ReadPart* parts, int n) {
 // every slot in use for -1).  The stream orders the upload behind the launches that read the
 // old tables; it is waited for only where graphs in flight have to be dropped.  fold: the tiles
 // or the number of accumulator copies of slots with a history may have changed (an admission
-// and a retirement leave the other slots' as they are).
+// and a retirement leave the other slots' as they are).  After one that failed, everything is
+// sent and folded.
 vp_status rebuild_tables(vp_handle* h, vpk::UploadArgs u, int only, bool fold) {
+  if (h->tables_lost) {
+    only = -1;
+    fold = true;
+    h->up_tiles.clear();
+    h->up_occ.clear();
+  }
+  h->tables_lost = true;  // until it is done
   bool graphs = h->gexec != nullptr;
   for (int p = 0; p < vpk::kRing; ++p) graphs = graphs || h->step_exec[p];
   if (graphs) VP_HIP(hipStreamSynchronize(h->stream));
@@ -449,12 +457,23 @@ vp_status rebuild_tables(vp_handle* h, vpk::UploadArgs u, int only, bool fold) {
   add_upload(h, u, h->d_tiles, h->up_tiles, h->h_tiles);
   add_upload(h, u, h->d_occ, h->up_occ, h->h_occ);
   VP_TRY(upload(h, u));
-  if (!fold) return VP_OK;
-  // the live ring entry of every slot into copy 0
-  for (int s : h->h_occ) h->slots[s].solved = false;
-  VP_HIP(vpk::launch_ring(h->precision, h->d_inst, h->d_occ, (int)h->h_occ.size(), vpk::kRingFold,
-                          h->phase, h->stream));
-  return sync_stream(h);
+  h->up_tiles = h->h_tiles;
+  h->up_occ = h->h_occ;
+  if (fold) {  // the live ring entry of every slot into copy 0
+    for (int s : h->h_occ) h->slots[s].solved = false;
+    VP_HIP(vpk::launch_ring(h->precision, h->d_inst, h->d_occ, (int)h->h_occ.size(), vpk::kRingFold,
+                            h->phase, h->stream));
+    VP_TRY(sync_stream(h));
+  }
+  h->tables_lost = false;
+  return VP_OK;
+}
+
+// The device's tables are the host's (again).
+vp_status ensure_tables(vp_handle* h) {
+  if (!h->tables_lost) return VP_OK;
+  VP_TRY(arena_reserve(h, 0));
+  return rebuild_tables(h, vpk::UploadArgs{}, -1, true);
 }
 
 vp_status check_slot(const vp_handle* h, int slot) {
@@ -950,6 +969,7 @@ vp_status vp_create_batch(int32_t n_inst, const vp_config* cfgs, const vp_partic
 
 vp_status vp_retire(vp_handle* h, int32_t slot) {
   VP_TRY(check_slot(h, slot));
+  VP_TRY(ensure_tables(h));
   Slot& sl = h->slots[slot];
   if (sl.pending) {
     VP_TRY(materialise_slot(h, slot));
@@ -978,12 +998,14 @@ vp_status vp_destroy(vp_handle* h) {
 vp_status vp_deposit(vp_handle* h) {
   if (!h) return fail(VP_ERR_ARG, "handle is NULL");
   if (h->h_occ.empty()) return VP_OK;
+  VP_TRY(ensure_tables(h));
   return deposit_all(h);
 }
 
 vp_status vp_poisson(vp_handle* h) {
   if (!h) return fail(VP_ERR_ARG, "handle is NULL");
   if (h->h_occ.empty()) return VP_OK;
+  VP_TRY(ensure_tables(h));
   return materialise_all(h);
 }
 
@@ -991,6 +1013,7 @@ vp_status vp_gather_push(vp_handle* h, double kick, double drift) {
   if (!h) return fail(VP_ERR_ARG, "handle is NULL");
   if (!std::isfinite(kick) || !std::isfinite(drift)) return fail(VP_ERR_ARG, "kick and drift must be finite");
   if (h->h_occ.empty()) return VP_OK;
+  VP_TRY(ensure_tables(h));
   if (h->field_stale) VP_TRY(materialise_all(h));
   VP_HIP(vpk::launch_gather_push(h->precision, h->threads, h->d_inst, h->d_tiles, 0, h->ntiles, h->ppt,
                                  h->max_ng, kick, drift, h->stream));
@@ -1002,6 +1025,7 @@ vp_status vp_step(vp_handle* h, int32_t nsteps) {
   if (!h) return fail(VP_ERR_ARG, "handle is NULL");
   if (nsteps < 0) return fail(VP_ERR_ARG, "nsteps < 0");
   if (h->h_occ.empty() || nsteps == 0) return VP_OK;
+  VP_TRY(ensure_tables(h));
   if (h->acc_stale) VP_TRY(deposit_all(h));
   int done = 0;
   while (done < nsteps) {
@@ -1037,6 +1061,7 @@ vp_status vp_prepare_step(vp_handle* h, int32_t nsteps) {
   if (!h) return fail(VP_ERR_ARG, "handle is NULL");
   if (nsteps < 0) return fail(VP_ERR_ARG, "nsteps < 0");
   if (h->h_occ.empty() || nsteps == 0 || h->tun.persistent) return VP_OK;
+  VP_TRY(ensure_tables(h));
   if (steps_resident(h, nsteps)) return VP_OK;
   if (!h->tun.use_graph || h->stream == nullptr) return VP_OK;
   if (nsteps >= graph_len_of(h)) VP_TRY(ensure_graph(h));
@@ -1047,6 +1072,7 @@ vp_status vp_prepare_step(vp_handle* h, int32_t nsteps) {
 vp_status vp_sync_state(vp_handle* h) {
   if (!h) return fail(VP_ERR_ARG, "handle is NULL");
   if (h->h_occ.empty()) return VP_OK;
+  VP_TRY(ensure_tables(h));
   VP_TRY(materialise_all(h));
   VP_HIP(vpk::launch_settle(h->precision, h->threads, h->d_inst, h->d_tiles, 0, h->ntiles, h->ppt,
                             h->max_ng, h->phase, h->stream));
@@ -1058,6 +1084,7 @@ vp_status vp_sync_state(vp_handle* h) {
 
 vp_status vp_sort(vp_handle* h, int32_t slot, int32_t* dev_perm) {
   if (!h) return fail(VP_ERR_ARG, "handle is NULL");
+  VP_TRY(ensure_tables(h));
   if (slot < 0) {
     if (dev_perm) return fail(VP_ERR_ARG, "dev_perm must be NULL when sorting every slot");
     for (int s : h->h_occ)
@@ -1079,6 +1106,7 @@ vp_status vp_sort(vp_handle* h, int32_t slot, int32_t* dev_perm) {
 vp_status vp_cell_index(vp_handle* h, int32_t slot, int32_t* dev_cells) {
   VP_TRY(check_slot(h, slot));
   if (!dev_cells) return fail(VP_ERR_ARG, "dev_cells is NULL");
+  VP_TRY(ensure_tables(h));
   VP_HIP(vpk::launch_cell_index(h->d_inst, slot, h->precision, dev_cells, h->slots[slot].cfg.n,
                                 h->stream));
   return VP_OK;
@@ -1087,6 +1115,7 @@ vp_status vp_cell_index(vp_handle* h, int32_t slot, int32_t* dev_cells) {
 vp_status vp_diagnostics(vp_handle* h, int32_t slot, vp_diag* host_out, double* host_grid) {
   VP_TRY(check_slot(h, slot));
   if (!host_out) return fail(VP_ERR_ARG, "host_out is NULL");
+  VP_TRY(ensure_tables(h));
   const Slot& sl = h->slots[slot];
   const InstDev& d = h->h_inst[slot];
   VP_TRY(materialise_slot(h, slot));
@@ -1128,6 +1157,7 @@ vp_status vp_history(vp_handle* h, int32_t slot, int64_t first_step, int32_t cou
                      vp_diag* host_out) {
   VP_TRY(check_slot(h, slot));
   if (count < 0 || (count > 0 && !host_out)) return fail(VP_ERR_ARG, "bad count or output");
+  VP_TRY(ensure_tables(h));
   const Slot& sl = h->slots[slot];
   const InstDev& d = h->h_inst[slot];
   const long long cap = sl.cfg.hist_cap;
@@ -1246,6 +1276,7 @@ vp_status vp_slot_status(vp_handle* h, int32_t n, int64_t* host_steps, int32_t* 
   }
   const int nocc = (int)h->h_occ.size();
   if (nocc == 0) return VP_OK;
+  VP_TRY(ensure_tables(h));
   std::vector<long long> buf(2 * (size_t)nocc);
   VP_HIP(vpk::launch_slot_status(h->d_inst, h->d_occ, nocc, h->d_status, h->stream));
   const ReadPart part{buf.data(), h->d_status, buf.size() * sizeof(long long)};
@@ -1455,6 +1486,7 @@ vp_status vp_tune(vp_handle* h, void* dev_scratch, int32_t steps_per_trial, vp_t
   if (!h || !dev_scratch) return fail(VP_ERR_ARG, "NULL argument");
   if (steps_per_trial < 1) return fail(VP_ERR_ARG, "steps_per_trial < 1");
   if (h->h_occ.empty()) return fail(VP_ERR_STATE, "no occupied slot to tune on");
+  VP_TRY(ensure_tables(h));
   char* scratch = static_cast<char*>(dev_scratch);
   std::vector<Slot> saved = h->slots;
   const vp_tuning orig = h->tun;

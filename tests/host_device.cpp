@@ -260,9 +260,41 @@ static void large_tables() {
   CHECK(pinned == 0);
 }
 
+// After an upload that failed, the next one brings every table.
+static void failed_upload() {
+  Instance a(5000), b(20000), c(9000);
+  vp_handle* h = nullptr;
+  CHECK(vp_engine_create(VP_FP64, 8, nullptr, &h) == VP_OK);
+  CHECK(vp_admit(h, 1, &a.cfg, a.parts, a.ws) == VP_OK);
+  check_step(h, {&a});
+  fail_at["launch_upload"] = 1;
+  CHECK(vp_admit(h, 2, &b.cfg, b.parts, b.ws) == VP_ERR_HIP);
+  CHECK(vp_admit(h, 2, &b.cfg, b.parts, b.ws) == VP_OK);
+  check_step(h, {&a, &b});
+  vp_tuning t{256, 4, 2, 0, 33, 0, 0}, t2{1024, 2, 8, 0, 33, 0, 0};
+  CHECK(vp_set_tuning(h, &t) == VP_OK);
+  fail_at["launch_upload"] = 1;
+  CHECK(vp_set_tuning(h, &t2) == VP_ERR_HIP);
+  check_step(h, {&a, &b});
+  CHECK(vp_admit(h, 3, &c.cfg, c.parts, c.ws) == VP_OK);
+  check_step(h, {&a, &b, &c});
+  fail_at["launch_upload"] = 1;
+  CHECK(vp_retire(h, 1) == VP_ERR_HIP);
+  check_step(h, {&b, &c});
+  CHECK(vp_admit(h, 1, &a.cfg, a.parts, a.ws) == VP_OK);
+  check_step(h, {&a, &b, &c});
+  fail_at["launch_ring"] = 1;
+  CHECK(vp_set_tuning(h, &t2) == VP_ERR_HIP);
+  check_step(h, {&a, &b, &c});
+  CHECK(vp_set_tuning(h, &t2) == VP_OK);
+  check_step(h, {&a, &b, &c});
+  CHECK(vp_destroy(h) == VP_OK);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {{"no_pinned_memory", no_pinned_memory},
-                                                    {"large_tables", large_tables}};
+                                                    {"large_tables", large_tables},
+                                                    {"failed_upload", failed_upload}};
   if (argc == 2 && checks.count(argv[1])) {
     checks.at(argv[1])();
   } else {

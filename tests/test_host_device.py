@@ -24,7 +24,7 @@ def program(tmp_path_factory):
     return out
 
 
-CHECKS = ["no_pinned_memory", "large_tables"]
+CHECKS = ["no_pinned_memory", "large_tables", "failed_upload"]
 
 
 @pytest.mark.parametrize("check", CHECKS)
