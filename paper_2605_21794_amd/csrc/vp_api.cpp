@@ -354,29 +354,9 @@ vp_status read_back(vp_handle* h, const ReadPart* parts, int n) {
   return VP_OK;
 }
 
-// Rebuild the tile list and occupied-slot list from the slots and upload what changed in them,
-// with the parts already in u (the arena is reserved) and the instance table (slot `only`, or
-// every slot in use for -1).  The stream orders the upload behind the launches that read the
-// old tables; it is waited for only where graphs in flight have to be dropped.  fold: the tiles
-// or the number of accumulator copies of slots with a history may have changed (an admission
-// and a retirement leave the other slots' as they are).  After one that failed, everything is
-// sent and folded.
-vp_status rebuild_tables(vp_handle* h, vpk::UploadArgs u, int only, bool fold) {
-  if (h->tables_lost) {
-    only = -1;
-    fold = true;
-    h->up_tiles.clear();
-    h->up_occ.clear();
-  }
-  h->tables_lost = true;  // until it is done
-  bool graphs = h->gexec != nullptr;
-  for (int p = 0; p < vpk::kRing; ++p) graphs = graphs || h->step_exec[p];
-  if (graphs) VP_HIP(hipStreamSynchronize(h->stream));
-  drop_graph(h);
-  h->steps_since_tables = 0;
-  const int threads = threads_of(h);
-  if (threads != h->threads) fold = true;
-  h->threads = threads;
+// The tile list and the occupied-slot list of the slots, and what follows from them (host only).
+vp_status build_lists(vp_handle* h) {
+  h->threads = threads_of(h);
   h->ppt = 1;
   h->h_tiles.clear();
   h->h_occ.clear();
@@ -438,6 +418,31 @@ vp_status rebuild_tables(vp_handle* h, vpk::UploadArgs u, int only, bool fold) {
   h->nontemporal = bytes < kCachedLow || bytes > kCachedHigh;
   h->any_fft = false;
   for (int s : h->h_occ) h->any_fft = h->any_fft || h->slots[s].cfg.solver == VP_SOLVE_FFT;
+  return VP_OK;
+}
+
+// Rebuild the tile list and occupied-slot list from the slots and upload what changed in them,
+// with the parts already in u (the arena is reserved) and the instance table (slot `only`, or
+// every slot in use for -1).  The stream orders the upload behind the launches that read the
+// old tables; it is waited for only where graphs in flight have to be dropped.  fold: the tiles
+// or the number of accumulator copies of slots with a history may have changed (an admission
+// and a retirement leave the other slots' as they are).  After one that failed, everything is
+// sent and folded.
+vp_status rebuild_tables(vp_handle* h, vpk::UploadArgs u, int only, bool fold) {
+  if (h->tables_lost) {
+    only = -1;
+    fold = true;
+    h->up_tiles.clear();
+    h->up_occ.clear();
+  }
+  h->tables_lost = true;  // until it is done
+  bool graphs = h->gexec != nullptr;
+  for (int p = 0; p < vpk::kRing; ++p) graphs = graphs || h->step_exec[p];
+  if (graphs) VP_HIP(hipStreamSynchronize(h->stream));
+  drop_graph(h);
+  h->steps_since_tables = 0;
+  if (threads_of(h) != h->threads) fold = true;
+  VP_TRY(build_lists(h));
   if ((size_t)h->ntiles > h->tiles_cap) {
     VP_HIP(hipStreamSynchronize(h->stream));
     if (h->d_tiles) VP_HIP(hipFree(h->d_tiles));
@@ -467,6 +472,17 @@ vp_status rebuild_tables(vp_handle* h, vpk::UploadArgs u, int only, bool fold) {
   }
   h->tables_lost = false;
   return VP_OK;
+}
+
+// Back to the slots and the tuning as they are now, after a change of them that failed (`st`):
+// the host's lists without it, the device's tables before their next use.
+vp_status undone(vp_handle* h, vp_status st) {
+  const std::string keep = g_err;
+  h->tables_lost = true;
+  (void)build_lists(h);
+  (void)sync_stream(h);  // the caller's buffers are free again
+  g_err = keep;
+  return st;
 }
 
 // The device's tables are the host's (again).
@@ -902,11 +918,13 @@ vp_status vp_admit(vp_handle* h, int32_t slot, const vp_config* cfg, vp_particle
   const int ng = cfg->ng;
   const MeshTables& mt = mesh_tables(h, ng);
   const size_t tab_bytes = w.scal - w.tw;
-  const vp_status room = arena_reserve(h, tab_bytes);
-  if (room != VP_OK) {
+  auto refuse = [&](vp_status st) {
     sl.used = false;
-    return room;
-  }
+    h->h_inst[slot] = InstDev{};
+    return undone(h, st);
+  };
+  const vp_status room = arena_reserve(h, tab_bytes);
+  if (room != VP_OK) return refuse(room);
   char* tab = arena_take(h, tab_bytes);
   std::memset(tab, 0, tab_bytes);
   std::memcpy(tab, mt.tw.data(), ng * sizeof(double));
@@ -918,22 +936,20 @@ vp_status vp_admit(vp_handle* h, int32_t slot, const vp_config* cfg, vp_particle
   u.seg[u.nseg++] = {ws + w.tw, tab, tab_bytes / 8};
   u.zero[u.nzero++] = {ws, nullptr, w.tw / 8};
   u.zero[u.nzero++] = {ws + w.scal, nullptr, (w.total - w.scal) / 8};
-  if (cfg->monopole_only) {  // p* = q* = 0 from the start
-    const size_t bytes = (size_t)cfg->n * state_elem_size(cfg->precision);
-    VP_HIP(vpk::launch_fill_zero(parts.qs, bytes, h->stream));
-    VP_HIP(vpk::launch_fill_zero(parts.ps, bytes, h->stream));
-  }
-
-  vp_status st = rebuild_tables(h, u, slot, false);
-  if (st != VP_OK) {
-    sl.used = false;
-    (void)hipStreamSynchronize(h->stream);  // the caller's buffers are free again
-    return st;
-  }
-  // Load vector and field at t = 0 from the initial state (the ring entries start cleared).
-  VP_HIP(vpk::launch_deposit(h->precision, h->threads, h->d_inst, h->d_tiles, sl.tile_begin, sl.ntiles,
-                             h->ppt, h->max_ng, h->phase, h->stream));
-  return materialise_slot(h, slot);
+  auto place = [&]() -> vp_status {
+    if (cfg->monopole_only) {  // p* = q* = 0 from the start
+      const size_t bytes = (size_t)cfg->n * state_elem_size(cfg->precision);
+      VP_HIP(vpk::launch_fill_zero(parts.qs, bytes, h->stream));
+      VP_HIP(vpk::launch_fill_zero(parts.ps, bytes, h->stream));
+    }
+    VP_TRY(rebuild_tables(h, u, slot, false));
+    // Load vector and field at t = 0 from the initial state (the ring entries start cleared).
+    VP_HIP(vpk::launch_deposit(h->precision, h->threads, h->d_inst, h->d_tiles, sl.tile_begin,
+                               sl.ntiles, h->ppt, h->max_ng, h->phase, h->stream));
+    return materialise_slot(h, slot);
+  };
+  const vp_status st = place();
+  return st == VP_OK ? st : refuse(st);
 }
 
 vp_status vp_create(const vp_config* cfg, vp_particles parts, void* workspace, void* stream,
@@ -980,8 +996,9 @@ vp_status vp_retire(vp_handle* h, int32_t slot) {
   VP_TRY(sync_stream(h));
   sl.used = false;
   h->h_inst[slot] = InstDev{};
-  VP_TRY(arena_reserve(h, 0));
-  return rebuild_tables(h, vpk::UploadArgs{}, slot, false);
+  vp_status st = arena_reserve(h, 0);
+  if (st == VP_OK) st = rebuild_tables(h, vpk::UploadArgs{}, slot, false);
+  return st == VP_OK ? st : undone(h, st);
 }
 
 vp_status vp_destroy(vp_handle* h) {
@@ -1216,22 +1233,19 @@ vp_status vp_set_tuning(vp_handle* h, const vp_tuning* t) {
   h->tun = *t;
   h->tun.use_graph = t->use_graph ? 1 : 0;
   h->tun.persistent = t->persistent ? 1 : 0;
-  VP_TRY(arena_reserve(h, 0));
-  VP_TRY(rebuild_tables(h, vpk::UploadArgs{}, -1, true));
-  if (h->tun.persistent) {
+  vp_status st = arena_reserve(h, 0);
+  if (st == VP_OK) st = rebuild_tables(h, vpk::UploadArgs{}, -1, true);
+  if (st == VP_OK && h->tun.persistent) {
     const int cap = vpk::persist_capacity(h->precision, h->tun.threads, h->tun.ppt, h->max_ng,
                                           h->any_fft, any_general(h), any_p2(h));
-    if (h->ntiles > cap) {
-      const int need = h->ntiles;
-      h->tun = old;
-      h->tuned = old_tuned;
-      VP_TRY(arena_reserve(h, 0));
-      VP_TRY(rebuild_tables(h, vpk::UploadArgs{}, -1, true));
-      return fail(VP_ERR_ARG, "persistent steps need all %d workgroups resident; the device holds %d",
-                  need, cap);
-    }
+    if (h->ntiles > cap)
+      st = fail(VP_ERR_ARG, "persistent steps need all %d workgroups resident; the device holds %d",
+                h->ntiles, cap);
   }
-  return VP_OK;
+  if (st == VP_OK) return st;
+  h->tun = old;
+  h->tuned = old_tuned;
+  return undone(h, st);
 }
 
 vp_status vp_get_tuning(const vp_handle* h, vp_tuning* t) {

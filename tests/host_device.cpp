@@ -291,10 +291,56 @@ static void failed_upload() {
   CHECK(vp_destroy(h) == VP_OK);
 }
 
+// Whatever call of an admission fails, the slot stays empty and the others go on; a tuning that
+// fails leaves the one before.
+static void failed_admission() {
+  Instance a(5000), b(20000, 16, true);
+  for (const char* name : {"launch_fill_zero", "launch_upload", "launch_deposit", "launch_solve"})
+    for (int call = 1; call <= (std::string(name) == "launch_fill_zero" ? 2 : 1); ++call) {
+      vp_handle* h = nullptr;
+      CHECK(vp_engine_create(VP_FP64, 8, nullptr, &h) == VP_OK);
+      CHECK(vp_admit(h, 1, &a.cfg, a.parts, a.ws) == VP_OK);
+      check_step(h, {&a});
+      fail_at[name] = call;
+      CHECK(vp_admit(h, 2, &b.cfg, b.parts, b.ws) == VP_ERR_HIP);
+      CHECK(std::strstr(vp_last_error(), "made to fail") != nullptr);
+      int32_t slots = 0;
+      int64_t n = 0;
+      CHECK(vp_occupancy(h, &slots, &n) == VP_OK && slots == 1 && n == a.cfg.n);
+      CHECK(vp_retire(h, 2) == VP_ERR_STATE);
+      check_step(h, {&a});
+      check_reads(h, 1, 2);
+      CHECK(vp_admit(h, 2, &b.cfg, b.parts, b.ws) == VP_OK);
+      check_step(h, {&a, &b});
+      CHECK(vp_destroy(h) == VP_OK);
+    }
+  vp_handle* h = nullptr;
+  CHECK(vp_engine_create(VP_FP64, 8, nullptr, &h) == VP_OK);
+  CHECK(vp_admit(h, 1, &a.cfg, a.parts, a.ws) == VP_OK);
+  vp_tuning t{256, 4, 2, 0, 33, 0, 0}, bad{1024, 2, 8, 0, 33, 0, 0}, got{};
+  CHECK(vp_set_tuning(h, &t) == VP_OK);
+  fail_at["launch_upload"] = 1;
+  CHECK(vp_set_tuning(h, &bad) == VP_ERR_HIP);
+  CHECK(vp_get_tuning(h, &got) == VP_OK && std::memcmp(&got, &t, sizeof t) == 0);
+  int32_t th = 0, ppt = 0, k = 0;
+  CHECK(vp_step_launch(h, 1, 5, &th, &ppt, &k) == VP_OK && th == 256 && ppt == 4 && k == 1);
+  check_step(h, {&a});
+  bad.persistent = 1;
+  CHECK(vp_admit(h, 2, &b.cfg, b.parts, b.ws) == VP_OK);
+  Instance c(1 << 20);
+  CHECK(vp_admit(h, 0, &c.cfg, c.parts, c.ws) == VP_OK);  // 512 tiles and more: not all resident
+  CHECK(vp_set_tuning(h, &bad) == VP_ERR_ARG);
+  CHECK(std::strstr(vp_last_error(), "the device holds 256") != nullptr);
+  CHECK(vp_get_tuning(h, &got) == VP_OK && std::memcmp(&got, &t, sizeof t) == 0);
+  check_step(h, {&a, &b, &c});
+  CHECK(vp_destroy(h) == VP_OK);
+}
+
 int main(int argc, char** argv) {
   const std::map<std::string, void (*)()> checks = {{"no_pinned_memory", no_pinned_memory},
                                                     {"large_tables", large_tables},
-                                                    {"failed_upload", failed_upload}};
+                                                    {"failed_upload", failed_upload},
+                                                    {"failed_admission", failed_admission}};
   if (argc == 2 && checks.count(argv[1])) {
     checks.at(argv[1])();
   } else {

@@ -24,7 +24,7 @@ def program(tmp_path_factory):
     return out
 
 
-CHECKS = ["no_pinned_memory", "large_tables", "failed_upload"]
+CHECKS = ["no_pinned_memory", "large_tables", "failed_upload", "failed_admission"]
 
 
 @pytest.mark.parametrize("check", CHECKS)
