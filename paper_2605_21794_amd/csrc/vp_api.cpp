@@ -625,7 +625,8 @@ vp_status advance_persistent(vp_handle* h, int k) {
 // is small enough (resident_capacity), and there is more than one step to share the launch.
 bool steps_resident(const vp_handle* h, int k) {
   if (!by_size(h) || k < 2) return false;
-  const long long cap = vpk::resident_capacity(h->precision, any_general(h), any_p2(h));
+  const long long cap = vpk::resident_capacity(h->precision, any_general(h), any_p2(h),
+                                               (int)h->h_occ.size());
   for (int s : h->h_occ)
     if (h->slots[s].cfg.n > cap || h->h_inst[s].k3) return false;
   return true;

@@ -158,7 +158,7 @@ int persist_capacity(int mode, int tpb, int ppt, int max_ng, bool lds_fft, bool 
 // registers, load vector in LDS; no instance waits for another).  nmax: the largest instance, at
 // most resident_capacity; none with second moments.
 constexpr int kResidentThreads = 1024;
-long long resident_capacity(int mode, bool general, bool p2);
+long long resident_capacity(int mode, bool general, bool p2, int nslots);
 int resident_ppt(long long nmax);  // particles per thread
 hipError_t launch_resident(int mode, long long nmax, const InstDev* d_inst, const int* d_slots,
                            int nslots, int max_ng, bool lds_fft, bool general, bool p2, int phase,

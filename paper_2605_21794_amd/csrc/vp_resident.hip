@@ -216,11 +216,18 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(
 // 14.7 and 4096 18.4 / 14.7, the naive mode 1024 4.7 / 10.3 and 2048 12.5 / 10.5 (their LDS
 // updates are slow and one CU takes them all).  (Measured before wave_totals, which since took
 // 0.5 us off the resident steps and 0.2 off the fused.)
-long long resident_capacity(int mode, bool general, bool p2) {
+// One workgroup of 1024 threads fills a CU's registers, so more than 256 instances are taken in
+// rounds, where the fused step spreads its tiles.  256, 512, 1024 instances, resident against
+// 512 x 4 fused: float64 4096 particles 4.4 / 15.8, 8.7 / 29.6, 17 / 53; 200 particles 2.6 / 7.2,
+// 5.0 / 10, 9.8 / 17; with a prescribed potential 4096 10 / 19, 20 / 36, 38 / 64; float32 state
+// with float64 sums 8192 7.5 / 21, 15 / 36, 28 / 61; naive mode 1024 4.8 / 11, 9.6 / 17, 19 / 31.
+// Only the pairs turn, above 1024 particles: 2048 11 / 16, 22 / 20, 43 / 36 (300 instances 21 /
+// 18), 1500 9.1 / 14, 18 / 17, 36 / 31; 1024 6.8 / 12, 14 / 15, 27 / 26.
+long long resident_capacity(int mode, bool general, bool p2, int nslots) {
   switch (mode) {
     case kFP64: return 4LL * kResidentThreads;
     case kFP32Comp: return (general || p2 ? 4LL : 8LL) * kResidentThreads;
-    case kFP32TwoSum: return 2LL * kResidentThreads;
+    case kFP32TwoSum: return (nslots > 256 ? 1LL : 2LL) * kResidentThreads;
     default: return kResidentThreads;
   }
 }
@@ -251,7 +258,7 @@ hipError_t launch_resident(int mode, long long nmax, const InstDev* d_inst, cons
                            int nslots, int max_ng, bool lds_fft, bool general, bool p2, int phase,
                            int nsteps, hipStream_t s) {
   if (nslots <= 0 || nsteps <= 0) return hipSuccess;
-  if (nmax > resident_capacity(mode, general, p2) || (p2 && mode == kFP32))
+  if (nmax > resident_capacity(mode, general, p2, nslots) || (p2 && mode == kFP32))
     return hipErrorInvalidValue;
   const size_t lds = fused_lds_bytes(lds_fft, max_ng);
   const int ppt = resident_ppt(nmax);

@@ -139,7 +139,7 @@ hipError_t launch_diag(int, int, const InstDev* i, const Tile* t, int tile0, int
 }
 hipError_t launch_persist(int, int, int, const InstDev* i, const Tile* t, int n, int, bool, bool, bool, int, int, hipStream_t) { return tiles("launch_persist", i, t, 0, n); }
 int persist_capacity(int, int, int, int, bool, bool, bool) { return 256; }
-long long resident_capacity(int, bool, bool) { return 4096; }
+long long resident_capacity(int, bool, bool, int) { return 4096; }
 int resident_ppt(long long) { return 4; }
 hipError_t launch_resident(int, long long, const InstDev*, const int*, int, int, bool, bool, bool, int, int, hipStream_t) { return hipErrorUnknown; }
 static hipError_t slots(const char* name, const InstDev* insts, const int* s, int first, int n) {
