@@ -85,7 +85,8 @@ typedef struct vp_config {
                             comparison method and the k = 1 member of the hierarchy).  Admission
                             fills qs and ps with zeros; the fused step then neither reads nor
                             writes them (20 bytes of particle traffic per update instead of
-                            36); the other calls carry the zeros through, and they stay zero.
+                            36); the other calls, and steps that keep particles on chip from one
+                            to the next, carry the zeros through, and they stay zero.
                             0: decorated particles (default). */
   int32_t no_self_field; /* 1: the particles feel no field of their own (charge e = 0; the
                             paper's test-particle example, eq. swpic_test_particle): the load
@@ -294,8 +295,10 @@ vp_status vp_gather_push(vp_handle* h, double kick, double drift);
  * field of the current positions from the load vector the
  * previous step deposited, then runs its particles through the pending half-kick, the
  * diagnostics at the integer step, the half-kick, the drift and the deposit of the new
- * load vector; optionally replayed from captured HIP graphs.  Equals the primitive
- * composition up to rounding.  Leaves a pending half-kick (P, q* at t + dt/2); every state
+ * load vector; optionally replayed from captured HIP graphs.  Where the launch shapes are chosen
+ * by size (vp_tuning) and every instance fits one workgroup, a call of two steps or more runs up
+ * to 1024 of them per launch, one workgroup per instance with its particles in registers.  Equals
+ * the primitive composition up to rounding.  Leaves a pending half-kick (P, q* at t + dt/2); every state
  * read-back must go through vp_sync_state, vp_retire or vp_diagnostics (which accounts for
  * it).  With vp_tuning.persistent, up to 1024 steps run in one cooperative launch whose
  * workgroups keep their particles in registers and wait for one another between steps;
@@ -403,8 +406,10 @@ vp_status vp_slot_status(vp_handle* h, int32_t n, int64_t* host_steps, int32_t* 
  * each; init_idx: k marker indices in [0, m) (device int32; checked on the host,
  * VP_ERR_ARG if out of range; normally distinct: a repeated index starts two centres at
  * one place, and the higher-numbered one gets no markers in the first assignment).  1 <= k <= m < 2^31, iters >= 0, L > 0.
- * workspace: vp_cluster_workspace_bytes(m, k) bytes of device memory, 256-byte aligned.
- * Outputs (device, float64, capacity k each): Q, P, qs (q*), ps (p*), psi of the non-empty
+ * workspace: vp_cluster_workspace_bytes(m, k) bytes of device memory, 256-byte aligned (never
+ * less for more markers or clusters: one of the largest call serves the smaller ones).
+ * Outputs (device, float64, capacity k each, written once the inputs have been read): Q, P, qs
+ * (q*), ps (p*), psi of the non-empty
  * clusters; assign_out (device int32, m, or NULL): final cluster of each marker;
  * *n_out (host): the number of decorated particles written.  Runs on `stream` (a
  * hipStream_t, or NULL) and synchronises it.  Errors: VP_ERR_ARG, VP_ERR_HIP. */
@@ -447,7 +452,8 @@ vp_status vp_cluster_markers_static(const double* Qm, const double* Pm, const do
  * after its iterations: a final assignment of every marker and one decorated particle per
  * non-empty cluster.  Arguments as for vp_cluster_markers, plus: 1 <= batch <= m,
  * nbatch >= 1, batch * nbatch < 2^31; workspace of
- * vp_cluster_minibatch_workspace_bytes(m, k, batch) bytes; absorbed_out (device float64,
+ * vp_cluster_minibatch_workspace_bytes(m, k, batch) bytes (never less for more of either);
+ * absorbed_out (device float64,
  * k, or NULL) receives each centre's v.  Every batch index is checked on the device before
  * use (VP_ERR_ARG if any lies outside [0, m)).  Synchronises the stream.  Errors:
  * VP_ERR_ARG, VP_ERR_HIP. */

@@ -47,7 +47,7 @@ vp_status fail(vp_status s, const char* fmt, ...) {
     if (s_ != VP_OK) return s_;   \
   } while (0)
 
-constexpr int kGroups = 10;       // kinds of tiles, one fused launch each (see rebuild_tables)
+constexpr int kGroups = 10;       // kinds of tiles, one fused launch each (see build_lists)
 constexpr int kGroupMoments = 8;  // the two kinds of instances with second moments
 constexpr int kDefaultCopies = 4;  // accumulator copies of a handle that was never tuned
 
@@ -129,7 +129,7 @@ struct MeshTables {
 // The scalars of an instance that the host reads: what lies before the barrier's counters.
 static_assert(sizeof(InstDev) % 8 == 0 && sizeof(Tile) % 8 == 0, "uploaded in 64-bit words");
 constexpr size_t kScalHead = offsetof(vpk::InstScal, arrive);
-constexpr size_t kCachedLow = 56u << 20, kCachedHigh = 256u << 20;  // see rebuild_tables
+constexpr size_t kCachedLow = 56u << 20, kCachedHigh = 256u << 20;  // see build_lists
 // Pinned staging of the table uploads and read-backs: what is taken first, and the most.  An upload
 // above that, or where pinned memory is not to be had, goes by plain copies.
 constexpr size_t kArenaBytes = 256u << 10, kArenaMax = 4u << 20;
@@ -158,7 +158,6 @@ struct vp_handle {
   MeshTables mesh[11];        // by log2 of ng, made when first needed
   long long steps_since_tables = 0;  // steps run since the tables last changed
   int ntiles = 0;
-  int ntiles_dip = 0;      // tiles of decorated instances
   // tile ranges by kind: decorated / monopole-only x P1 / P2 x without / with general
   // options, then the instances with second moments
   int group_end[kGroups] = {};
@@ -213,15 +212,15 @@ bool by_size(const vp_handle* h) { return h->tun.threads == 0; }
 // Particles per thread of a slot's tiles: the tuning's where one was set; by default, at 512
 // threads, 4 while every tile is resident at once (two workgroups to a CU for the float64 state,
 // three for the float32 ones), 8 above, and 16 for the largest float32 states.  us a step at
-// 512 x 4, x 8, x 16 and, before, 1024 x 4 (Ng 512, 4 copies; the accesses as rebuild_tables
-// picks them): float32 state with float64 sums 2^17 8.1, 10.0, -, 9.6; 2^20 10.9, 11.3, 15.2,
-// 10.6 (11.0 against 10.25 with a ragged tail); 3 * 2^19 13.1, 14.3, 15.9, -; 2^21 18.2, 16.1,
-// 17.7, 19.0; 7 * 2^19 27.8, 26.3, 24.9, -; 2^22 31.2, 27.3, 27.2, 39.0; 2^23 54.2, 50.2, 50.4,
-// 70.7 (2^22 P2 41.0, 34.2, 31.1, 43.6; without dipoles -, 19.9, 18.8, 26.4); float64 2^18 8.8,
-// 11.3, -, 10.8; 2^20 14.0, 16.2, 22.6, 15.5; 3 * 2^19 22.7, 21.0, 22.5, -; 2^22 49.9, 47.2,
-// 49.1, 59.1.  Particles with second moments, whose push is longer: 2 up to 2^19 (512 x 2, x 4,
-// x 8; float32 state: 2^18 9.4, 11.0, 14.3; 2^19 11.1, 11.5, 14.6; 2^20 19.0, 15.5, 16.5; 2^21
-// 35.1, 28.9, 27.1), 4 up to 2^20 and 8 above.
+// 512 x 4, x 8, x 16 and 1024 x 4 (Ng 512, 4 copies; the accesses as build_lists picks them):
+// float32 state with float64 sums 2^17 7.5, 9.4, 13.1, 8.8; 2^20 10.6, 11.1, 14.9, 10.0 (10.3 and
+// 10.0 on another card; 10.1 and 10.0 with a ragged tail); 3 * 2^19 12.5, 14.0, 15.7, 17.1; 2^21
+// 17.9, 15.9, 17.5, 18.2; 7 * 2^19 27.1, 25.3, 24.2, 33.2; 2^22 30.1, 28.5, 26.8, 34.9; 2^23 53.7,
+// 49.4, 52.6, 71.6 (2^22 P2 39.8, 32.8, 29.7, 42.0; without dipoles 23.4, 19.7, 18.4, 25.4);
+// float64 2^18 8.3, 10.7, 15.3, 10.2; 2^20 13.8, 16.3, 22.1, 15.1; 3 * 2^19 23.3, 20.2, 22.4, 27.0;
+// 2^22 49.0, 47.3, 47.5, 59.3.  Particles with second moments, whose push is longer: 2 up to 2^19
+// (512 x 2, x 4, x 8; float32 state: 2^18 9.0, 10.2, 13.4; 2^19 10.8, 11.3, 14.5; 2^20 18.7, 15.2,
+// 16.0; 2^21 34.8, 26.7, 24.1), 4 up to 2^20 and 8 above.
 int ppt_of(const vp_handle* h, const vp_config& c) {
   if (!by_size(h)) return h->tun.ppt;
   if (c.moment_order == 3) return c.n <= 1LL << 19 ? 2 : c.n <= 1LL << 20 ? 4 : 8;
@@ -376,7 +375,6 @@ vp_status build_lists(vp_handle* h) {
   for (int gi = 0; gi < kGroups; ++gi)
     for (int s : h->h_occ)
       if (group_of(s) == gi) order.push_back(s);
-  h->ntiles_dip = 0;
   for (int gi = 0; gi < kGroups; ++gi) h->group_end[gi] = 0;
   for (int s : order) {
     Slot& sl = h->slots[s];
@@ -401,7 +399,6 @@ vp_status build_lists(vp_handle* h) {
     d.acc_copies = std::max(1, std::min(h->tun.acc_copies, nt));
     d.seg = h->tun.wave_reduce;
     d.spin_limit = h->spin_limit;
-    if (!sl.cfg.monopole_only) h->ntiles_dip += nt;
     for (int gi = group_of(s); gi < kGroups; ++gi) h->group_end[gi] += nt;
   }
   h->ntiles = (int)h->h_tiles.size();

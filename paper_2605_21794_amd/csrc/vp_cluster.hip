@@ -386,7 +386,9 @@ __device__ __forceinline__ int nearest_centre(
     lim = fmin(lim, best);
   };
   // Distances to cell edges are taken smaller by a millionth of a cell, far above the rounding
-  // of the cell coordinates: a cell is left out only when it lies farther for certain.
+  // of the cell coordinates: a cell is left out only when it lies farther for certain.  (Also
+  // where pmin is so large that pmin + y sp rounds by more: rounding is monotone, so the rounded
+  // edge still has each row's centres, which are doubles, on its side.)
   const double mx = 1e-6 * g.sx, my = 1e-6 * g.sp;
   auto low = [](double d, double margin) { return fmax(0.0, d - margin); };
   auto row_gap = [&](int y) {

@@ -70,11 +70,6 @@ __device__ __forceinline__ T ldx(VPG T* p) {
   if constexpr (DEV) return gld(p);
   else return *p;
 }
-template <bool DEV, typename T>
-__device__ __forceinline__ void stx(VPG T* p, T v) {
-  if constexpr (DEV) gst(p, v);
-  else *p = v;
-}
 
 // Streaming access to the particle arrays: every element is read and written once per step,
 // so the loads and stores are marked non-temporal (they do not displace cached grid data).
@@ -473,11 +468,6 @@ __device__ __forceinline__ void wave_sum_n(double (&v)[N]) {
   for (int i = 0; i < N; ++i)
     v[i] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(t), wave_totals_lane(i)),
                             __builtin_amdgcn_readlane(__double2loint(t), wave_totals_lane(i)));
-}
-
-// Exclusive prefix over lanes of one value per lane.
-__device__ __forceinline__ double wave_excl_scan(double v, int /*lane*/) {
-  return wave_incl_scan(v) - v;
 }
 
 struct Cplx { double re, im; };
