@@ -461,7 +461,7 @@ __device__ __forceinline__ int nearest_centre(
 // cluster (cnt), and slot receives the count before it; else q, p and assign are in marker order,
 // reached through perm.  prev: assign holds the previous iteration's labels.
 // Bound by the latency of the list and centre loads from L2 (finer grids, with fewer centres to
-// compare, are no faster).  4194304 markers and 419430 centres, ten markers a centre: 148 us a
+// compare, are no faster).  4194304 markers and 419430 centres, ten markers a centre: 140 us a
 // pass, against 1515 us with cell lists read through two indirections, square rings searched cell
 // by cell and the clusters counted in a pass of their own (159 us).
 // RUNS: a workgroup counts its markers per label in an LDS table and adds each label's count to
