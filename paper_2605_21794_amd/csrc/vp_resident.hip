@@ -187,6 +187,23 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(
         gp(d.acc)[acc_off(d, ring_next(rf), c) + j] = 0.0;
       }
     }
+  __syncthreads();  // the last wavefront's verdict
+  if ((stop & 3) || (nonfinite & 2)) {
+    // Frozen, while the engine's phase goes on: a read-back may come at the entry that the last
+    // pass solved, so its load is put back there (from b~, and for P2 from g: see solve_compute).
+    const double mean = solve_total(sred, 0) * inv_pow2(d.log2ng);
+    for (int c = 0; c < copies; ++c)
+      for (int j = tid; j < nacc; j += TPB) {
+        double x = 0.0;
+        if (c == 0) {
+          auto mid = [&](int e) { return (2.0 / 3.0) * mean - fG[e & (ng - 1)] / (1.5 * d.inv_h); };
+          if (!(P2 && d.order == 2)) x = bt[j] + mean;
+          else x = j >= ng ? mid(j) : (bt[j] + mean) - 0.5 * (mid(j - 1) + mid(j));
+        }
+        if constexpr (MODE == kFP32) gp<float>(d.acc)[acc_off(d, rl, c) + j] = (float)x;
+        else gp(d.acc)[acc_off(d, rl, c) + j] = x;
+      }
+  }
   if (wid == kWaves - 1) {
     VPG double* kin = gp(d.kin) + (size_t)rl * d.kin_cap * kKinFields;
     for (int t = lane; t < d.ntiles * kKinFields; t += 64)
@@ -195,7 +212,9 @@ __global__ __launch_bounds__(kResidentThreads) void k_resident(
     if (lane == 4) {
       sc->W[rl] = tot;
       sc->step = step0 + done;
-      sc->pend[rf] = 1;
+      sc->pend[rf] = 1;  // and those of the passes before, as each pass sets its next
+      if (done > 1) sc->pend[rl] = 1;
+      if (done > 2) sc->pend[ring_next(rf)] = 1;
       if (!isfinite(tot) || (stop & 3)) sc->nonfinite = 1;
     }
     if (lane == 5) sc->e1r[rl] = tot;

@@ -10,9 +10,9 @@ FIELDS = ("Q", "P", "qs", "ps")
 
 
 def both(vp, st, L, ng, dt, first, **opt):
-    """(statuses after `first` and eight more steps, records, state as stepped) of either.  The
-    record of the step an instance froze at is left out: reading it solves the field of a ring
-    entry the frozen instance did not reach."""
+    """(statuses after `first` and eight more steps, records, state as stepped, diagnostics) of
+    either.  The record of the step an instance froze at is left out: reading it solves the field
+    of a ring entry the frozen instance did not reach."""
     runs = []
     for tuned in (False, True):
         sim = vp.Simulation(st, L, ng, dt, "fp64", hist_cap=32, **opt)
@@ -24,7 +24,12 @@ def both(vp, st, L, ng, dt, first, **opt):
             steps.append(sim.slot_status()[0])
         n = steps[-1][0]
         state = {f: sim.state(0)[f].cpu().numpy() for f in FIELDS}
-        runs.append((steps, sim.history_array(0, 0, n - 1, allow_nonfinite=True), state))
+        rec = sim.history_array(0, 0, n - 1, allow_nonfinite=True)
+        diag = []
+        for k in (0, 1, 1):       # the engine's phase goes on: each entry of the ring in turn
+            sim.step(k)
+            diag.append(sim.diagnostics(0, grid=True, allow_nonfinite=True))
+        runs.append((steps, rec, state, diag))
         sim.close()
     return runs
 
@@ -32,7 +37,7 @@ def both(vp, st, L, ng, dt, first, **opt):
 def agree(runs, momentum):
     """`momentum`: the sum of the particles' |psi P|, the scale of the momentum's sum (which may
     cancel)."""
-    (sa, ra, ga), (sb, rb, gb) = runs
+    (sa, ra, ga, da), (sb, rb, gb, db) = runs
     assert sa == sb
     for f in ("K", "W", "U", "charge", "momentum"):
         fin = np.isfinite(rb[f])
@@ -41,6 +46,14 @@ def agree(runs, momentum):
         assert np.all(np.abs(ra[f][fin] - rb[f][fin]) <= 1e-12 * scale), f
     for f in FIELDS:
         assert np.max(np.abs(ga[f] - gb[f])) <= 1e-12 * np.max(np.abs(gb[f])), f
+    for k, (x, y) in enumerate(zip(da, db)):
+        assert x["step"] == y["step"], k
+        for f in ("W", "K"):          # K counts the half-kick pending at that entry
+            assert np.isfinite(x[f]) == np.isfinite(y[f]), (k, f)
+            assert not np.isfinite(y[f]) or abs(x[f] - y[f]) <= 1e-10 * abs(y[f]), (k, f)
+        for f in ("bt", "E"):
+            scale = max(np.max(np.abs(y[f])), 1e-300)
+            assert np.max(np.abs(x[f] - y[f])) <= 1e-10 * scale, (k, f)
 
 
 @pytest.mark.parametrize("opt,ng", [({}, 32), ({}, 512), ({"solver": "fft"}, 64),
@@ -58,7 +71,7 @@ def test_overflowing_field_energy(vp, opt, ng, first):
     st = {"Q": q, "P": 1e74 * np.sin(2 * np.pi * q / L), "qs": np.zeros(n), "ps": np.zeros(n),
           "psi": np.full(n, charge / n)}
     runs = both(vp, st, L, ng, dt, first, **opt)
-    (steps, rec, _) = runs[1]
+    steps, rec = runs[1][:2]
     assert 3 < steps[-1][0] < 10 and not steps[-1][1]    # the fused steps froze on the way
     assert np.all(np.isfinite(rec["K"])) and np.all(np.isfinite(rec["W"]))
     agree(runs, charge * 1e74)
@@ -75,7 +88,7 @@ def test_overflowing_kinetic_energy(vp, first):
           "psi": np.full(n, 2 * 0.9 * (1.797e308 / P / P) / n)}
     amp = 0.02 * P / dt / (2 * np.pi / L)
     runs = both(vp, st, L, 64, dt, first, external={"amp": amp, "mode": 1})
-    steps, rec, _ = runs[1]
+    steps, rec = runs[1][:2]
     assert np.isfinite(rec["K"][0]) and not np.isfinite(rec["K"][-1]) and np.all(np.isfinite(rec["W"]))
     assert steps[-1] == (5, False)     # found in the fifth pass, which still ran
     agree(runs, 2 * 1.8e308 / P)
